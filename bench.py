@@ -243,10 +243,11 @@ def cpu_baseline(pd, plan, W, target_s=12.0):
 
 
 def dedisp_source_hash():
-    """SHA-256 over what the dedispersion kernel is compiled from, in a fixed order: its
-    section of kernels.hip (from the dedispersion banner to the next kernel's), the
-    staging-depth constant of kernels.h, and the headers that define its descriptors
-    and device helpers.  Edits to the other kernels leave it unchanged."""
+    """SHA-256 over what the dedispersion kernels are compiled from, in a fixed order: the
+    row-staging kernel's section of kernels.hip (from the dedispersion banner to the next
+    kernel's), the staging-depth constant of kernels.h, the shared-row kernel and its
+    tables, and the headers that define the descriptors and device helpers.  Edits to the
+    other kernels leave it unchanged."""
     import hashlib
     import re
     csrc = os.path.join(ROOT, "paper_2606_27262_amd", "csrc")
@@ -257,7 +258,7 @@ def dedisp_source_hash():
     h.update(src[i:j].encode())
     h.update("\n".join(re.findall(r"^constexpr int dedisp_stage_rows.*$", open(os.path.join(csrc, "kernels.h")).read(),
                                    re.M)).encode())
-    for f in ("spl_internal.h", "spl_device.h"):
+    for f in ("dedisp_shared.hip", "shared_sums.h", "shared_sums.cpp", "spl_internal.h", "spl_device.h"):
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()
 

@@ -297,7 +297,10 @@ spl_status spl_batch_moments(const spl_batch *batch, int32_t beam, const int64_t
  * CU with other workgroups, and the whole LDS for 16).  With two LDS buffers (16-wavefront tiles
  * only) the next chunk is staged while the current one is summed.  The compiled shapes
  * (dm_per_wave, time_groups, waves[, buffers]): (2,2,8) (4,1,4) (4,2,4) (4,1,8) (4,2,8)
- * (8,1,4) (8,1,8), and (4,1,16) (4,2,16) (2,2,16) with one or two buffers. */
+ * (8,1,4) (8,1,8), and (4,1,16) (4,2,16) (2,2,16) with one or two buffers.
+ * With 16 wavefronts, a plan whose trials share the delay patterns of adjacent channels
+ * is summed by a kernel that forms those channels' sums once per tile (the same integers;
+ * its tile extents and staging are its own, and the other fields take no effect). */
 typedef struct spl_tiles {
     int32_t dm_per_wave;
     int32_t time_groups;
@@ -589,6 +592,12 @@ spl_status spl_inject_quantised(uint8_t *d_block, int64_t pitch, int64_t n_t, in
  * arrays n, s1, s2 (n > 0, s1 >= 0, s2 >= 0) into double device arrays. */
 spl_status spl_debug_mu_sigma(const int64_t *d_n, const int64_t *d_s1, const int64_t *d_s2, int64_t count,
                               double *d_mu, double *d_sigma, hipStream_t stream);
+
+/* The delays [ndm][nchans] that the shared-row tables of a beam encode, decoded on the
+ * host: equal to spl_plan_delays when the tables are right; -1 where a (trial, channel)
+ * is summed by no row, -2 where twice or out of its buffer.  SPL_E_UNSUPPORTED when the
+ * beam's tiling stages single channels. */
+spl_status spl_debug_shared_delays(const spl_batch *batch, int32_t beam, int32_t *host_out);
 
 /* Device view of the max-pool decisions of conv layer `layer` (0..3) of the ranker's
  * last pass, for parity tests: bytes [Nb][H/2][W/2][32] (Nb = max_batch rounded up to

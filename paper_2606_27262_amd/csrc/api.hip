@@ -16,6 +16,7 @@
 #include "inject.h"
 #include "kernels.h"
 #include "ranker.h"
+#include "shared_sums.h"
 #include "spl_internal.h"
 #include "spotlight.h"
 
@@ -236,12 +237,16 @@ struct Tiles {
 struct PlanLayout {
     const spl_plan *plan = nullptr;
     Tiles tiles;
-    int td = 0, ndm_pad = 0, ntile_d = 0, ntile_t = 0;
-    std::vector<int32_t> dcm;        // delays [nch][ndm_pad]
+    int td = 0, ndm_pad = 0;         // of the row-staging tile
+    int tile_trials = 0, tile_samples = 0, ntile_d = 0, ntile_t = 0;   // of the work items
     std::vector<int32_t> dtab;       // LDS byte offsets [nch][ndm_pad]
     int quarter = 0;                 // bytes per shifted copy of the staged rows
-    std::vector<int32_t> tile_base;  // [ntile_d][nch]
-    std::vector<int32_t> row_bytes;  // [ntile_d]
+    std::vector<int32_t> tile_base;  // [ndm_pad / td][nch]
+    std::vector<int32_t> row_bytes;  // [ndm_pad / td]
+    // the shared-row form of the tiling (16-wavefront tiles of plans whose delays allow it)
+    bool shared = false;
+    bool shared_tried = false;       // sh was built, or found not to pay, for this plan
+    SharedTables sh;                 // sh.ntiles = 0: row staging
     size_t off_dcm = 0, off_base = 0, off_dms = 0, off_delays = 0;
 };
 
@@ -266,7 +271,20 @@ struct spl_batch {
     int max_nst = 0, w_max = 0;
     std::vector<DedispItem> items;
     // shape groups for the persistent launch
-    struct Group { int dw, j, nw, sv, nb; int item_lo, item_hi; size_t lds; int occ; };
+    struct Group {
+        Tiles tiles;
+        bool shared = false;
+        SharedShape shape;
+        int item_lo = 0, item_hi = 0;
+        size_t lds = 0;
+        int occ = 0;
+        bool holds(const PlanLayout &L) const {
+            if (shared != L.shared) return false;
+            if (shared) return shape == L.sh.shape;
+            const Tiles &t = L.tiles;
+            return t.dw == tiles.dw && t.j == tiles.j && t.nw == tiles.nw && t.sv == tiles.sv && t.nb == tiles.nb;
+        }
+    };
     std::vector<Group> groups;
     std::vector<size_t> beam_lds;          // per beam (plain per-beam launches)
     // workspace
@@ -306,6 +324,36 @@ struct spl_batch {
     bool tables_uploaded = false;
 };
 
+// Clocks of a CU per added sample of the row-staging kernel (measured: 53 of 64 lanes add
+// in a clock on the 4096-channel band, 37 on the 2048-channel 300-500 MHz band).
+static constexpr double kRowAddsPerClock = 50.0;
+
+// Reserved bytes of a plan's offset table: room for the widest padding (64 trials).
+static size_t table_bytes(const spl_plan &p) {
+    return (size_t)p.nch * ((p.ndm + 63) / 64 * 64) * sizeof(int32_t);
+}
+
+// The plan's shared-row tables, built on first use; false when the plan's delays have too
+// little in common: a modelled tile must take fewer clocks than row staging needs.
+static bool shared_tables(PlanLayout &L) {
+    if (!L.shared_tried) {
+        L.shared_tried = true;
+        const spl_plan &p = *L.plan;
+        static const SharedShape shapes[] = {{4, 8, 8, 3}};
+        double best = (double)p.ndm * p.nch / kRowAddsPerClock;   // clocks per output sample
+        for (const SharedShape &s : shapes) {
+            SharedTables t;
+            if (!build_shared(p.delays.data(), p.ndm, p.nch, s, table_bytes(p), &t)) continue;
+            const double c = t.clocks / (2 * s.half());
+            if (c < best) {
+                best = c;
+                L.sh = std::move(t);
+            }
+        }
+    }
+    return L.sh.ntiles > 0;
+}
+
 static spl_status layout_plan(PlanLayout &L) {
     const spl_plan &p = *L.plan;
     if (!dedisp_shape_supported(L.tiles.dw, L.tiles.j, L.tiles.nw, 1, L.tiles.nb))
@@ -315,31 +363,31 @@ static spl_status layout_plan(PlanLayout &L) {
     if (L.tiles.cc < 0 || L.tiles.cc > cc_max)
         return fail(SPL_E_UNSUPPORTED, "chan_chunk must be in [0, %d] for %d wavefronts and %d LDS buffer(s)", cc_max,
                     L.tiles.nw, L.tiles.nb);
+    L.shared = L.tiles.nw == 16 && shared_tables(L);
     L.td = L.tiles.nw * L.tiles.dw;
     L.ndm_pad = (p.ndm + L.td - 1) / L.td * L.td;
-    L.ntile_d = L.ndm_pad / L.td;
+    const int nt = L.ndm_pad / L.td;
     const int TT = 256 * L.tiles.j;
-    L.ntile_t = (p.n_dd + TT - 1) / TT;
-    L.dcm.assign((size_t)p.nch * L.ndm_pad, 0);
-    for (int c = 0; c < p.nch; ++c)
-        for (int d = 0; d < L.ndm_pad; ++d) {
-            const int ds = std::min(d, p.ndm - 1);   // pad by repeating the last trial
-            L.dcm[(size_t)c * L.ndm_pad + d] = p.delays[(size_t)ds * p.nch + c];
-        }
-    L.tile_base.assign((size_t)L.ntile_d * p.nch, 0);
-    L.row_bytes.assign(L.ntile_d, 0);
-    for (int k = 0; k < L.ntile_d; ++k) {
-        int span = 0;
-        for (int c = 0; c < p.nch; ++c) {
-            int lo = INT32_MAX, hi = 0;
-            for (int d = k * L.td; d < (k + 1) * L.td; ++d) {
-                const int v = L.dcm[(size_t)c * L.ndm_pad + d];
-                lo = std::min(lo, v);
-                hi = std::max(hi, v);
+    // smallest and largest delay of every channel over each DM tile (the last trial is
+    // repeated up to the tile's end, which changes neither)
+    L.tile_base.assign((size_t)nt * p.nch, 0);
+    L.row_bytes.assign(nt, 0);
+    std::vector<int32_t> most(p.nch);
+    for (int k = 0; k < nt; ++k) {
+        int32_t *lo = L.tile_base.data() + (size_t)k * p.nch;
+        const int d1 = std::min(p.ndm, (k + 1) * L.td);
+        const int32_t *row = p.delays.data() + (size_t)k * L.td * p.nch;
+        std::copy(row, row + p.nch, lo);
+        std::copy(row, row + p.nch, most.begin());
+        for (int d = k * L.td + 1; d < d1; ++d) {
+            row += p.nch;
+            for (int c = 0; c < p.nch; ++c) {
+                lo[c] = std::min(lo[c], row[c]);
+                most[c] = std::max(most[c], row[c]);
             }
-            L.tile_base[(size_t)k * p.nch + c] = lo;
-            span = std::max(span, hi - lo);
         }
+        int span = 0;
+        for (int c = 0; c < p.nch; ++c) span = std::max(span, most[c] - lo[c]);
         // one copy of a staged row: 8-bit samples covering the tile's time span, its
         // spread of delays and 16-sample alignment slack
         L.row_bytes[k] = TT + 32 + (int)align_up((size_t)span, 16);
@@ -349,6 +397,10 @@ static spl_status layout_plan(PlanLayout &L) {
     if (rmax > 2048 || !dedisp_shape_supported(L.tiles.dw, L.tiles.j, L.tiles.nw, L.tiles.sv, L.tiles.nb))
         return fail(SPL_E_UNSUPPORTED, "a DM tile spans %d bytes of staged row: too wide for this tile shape "
                     "(use fewer trials per tile)", rmax);
+    L.tile_trials = L.shared ? L.sh.shape.td() : L.td;
+    L.tile_samples = L.shared ? 2 * L.sh.shape.half() : TT;
+    L.ntile_d = (p.ndm + L.tile_trials - 1) / L.tile_trials;
+    L.ntile_t = (p.n_dd + L.tile_samples - 1) / L.tile_samples;
     return SPL_OK;
 }
 
@@ -372,7 +424,7 @@ static bool tile_fits(const spl_plan &p, int td, int j) {
     return 256 * j + 32 + (int)align_up((size_t)worst + 64, 16) <= 2048;
 }
 
-static Tiles default_tiles(const spl_plan &p) {
+static Tiles default_row_tiles(const spl_plan &p) {
     static const int shapes[][3] = {{4, 2, 8}, {4, 1, 8}, {2, 2, 8}, {4, 1, 4}};   // (trials/wave, groups, waves)
     for (const auto &sh : shapes) {
         Tiles t;
@@ -392,6 +444,34 @@ static Tiles default_tiles(const spl_plan &p) {
     return t;
 }
 
+// The 16-wavefront tiles where shared rows are modelled to take less time than the row
+// staging of the tiles above on the whole chip (tiles per CU, rounded up, times the clocks
+// of one): a few large tiles leave CUs idle that many small ones would fill.
+static Tiles default_tiles(PlanLayout &L, int64_t beams) {
+    const spl_plan &p = *L.plan;
+    const Tiles row = default_row_tiles(p);
+    if (!shared_tables(L)) return row;
+    auto rounds = [&](int td, int tt) {
+        const int64_t n = beams * ((p.ndm + td - 1) / td) * ((p.n_dd + tt - 1) / tt);
+        return (double)((n + 255) / 256);
+    };
+    const int td = row.dw * row.nw, tt = 256 * row.j, ts = 2 * L.sh.shape.half();
+    const double by_row = rounds(td, tt) * ((double)td * tt * p.nch / kRowAddsPerClock);
+    const double by_sums = rounds(L.sh.shape.td(), ts) * (L.sh.clocks / L.sh.ntiles);
+    if (by_sums < by_row) {
+        static const int shapes[][2] = {{4, 2}, {2, 2}, {4, 1}};
+        for (const auto &sh : shapes) {
+            if (!tile_fits(p, 16 * sh[0], sh[1])) continue;
+            Tiles t;
+            t.dw = sh[0];
+            t.j = sh[1];
+            t.nw = 16;
+            return t;
+        }
+    }
+    return row;
+}
+
 // Channels per staging step: the largest power of two <= 256 whose four shifted copies
 // and offset table (in each LDS buffer) fit the LDS budget (a caller-set value is rounded
 // down to a power of two).  Then the table of LDS byte offsets of every delay.
@@ -408,25 +488,34 @@ static void choose_chunk(PlanLayout &L, size_t lds_budget) {
     while (p2 * 2 <= std::min(cc, 256)) p2 *= 2;
     L.tiles.cc = p2;
     L.quarter = (p2 + 1) * rmax;   // chan_chunk rows + the zero row
+    L.dtab.clear();
+    if (L.shared) return;
     const spl_plan &p = *L.plan;
-    L.dtab.assign(L.dcm.size(), 0);
-    for (int c = 0; c < p.nch; ++c) {
+    L.dtab.resize((size_t)p.nch * L.ndm_pad);
+    constexpr int kBlock = 32;   // channels by trials, transposed in blocks that stay in cache
+    for (int c0 = 0; c0 < p.nch; c0 += kBlock) {
+        const int c1 = std::min(p.nch, c0 + kBlock);
         for (int d = 0; d < L.ndm_pad; ++d) {
-            const size_t k = (size_t)c * L.ndm_pad + d;
-            const int sv = L.dcm[k];
-            // the row of channel c in DM tile d/td starts at sample t0 + (base & ~15)
-            const int b16 = L.tile_base[(size_t)(d / L.td) * p.nch + c] & ~15;
-            L.dtab[k] = ((sv - b16) & ~3) + (sv & 3) * L.quarter;
+            // pad by repeating the last trial; the row of channel c in DM tile d/td starts
+            // at sample t0 + (base & ~15)
+            const int32_t *sv = p.delays.data() + (size_t)std::min(d, p.ndm - 1) * p.nch;
+            const int32_t *base = L.tile_base.data() + (size_t)(d / L.td) * p.nch;
+            for (int c = c0; c < c1; ++c)
+                L.dtab[(size_t)c * L.ndm_pad + d] = ((sv[c] - (base[c] & ~15)) & ~3) + (sv[c] & 3) * L.quarter;
         }
     }
-    (void)p;
 }
 
 // Dynamic LDS of one dedispersion workgroup: per buffer, four copies of chan_chunk + 1
 // staged rows and the offset table (dedisp_stage_rows * waves + 4 rows of td entries).
-static size_t dedisp_lds_bytes(const PlanLayout &L) {
+static size_t row_lds_bytes(const PlanLayout &L) {
     return (size_t)L.tiles.nb *
            ((size_t)4 * L.quarter + (size_t)(dedisp_stage_rows(L.tiles.nb) * L.tiles.nw + 4) * L.td * sizeof(int32_t));
+}
+
+// Dynamic LDS of the kernel a plan launches (of the shared-row kernel, two buffers of rows).
+static size_t dedisp_lds_bytes(const PlanLayout &L) {
+    return L.shared ? 2 * (size_t)L.sh.buffer : row_lds_bytes(L);
 }
 
 static spl_status build_layout(spl_batch *B) {
@@ -445,29 +534,30 @@ static spl_status build_layout(spl_batch *B) {
     B->beam_lds.assign(nb, 0);
     B->max_nst = 0;
     B->w_max = 0;
-    // group beams by tile shape; items ordered by group, then beam, time tile, DM tile
+    // group beams by kernel shape; items ordered by group, then beam, time tile, DM tile
     B->groups.clear();
+    int row_groups = 0;
     for (int b = 0; b < nb; ++b) {
-        const Tiles &t = B->layouts[B->layout_of_beam[b]].tiles;
-        int g = -1;
-        for (size_t k = 0; k < B->groups.size(); ++k)
-            if (B->groups[k].dw == t.dw && B->groups[k].j == t.j && B->groups[k].nw == t.nw &&
-                B->groups[k].sv == t.sv && B->groups[k].nb == t.nb)
-                g = (int)k;
-        if (g < 0) {
-            if ((int)B->groups.size() >= kMaxShapeGroups)
-                return fail(SPL_E_UNSUPPORTED, "at most %d distinct tile shapes per batch", kMaxShapeGroups);
-            B->groups.push_back({t.dw, t.j, t.nw, t.sv, t.nb, 0, 0, 0, 0});
-        }
+        const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
+        bool found = false;
+        for (const auto &g : B->groups) found = found || g.holds(L);
+        if (found) continue;
+        if (!L.shared && ++row_groups > kMaxShapeGroups)
+            return fail(SPL_E_UNSUPPORTED, "at most %d distinct tile shapes per batch", kMaxShapeGroups);
+        spl_batch::Group g;
+        g.tiles = L.tiles;
+        g.shared = L.shared;
+        if (L.shared) g.shape = L.sh.shape;
+        B->groups.push_back(g);
     }
     std::vector<std::vector<DedispItem>> per_beam(nb);
     for (int b = 0; b < nb; ++b) {
         const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
         const spl_plan &p = *L.plan;
-        const int TT = 256 * L.tiles.j;
+        per_beam[b].reserve((size_t)L.ntile_t * L.ntile_d);
         for (int tt = 0; tt < L.ntile_t; ++tt)
             for (int k = 0; k < L.ntile_d; ++k)
-                per_beam[b].push_back({b, k * L.td, tt * TT, L.row_bytes[k]});
+                per_beam[b].push_back({b, k * L.tile_trials, tt * L.tile_samples, L.shared ? 0 : L.row_bytes[k]});
         B->beam_lds[b] = dedisp_lds_bytes(L);
         B->max_nst = std::max(B->max_nst, p.nst);
         B->w_max = std::max(B->w_max, p.w_max);
@@ -485,8 +575,7 @@ static spl_status build_layout(spl_batch *B) {
         g.item_lo = (int)B->items.size();
         size_t lds = 0;
         for (int b = 0; b < nb; ++b) {
-            const Tiles &t = B->layouts[B->layout_of_beam[b]].tiles;
-            if (t.dw != g.dw || t.j != g.j || t.nw != g.nw || t.sv != g.sv || t.nb != g.nb) continue;
+            if (!g.holds(B->layouts[B->layout_of_beam[b]])) continue;
             B->item_base[b] = (int)B->items.size();
             B->items.insert(B->items.end(), per_beam[b].begin(), per_beam[b].end());
             lds = std::max(lds, B->beam_lds[b]);
@@ -518,7 +607,7 @@ static spl_status build_layout(spl_batch *B) {
     B->off_items = take(sizeof(DedispItem) * std::max<size_t>(1, res_items));
     for (auto &L : B->layouts) {
         const spl_plan &p = *L.plan;
-        L.off_dcm = take((size_t)p.nch * ((p.ndm + 63) / 64 * 64) * sizeof(int32_t));
+        L.off_dcm = take(table_bytes(p));
         L.off_base = take((size_t)((p.ndm + 15) / 16) * p.nch * sizeof(int32_t));
         L.off_dms = take((size_t)p.ndm * sizeof(double));
         L.off_delays = take(p.delays.size() * sizeof(int32_t));
@@ -613,9 +702,10 @@ extern "C" spl_status spl_batch_create(const spl_plan *const *plans, int32_t n_b
         if (found < 0) {
             PlanLayout L;
             L.plan = plans[b];
-            const Tiles t = default_tiles(*plans[b]);
-            L.tiles = t;
-            B->layouts.push_back(L);
+            int together = 0;   // beams of this plan in one launch
+            for (int i = 0; i < n_beams; ++i) together += plans[i] == plans[b];
+            L.tiles = default_tiles(L, B->mode == SPL_MODE_PERSISTENT_GRAPH ? together : 1);
+            B->layouts.push_back(std::move(L));
             found = (int)B->layouts.size() - 1;
         }
         B->layout_of_beam[b] = found;
@@ -646,6 +736,14 @@ static void fill_host_beams(spl_batch *B) {
         d.pitch = B->cur_pitch[b];
         d.dtab = (const int32_t *)(B->ws + L.off_dcm);
         d.tile_base = (const int32_t *)(B->ws + L.off_base);
+        if (L.shared) {
+            d.shared = (const uint8_t *)(B->ws + L.off_dcm);
+            d.sh_items = (int32_t)L.sh.off_items;
+            d.sh_blocks = (int32_t)L.sh.off_blocks;
+            d.sh_taps = (int32_t)L.sh.off_taps;
+            d.sh_starts = (int32_t)L.sh.off_starts;
+            d.sh_buffer = L.sh.buffer;
+        }
         d.delays = (const int32_t *)(B->ws + L.off_delays);
         d.X = (int32_t *)(B->ws + B->off_X[b]);
         d.S1 = (int64_t *)(B->ws + B->off_S[b]);
@@ -695,10 +793,14 @@ static void fill_host_beams(spl_batch *B) {
 // workspace at B->ws (synchronous copies from host memory).
 static spl_status copy_tables(spl_batch *B) {
     for (auto &L : B->layouts) {
-        HIP_TRY(hipMemcpy(B->ws + L.off_dcm, L.dtab.data(), L.dtab.size() * sizeof(int32_t),
-                          hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(B->ws + L.off_base, L.tile_base.data(), L.tile_base.size() * sizeof(int32_t),
-                          hipMemcpyHostToDevice));
+        if (L.shared) {
+            HIP_TRY(hipMemcpy(B->ws + L.off_dcm, L.sh.blob.data(), L.sh.blob.size(), hipMemcpyHostToDevice));
+        } else {
+            HIP_TRY(hipMemcpy(B->ws + L.off_dcm, L.dtab.data(), L.dtab.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice));
+            HIP_TRY(hipMemcpy(B->ws + L.off_base, L.tile_base.data(), L.tile_base.size() * sizeof(int32_t),
+                              hipMemcpyHostToDevice));
+        }
         HIP_TRY(hipMemcpy(B->ws + L.off_dms, L.plan->dms.data(), L.plan->dms.size() * sizeof(double),
                           hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(B->ws + L.off_delays, L.plan->delays.data(), L.plan->delays.size() * sizeof(int32_t),
@@ -712,18 +814,31 @@ static spl_status copy_tables(spl_batch *B) {
     return SPL_OK;
 }
 
+// LDS limit and occupancy of the dedispersion kernel a group or plan launches.
+static hipError_t prepare_one(const Tiles &t, bool shared, const SharedShape &sh, size_t lds, int *occ) {
+    return shared ? prepare_dedisp_shared(sh, lds, occ)
+                  : prepare_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, lds, occ);
+}
+
+static hipError_t launch_one(const Tiles &t, bool shared, const SharedShape &sh, const DevBeam *beams,
+                             const DedispItem *items, int lo, int hi, int *queue, int grid, size_t lds,
+                             hipStream_t s) {
+    return shared ? launch_dedisp_shared(sh, beams, items, lo, hi, queue, grid, lds, s)
+                  : launch_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, beams, items, lo, hi, queue, grid, lds, s);
+}
+
 // LDS limits of the dedispersion instantiations the batch launches, and the occupancy of
 // each persistent shape group.
 static spl_status prepare_shapes(spl_batch *B) {
     for (auto &g : B->groups) {
         int occ = 0;
-        HIP_TRY(prepare_dedisp(g.dw, g.j, g.nw, g.sv, g.nb, g.lds, &occ));
+        HIP_TRY(prepare_one(g.tiles, g.shared, g.shape, g.lds, &occ));
         g.occ = std::max(1, occ);
     }
     for (int b = 0; b < B->nb; ++b) {
-        const Tiles &t = B->layouts[B->layout_of_beam[b]].tiles;
+        const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
         int occ = 0;
-        HIP_TRY(prepare_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, B->beam_lds[b], &occ));
+        HIP_TRY(prepare_one(L.tiles, L.shared, L.sh.shape, B->beam_lds[b], &occ));
     }
     return SPL_OK;
 }
@@ -819,17 +934,16 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
             const int n = G.item_hi - G.item_lo;
             if (n <= 0) continue;
             const int grid = std::min(n, G.occ * 256);
-            HIP_TRY(launch_dedisp(G.dw, G.j, G.nw, G.sv, G.nb, beams, items, G.item_lo, G.item_hi, &run->queue[g],
-                                  grid, G.lds, s));
+            HIP_TRY(launch_one(G.tiles, G.shared, G.shape, beams, items, G.item_lo, G.item_hi, &run->queue[g], grid,
+                               G.lds, s));
         }
     } else {
         for (int b = b_lo; b < b_hi; ++b) {
-            const Tiles &t = B->layouts[B->layout_of_beam[b]].tiles;
             const int lo = B->item_base[b];
             const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
             const int hi = lo + L.ntile_d * L.ntile_t;
-            HIP_TRY(launch_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, beams, items, lo, hi, nullptr, hi - lo, B->beam_lds[b],
-                                  s));
+            HIP_TRY(launch_one(L.tiles, L.shared, L.sh.shape, beams, items, lo, hi, nullptr, hi - lo, B->beam_lds[b],
+                               s));
         }
     }
     HIP_TRY(t_dd.stop());
@@ -928,6 +1042,22 @@ static spl_status check_run_args(const spl_batch *B, const uint8_t *const *d_blo
     return SPL_OK;
 }
 
+// The shared-row kernel addresses 16 rows by 32-bit offsets: a plan given a row pitch of
+// 2^28 bytes or more goes back to row staging, for good.
+static spl_status drop_shared_of_wide_rows(spl_batch *B, const int64_t *pitches) {
+    bool drop = false;
+    for (int b = 0; b < B->nb; ++b) {
+        PlanLayout &L = B->layouts[B->layout_of_beam[b]];
+        if (!L.shared || pitches[b] < ((int64_t)1 << 28)) continue;
+        L.sh = SharedTables{};
+        drop = true;
+    }
+    if (!drop) return SPL_OK;
+    spl_status st = build_layout(B);
+    if (st == SPL_OK && B->ws) st = upload_tables(B);
+    return st;
+}
+
 extern "C" spl_status spl_batch_run(spl_batch *B, const uint8_t *const *d_blocks, const int64_t *pitches,
                                     spl_candidate *d_cands, int64_t capacity, spl_run_stats *d_stats,
                                     hipStream_t stream) {
@@ -936,6 +1066,8 @@ extern "C" spl_status spl_batch_run(spl_batch *B, const uint8_t *const *d_blocks
     if (!B || !d_blocks || !pitches || !d_stats) return fail(SPL_E_INVALID_ARG, "NULL argument");
     if (!B->tables_uploaded) return fail(SPL_E_INVALID_ARG, "spl_batch_set_workspace was not called");
     spl_status vs = check_run_args(B, d_blocks, pitches, d_cands, capacity, d_stats);
+    if (vs != SPL_OK) return vs;
+    vs = drop_shared_of_wide_rows(B, pitches);
     if (vs != SPL_OK) return vs;
     bool changed = false;
     for (int b = 0; b < B->nb; ++b)
@@ -1011,6 +1143,8 @@ extern "C" spl_status spl_batch_run_static(spl_batch *B, const uint8_t *const *d
                                            hipStream_t stream) {
     if (!B || !d_blocks || !pitches || !d_stats) return fail(SPL_E_INVALID_ARG, "NULL argument");
     spl_status st = check_run_args(B, d_blocks, pitches, d_cands, capacity, d_stats);
+    if (st != SPL_OK) return st;
+    st = drop_shared_of_wide_rows(B, pitches);
     if (st != SPL_OK) return st;
     if (B->ws_bytes > kStaticScratchBytes)
         return fail(SPL_E_UNSUPPORTED, "the batch needs %zu workspace bytes, the static scratch holds %zu "
@@ -1095,7 +1229,7 @@ extern "C" spl_status spl_batch_set_tiles(spl_batch *B, int32_t beam, const spl_
     L.tiles.cc = tiles->chan_chunk;
     spl_status st = build_layout(B);
     if (st == SPL_OK) {
-        if (dedisp_lds_bytes(L) > 160 * 1024 - 256) st = fail(SPL_E_UNSUPPORTED, "tile does not fit the LDS");
+        if (row_lds_bytes(L) > 160 * 1024 - 256) st = fail(SPL_E_UNSUPPORTED, "tile does not fit the LDS");
     }
     if (st != SPL_OK) {
         L.tiles = old;
@@ -1187,6 +1321,7 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
         B->cur_x[b] = d_blocks[b];
         B->cur_pitch[b] = pitches[b];
     }
+    if (spl_status st = drop_shared_of_wide_rows(B, pitches); st != SPL_OK) return st;
     auto cache = read_cache(cache_path);
     constexpr int kTuneBeams = 4;
     // 16-wavefront tiles (64 trials) share each staged channel row among twice the trials;
@@ -1232,7 +1367,8 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
                 L.tiles.nb = sh[3];
                 L.tiles.cc = cc;
                 if (build_layout(B) != SPL_OK) continue;
-                if (B->beam_lds[rep] > 160 * 1024 - 256) continue;
+                if (L.shared && 2 * cc <= dedisp_stage_rows(sh[3]) * sh[2]) continue;   // the same kernel for every cc
+                if (row_lds_bytes(L) > 160 * 1024 - 256) continue;
                 spl_status st = upload_tables(B);
                 if (st != SPL_OK) { result = st; break; }
                 const DevBeam *beams = (const DevBeam *)(B->ws + B->off_beams);
@@ -1254,15 +1390,15 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
                 }
                 const Tiles t = L.tiles;
                 int occ = 0;
-                HIP_TRY(prepare_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, B->beam_lds[rep], &occ));
+                HIP_TRY(prepare_one(t, L.shared, L.sh.shape, B->beam_lds[rep], &occ));
                 const int grid = std::min(hi - lo, std::max(1, occ) * 256);
                 int *queue = &((DevRun *)(B->ws + B->off_run))->queue[0];
                 float best_run = 1e30f;
                 for (int r = 0; r < 4; ++r) {
                     HIP_TRY(hipMemsetAsync(queue, 0, sizeof(int), stream));
                     HIP_TRY(hipEventRecord(e0, stream));
-                    HIP_TRY(launch_dedisp(t.dw, t.j, t.nw, t.sv, t.nb, beams, items, lo, hi, queue, grid,
-                                          B->beam_lds[rep], stream));
+                    HIP_TRY(launch_one(t, L.shared, L.sh.shape, beams, items, lo, hi, queue, grid, B->beam_lds[rep],
+                                       stream));
                     HIP_TRY(hipEventRecord(e1, stream));
                     HIP_TRY(hipEventSynchronize(e1));
                     float ms = 0.f;
@@ -1434,5 +1570,15 @@ extern "C" spl_status spl_debug_mu_sigma(const int64_t *d_n, const int64_t *d_s1
     if (count < 0 || (count > 0 && (!d_n || !d_s1 || !d_s2 || !d_mu || !d_sigma)))
         return fail(SPL_E_INVALID_ARG, "bad argument");
     HIP_TRY(launch_mu_sigma(d_n, d_s1, d_s2, count, d_mu, d_sigma, stream));
+    return SPL_OK;
+}
+
+extern "C" spl_status spl_debug_shared_delays(const spl_batch *B, int32_t beam, int32_t *host_out) {
+    if (!B || !host_out || beam < 0 || beam >= B->nb) return fail(SPL_E_INVALID_ARG, "bad argument");
+    const PlanLayout &L = B->layouts[B->layout_of_beam[beam]];
+    if (!L.shared) return fail(SPL_E_UNSUPPORTED, "the beam's channels are staged one by one");
+    std::vector<int32_t> all;
+    decode_shared(L.sh, L.plan->nch, &all);
+    std::memcpy(host_out, all.data(), (size_t)L.plan->ndm * L.plan->nch * sizeof(int32_t));
     return SPL_OK;
 }

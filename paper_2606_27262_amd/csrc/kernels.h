@@ -2,6 +2,7 @@
 // returns the launch status.
 #pragma once
 
+#include "shared_sums.h"
 #include "spl_internal.h"
 #include "spotlight.h"
 
@@ -17,6 +18,11 @@ bool dedisp_shape_supported(int dw, int j, int nw, int sv, int nbuf);
 hipError_t prepare_dedisp(int dw, int j, int nw, int sv, int nbuf, size_t lds_bytes, int *blocks_per_cu);
 hipError_t launch_dedisp(int dw, int j, int nw, int sv, int nbuf, const DevBeam *beams, const DedispItem *items,
                          int item_lo, int item_hi, int *queue, int grid, size_t lds_bytes, hipStream_t s);
+// The shared-row kernel; lds_bytes holds both row buffers.
+bool shared_shape_supported(const SharedShape &s);
+hipError_t prepare_dedisp_shared(const SharedShape &s, size_t lds_bytes, int *blocks_per_cu);
+hipError_t launch_dedisp_shared(const SharedShape &s, const DevBeam *beams, const DedispItem *items, int item_lo,
+                                int item_hi, int *queue, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_thresholds(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo, int row_hi,
                              hipStream_t s);

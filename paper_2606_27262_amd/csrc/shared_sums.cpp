@@ -1,0 +1,335 @@
+// Host half of the shared partial sums: cuts each DM tile's channels into runs, finds the
+// runs' delay patterns and lays the kernel's tables out (see shared_sums.h).
+#include "shared_sums.h"
+
+#include <algorithm>
+#include <cstring>
+
+namespace spl {
+
+namespace {
+
+constexpr int kSumming = 8;   // summing wavefronts
+constexpr int kMaxTrials = 64;
+
+// One run of channels of one tile.
+struct Run {
+    int c0, n, patterns, groups;         // groups: row elements / 64
+    uint8_t pattern[kMaxTrials];         // of every trial
+    int32_t shift[kMaxTrials];           // delay of channel c0 less its smallest
+    uint8_t e[kSharedPatterns][kSharedChans];   // samples of (pattern, channel) after start, 0..4
+    int32_t start[kSharedChans];         // first sample of the channel's rows from t0, a multiple of 4
+};
+
+// The longest run starting at channel c0, from the delays rows[trial][channel] of a tile.
+bool make_run(const int32_t *const *rows, int td, int nch, int c0, const SharedShape &sh, Run *r) {
+    const int half = sh.half();
+    int32_t lo = rows[0][c0], hi = lo;
+    int32_t first[kMaxTrials];
+    for (int d = 0; d < td; ++d) {
+        first[d] = rows[d][c0];
+        lo = std::min(lo, first[d]);
+        hi = std::max(hi, first[d]);
+    }
+    r->c0 = c0;
+    r->n = 1;
+    r->patterns = 1;
+    const int64_t groups = ((int64_t)half + (hi - lo) + 3 + 63) / 64;   // rows may start 3 samples early
+    if (groups > 255 || groups * 256 > kSharedBuffer) return false;
+    r->groups = (int)groups;
+    const int most = (int)std::min<int64_t>(kSharedPatterns, kSharedBuffer / (groups * 256));
+    std::memset(r->pattern, 0, sizeof r->pattern);
+    r->e[0][0] = 0;
+    r->start[0] = lo;
+    uint32_t early = 15;   // bit s: rows starting s samples early keep every channel within kSharedLate
+    while (r->n < kSharedChans && c0 + r->n < nch) {
+        const int c = c0 + r->n;
+        int32_t dl[kMaxTrials], least = INT32_MAX, largest = INT32_MIN;
+        for (int d = 0; d < td; ++d) {
+            dl[d] = rows[d][c] - first[d];
+            least = std::min(least, dl[d]);
+            largest = std::max(largest, dl[d]);
+        }
+        uint32_t ok = 0;
+        for (int s = 0; s < 4; ++s)
+            if (((lo + least - s) & 3) + (largest - least) <= kSharedLate) ok |= 1u << s;
+        ok &= early;
+        if (!ok) break;
+        // (pattern so far, extra delay) -> pattern
+        int8_t id[kSharedPatterns * (kSharedLate + 1)];
+        uint8_t from[kSharedPatterns], extra[kSharedPatterns], next[kMaxTrials];
+        std::memset(id, -1, sizeof id);
+        int np = 0;
+        bool fits = true;
+        for (int d = 0; d < td; ++d) {
+            const int key = r->pattern[d] * (kSharedLate + 1) + (dl[d] - least);
+            if (id[key] < 0) {
+                if (np == most) {
+                    fits = false;
+                    break;
+                }
+                from[np] = r->pattern[d];
+                extra[np] = (uint8_t)(dl[d] - least);
+                id[key] = (int8_t)np++;
+            }
+            next[d] = (uint8_t)id[key];
+        }
+        if (!fits) break;
+        uint8_t old[kSharedPatterns][kSharedChans];
+        std::memcpy(old, r->e, sizeof old);
+        for (int p = 0; p < np; ++p) {
+            std::memcpy(r->e[p], old[from[p]], r->n);
+            r->e[p][r->n] = extra[p];
+        }
+        std::memcpy(r->pattern, next, td);
+        r->start[r->n] = lo + least;
+        r->patterns = np;
+        early = ok;
+        ++r->n;
+    }
+    int s = 0;
+    while (!(early >> s & 1)) ++s;
+    for (int d = 0; d < td; ++d) r->shift[d] = first[d] - lo + s;
+    for (int c = 0; c < r->n; ++c) {
+        const int32_t at = r->start[c] - s, aligned = at & ~3;
+        r->start[c] = aligned;
+        for (int p = 0; p < r->patterns; ++p) r->e[p][c] = (uint8_t)(r->e[p][c] + (at - aligned));
+    }
+    return true;
+}
+
+}  // namespace
+
+bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, SharedTables *out) {
+    const int td = sh.td(), ntiles = (ndm + td - 1) / td;
+    if (td < 1 || td > kMaxTrials || nch < kSharedChans || nch > 65536 || ndm < 1) return false;
+    const int max_runs = (kSharedBlock - 1) / sh.dw;   // rows of a chunk's runs fit the block
+    const size_t per_sub = 64 * sizeof(uint32_t) + kSharedChans * sizeof(int32_t);
+    const size_t per_chunk = (size_t)kSumming * kSharedBlock * sizeof(int32_t);
+    std::vector<SharedTile> tiles(ntiles);
+    std::vector<SharedItem> items;
+    std::vector<int32_t> blocks, starts;
+    std::vector<uint32_t> taps;
+    std::vector<int> channels;   // of every chunk
+    int buffer = 0;
+    double clocks = 0;
+    std::vector<Run> in_chunk;
+    const int32_t *rows[kMaxTrials];
+    // the 16 channels ahead of a run, copied together (the delay rows lie nch entries apart)
+    std::vector<int32_t> block((size_t)kMaxTrials * 64);
+    for (int k = 0; k < ntiles; ++k) {
+        tiles[k].round = (int32_t)(items.size() / sh.np);
+        tiles[k].chunk = (int32_t)channels.size();
+        int used_bytes = 0;
+        auto close_chunk = [&]() {
+            if (in_chunk.empty()) return;
+            const size_t base = blocks.size();
+            blocks.resize(base + (size_t)kSumming * kSharedBlock, 0);
+            auto block = [&](int wave) { return blocks.data() + base + (size_t)wave * kSharedBlock; };
+            for (int w = 0; w < kSumming; ++w) block(w)[0] = (int32_t)in_chunk.size();
+            std::vector<SharedItem> first_item;   // of every run
+            int lds = 0, chans = 0, groups = 0;
+            for (size_t ri = 0; ri < in_chunk.size(); ++ri) {
+                const Run &r = in_chunk[ri];
+                const int sub = (int)(taps.size() / 64);
+                const int rb = r.groups * 256;
+                // all 16 channels read exist: a run at the band's end moves up
+                const int col0 = std::min(r.c0, nch - kSharedChans), skip = r.c0 - col0;
+                int32_t start[kSharedChans];
+                for (int c = 0; c < kSharedChans; ++c)
+                    start[c] = r.start[std::max(0, std::min(c - skip, r.n - 1))];
+                SharedItem it{};
+                it.sub = sub;
+                it.row_bytes = rb;
+                it.c0 = col0;
+                it.lds = lds;
+                first_item.push_back(it);
+                groups += r.groups;
+                for (int lane = 0; lane < 64; ++lane) {
+                    const int p = lane & 15, q = lane >> 4;
+                    uint32_t v = 0;
+                    for (int u = 0; u < 4; ++u) {
+                        const int c = 8 * (u >> 1) + 2 * q + (u & 1) - skip;
+                        if (p < r.patterns && c >= 0 && c < r.n) v |= 1u << (8 * u + r.e[p][c]);
+                    }
+                    taps.push_back(v);
+                }
+                for (int q = 0; q < 4; ++q)
+                    for (int u = 0; u < 4; ++u) starts.push_back(start[8 * (u >> 1) + 2 * q + (u & 1)]);
+                for (int d = 0; d < td; ++d)
+                    block(d / sh.dw)[1 + ri * sh.dw + d % sh.dw] = lds + r.pattern[d] * rb + r.shift[d] * 4;
+                lds += r.patterns * rb;
+                chans += r.n;
+            }
+            // the chunk's groups in np parts of nearly equal size, each as items of one run
+            std::vector<std::vector<SharedItem>> part(sh.np);
+            int run = 0, g = 0, rounds = 1;
+            for (int w = 0; w < sh.np; ++w) {
+                for (int left = groups / sh.np + (w < groups % sh.np); left > 0;) {
+                    const Run &r = in_chunk[run];
+                    const int ng = std::min(std::min(left, r.groups - g), sh.gp);
+                    SharedItem it = first_item[run];
+                    it.png = (int32_t)((uint32_t)r.patterns | (uint32_t)r.n << 8 | (uint32_t)g << 16 |
+                                       (uint32_t)ng << 24);
+                    it.lds += g * 256;
+                    part[w].push_back(it);
+                    left -= ng;
+                    g += ng;
+                    if (g == r.groups) {
+                        ++run;
+                        g = 0;
+                    }
+                }
+                rounds = std::max(rounds, (int)part[w].size());
+            }
+            for (int i = 0; i < rounds; ++i)
+                for (int w = 0; w < sh.np; ++w) {
+                    // an empty item names an existing run: its tables are loaded all the same
+                    SharedItem it = i < (int)part[w].size() ? part[w][i] : part[w].empty() ? first_item[0] : part[w].back();
+                    if (i >= (int)part[w].size()) it.png &= 0xFFFFFF;
+                    it.last = i + 1 == rounds;
+                    items.push_back(it);
+                }
+            buffer = std::max(buffer, lds);
+            channels.push_back(chans);
+            // modelled clocks of a CU: the staging wavefronts take about 1400 per group and
+            // the chunk's hand-over 300 (the 4096-channel band: 5590 per chunk of 15.2 groups)
+            clocks += (double)groups / sh.np * 1400.0 + 300.0;
+            in_chunk.clear();
+            used_bytes = 0;
+        };
+        int c = 0, block_c0 = 0, block_n = 0;
+        while (c < nch) {
+            if (c + kSharedChans > block_c0 + block_n && block_c0 + block_n < nch) {
+                block_c0 = c;
+                block_n = std::min(64, nch - c);
+                for (int d = 0; d < td; ++d) {
+                    const int ds = std::min(k * td + d, ndm - 1);
+                    std::memcpy(block.data() + (size_t)d * 64, delays + (size_t)ds * nch + c,
+                                (size_t)block_n * sizeof(int32_t));
+                    rows[d] = block.data() + (size_t)d * 64;
+                }
+            }
+            Run r;
+            if (!make_run(rows, td, block_n, c - block_c0, sh, &r)) return false;
+            r.c0 = c;
+            const int bytes = r.patterns * r.groups * 256;
+            if (used_bytes + bytes > kSharedBuffer || (int)in_chunk.size() == max_runs) close_chunk();
+            used_bytes += bytes;
+            in_chunk.push_back(r);
+            c += r.n;
+        }
+        close_chunk();
+        tiles[k].nrounds = (int32_t)(items.size() / sh.np) - tiles[k].round;
+        tiles[k].nchunks = (int32_t)channels.size() - tiles[k].chunk;
+        // the 16-bit fields hold a low byte and 256 channels of 255: the high bytes move on
+        // before the chunk that would exceed that
+        const int *chans = channels.data() + tiles[k].chunk;
+        for (int j = 0, pending = 0; j < tiles[k].nchunks; ++j) {
+            pending += chans[j];
+            if (j + 1 < tiles[k].nchunks && pending + chans[j + 1] <= 256) continue;
+            for (int w = 0; w < kSumming; ++w)
+                blocks[((size_t)(tiles[k].chunk + j) * kSumming + w) * kSharedBlock] |= pending << 8;
+            pending = 0;
+        }
+        if ((taps.size() / 64) * per_sub + channels.size() * per_chunk +
+                items.size() * sizeof(SharedItem) + ntiles * sizeof(SharedTile) + 256 >
+            max_bytes)
+            return false;
+    }
+    SharedTables &t = *out;
+    t.shape = sh;
+    t.ntiles = ntiles;
+    t.nsubs = (int)(taps.size() / 64);
+    t.nrounds = (int)(items.size() / sh.np);
+    t.nchunks = (int)channels.size();
+    t.buffer = buffer;
+    t.clocks = clocks;
+    auto up = [](size_t v) { return (v + 127) & ~(size_t)127; };
+    t.off_items = up(tiles.size() * sizeof(SharedTile));
+    t.off_blocks = up(t.off_items + items.size() * sizeof(SharedItem));
+    t.off_taps = up(t.off_blocks + blocks.size() * sizeof(int32_t));
+    t.off_starts = up(t.off_taps + taps.size() * sizeof(uint32_t));
+    const size_t bytes = up(t.off_starts + starts.size() * sizeof(int32_t));
+    if (bytes > max_bytes || bytes > INT32_MAX) return false;
+    t.blob.assign(bytes, 0);
+    std::memcpy(t.blob.data(), tiles.data(), tiles.size() * sizeof(SharedTile));
+    std::memcpy(t.blob.data() + t.off_items, items.data(), items.size() * sizeof(SharedItem));
+    std::memcpy(t.blob.data() + t.off_blocks, blocks.data(), blocks.size() * sizeof(int32_t));
+    std::memcpy(t.blob.data() + t.off_taps, taps.data(), taps.size() * sizeof(uint32_t));
+    std::memcpy(t.blob.data() + t.off_starts, starts.data(), starts.size() * sizeof(int32_t));
+    return true;
+}
+
+void decode_shared(const SharedTables &t, int nch, std::vector<int32_t> *out) {
+    const int td = t.shape.td(), dw = t.shape.dw;
+    out->assign((size_t)t.ntiles * td * nch, -1);
+    const uint8_t *b = t.blob.data();
+    const SharedTile *tiles = (const SharedTile *)b;
+    const SharedItem *items = (const SharedItem *)(b + t.off_items);
+    const int32_t *blocks = (const int32_t *)(b + t.off_blocks);
+    const uint32_t *taps = (const uint32_t *)(b + t.off_taps);
+    const int32_t *starts = (const int32_t *)(b + t.off_starts);
+    for (int k = 0; k < t.ntiles; ++k) {
+        int pending = 0;   // channels in the 16-bit fields
+        int round = tiles[k].round;
+        for (int j = tiles[k].chunk; j < tiles[k].chunk + tiles[k].nchunks; ++j) {
+            auto block = [&](int w) { return blocks + ((size_t)j * kSumming + w) * kSharedBlock; };
+            std::vector<SharedItem> mine;   // the chunk's items
+            for (bool last = false; !last && round < tiles[k].round + tiles[k].nrounds; ++round)
+                for (int w = 0; w < t.shape.np; ++w) {
+                    const SharedItem &it = items[(size_t)round * t.shape.np + w];
+                    last = it.last != 0;
+                    if ((uint32_t)it.png >> 24) mine.push_back(it);
+                }
+            std::sort(mine.begin(), mine.end(), [](const SharedItem &a, const SharedItem &b) { return a.lds < b.lds; });
+            const int runs = block(0)[0] & 255;
+            int ri = 0;
+            for (const SharedItem &it : mine) {
+                if ((it.png >> 16) & 255) continue;   // a run's first item names it
+                const int np = it.png & 255, n = (it.png >> 8) & 255;
+                int groups = 0;   // staged groups of the run, each at its place
+                for (const SharedItem &o : mine) {
+                    const int g0 = (o.png >> 16) & 255, ng = (int)((uint32_t)o.png >> 24);
+                    if (o.sub != it.sub || o.lds != it.lds + 256 * g0 || o.row_bytes != it.row_bytes ||
+                        o.c0 != it.c0 || g0 != groups || ng < 1 || ng > t.shape.gp)
+                        continue;
+                    groups += ng;
+                }
+                bool good = groups * 256 == it.row_bytes && it.lds + np * it.row_bytes <= t.buffer && ri < runs &&
+                            it.c0 >= 0 && it.c0 + kSharedChans <= nch;
+                pending += n;
+                good = good && pending <= 256;
+                for (int d = 0; d < td; ++d) {
+                    const int off = block(d / dw)[1 + ri * dw + d % dw] - it.lds;
+                    const int p = off / it.row_bytes, shift = (off % it.row_bytes) / 4;
+                    int taken = 0;
+                    for (int c = 0; c < kSharedChans && off >= 0 && p < np; ++c) {
+                        const int q = (c % 8) / 2, u = 2 * (c / 8) + c % 2;
+                        const uint32_t hot = (taps[(size_t)it.sub * 64 + 16 * q + p] >> (8 * u)) & 255u;
+                        if (!hot) continue;
+                        ++taken;
+                        int e = 0;
+                        while (!(hot >> e & 1)) ++e;
+                        const int s = starts[(size_t)it.sub * 16 + 4 * q + u];
+                        int32_t &o = (*out)[((size_t)k * td + d) * nch + it.c0 + c];
+                        const bool fine = good && o == -1 && (hot >> e) == 1 && e <= kSharedLate && !(off & 3) &&
+                                          !(s & 3) && shift * 4 + t.shape.half() * 4 <= it.row_bytes;
+                        o = fine ? s + shift + e : -2;
+                    }
+                    if (taken != n) (*out)[((size_t)k * td + d) * nch + it.c0] = -2;
+                }
+                ++ri;
+            }
+            for (int w = 0; w < kSumming; ++w)
+                if (block(w)[0] != block(0)[0] || ri != runs) (*out)[(size_t)k * td * nch] = -2;
+            if (block(0)[0] >> 8) {
+                if (block(0)[0] >> 8 != pending) (*out)[(size_t)k * td * nch] = -2;
+                pending = 0;
+            }
+        }
+        if (pending || round != tiles[k].round + tiles[k].nrounds) (*out)[(size_t)k * td * nch] = -2;
+    }
+}
+
+}  // namespace spl

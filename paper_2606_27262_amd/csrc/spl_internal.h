@@ -13,7 +13,8 @@ constexpr int kThreads = 256;         // threads per workgroup of every kernel
 constexpr int kNmsBlockShift = 6;     // the peak filter indexes hit rows in blocks of 64 samples
 constexpr int kScanPerBlock = 4096;   // elements per block of the device-wide scan
 constexpr int kMaxWmax = 8192;
-constexpr int kMaxShapeGroups = 4;  // distinct dedispersion tile shapes per batch
+constexpr int kMaxShapeGroups = 4;  // distinct row-staging tile shapes per batch
+constexpr int kMaxSharedShapes = 4; // shapes of the shared-row kernel (a group of each may join them)
 
 // One beam of a batch, resident in the workspace.
 struct DevBeam {
@@ -24,6 +25,7 @@ struct DevBeam {
                              // ((s - b) & ~3) + (s & 3)*lds_quarter, b = tile_base & ~15
     const int32_t *tile_base;// min delay over each DM tile [ndm_tiles][nch]
     const int32_t *delays;   // delay table in samples [ndm][nch] (snippet extraction)
+    const uint8_t *shared;   // tables of k_dedisp_shared (then dtab and tile_base are not used)
     int32_t *X;              // DM transform [ndm][xpitch]
     int64_t *S1, *S2;        // [ndm][nseg]
     double *mu, *sigma;      // [ndm][nseg]
@@ -42,6 +44,8 @@ struct DevBeam {
     int32_t chan_chunk;      // channels staged in LDS per step (power of two <= 256)
     int32_t lds_quarter;     // bytes per shifted copy of the staged rows in the LDS
     int32_t tile_dm;         // DM trials per dedispersion tile
+    int32_t sh_items, sh_blocks, sh_taps, sh_starts;   // byte offsets in `shared`
+    int32_t sh_buffer;       // LDS bytes of one buffer of shared rows
     int32_t beam;
     int32_t w_max;
     int32_t nst;             // peak filters of this beam's plan
@@ -75,7 +79,7 @@ struct DevRun {
     int64_t n_alive[kMaxStencils];
     int64_t n_surv;        // survivors of the first peak filter (the compacted list's length)
     int32_t hit_overflow;
-    int32_t queue[kMaxShapeGroups];  // persistent-kernel work counters
+    int32_t queue[kMaxShapeGroups + kMaxSharedShapes];  // persistent-kernel work counters
     int32_t box_stall;     // 1: a boxcar look-back gave up waiting (hit offsets invalid)
 };
 

@@ -125,6 +125,7 @@ STATIC_SCRATCH_BYTES = 64 << 20   # SPL_STATIC_SCRATCH_BYTES
 _sig("spl_batch_set_profiling", [_P, _I32])
 _sig("spl_autotune", [_P, ctypes.POINTER(_P), ctypes.POINTER(_I64), ctypes.c_char_p, _I32, _P])
 _sig("spl_batch_stage_times", [_P, _P, _P, _I32])
+_sig("spl_debug_shared_delays", [_P, _I32, _P])
 _sig("spl_debug_mu_sigma", [_P, _P, _P, _I64, _P, _P, _P])
 _sig("spl_opt_defaults", [ctypes.POINTER(_OptParams)], None)
 _sig("spl_optimise_plain", [_P, _I64, _P, _I32, ctypes.POINTER(_OptParams), _P, _I64, ctypes.POINTER(_I64)])
@@ -296,6 +297,17 @@ class Batch:
         _check(_lib.spl_batch_set_tiles(self._h, beam, ctypes.byref(t)))
         if self.ws is not None:
             self.attach()
+
+    def shared_delays(self, beam=0):
+        """Delays int32 [ndm][nchans] encoded by the beam's shared-row tables (test hook),
+        or None when its tiling stages single channels."""
+        info = self.plans[beam].info
+        out = np.empty((info["ndm"], info["nchans"]), np.int32)
+        st = _lib.spl_debug_shared_delays(self._h, beam, out.ctypes.data)
+        if st == SPL_E_UNSUPPORTED:
+            return None
+        _check(st)
+        return out
 
     def attach(self):
         """Allocate (or grow) the workspace with torch and upload the plan tables."""
