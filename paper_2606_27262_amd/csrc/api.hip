@@ -339,7 +339,7 @@ static bool shared_tables(PlanLayout &L) {
     if (!L.shared_tried) {
         L.shared_tried = true;
         const spl_plan &p = *L.plan;
-        static const SharedShape shapes[] = {{4, 8, 8, 3}};
+        static const SharedShape shapes[] = {{4, 8, 8, 6}};
         double best = (double)p.ndm * p.nch / kRowAddsPerClock;   // clocks per output sample
         for (const SharedShape &s : shapes) {
             SharedTables t;

@@ -11,6 +11,7 @@ namespace {
 
 constexpr int kSumming = 8;   // summing wavefronts
 constexpr int kMaxTrials = 64;
+constexpr int kTaps = 64;   // words of a run
 
 // One run of channels of one tile.
 struct Run {
@@ -35,9 +36,9 @@ bool make_run(const int32_t *const *rows, int td, int nch, int c0, const SharedS
     r->n = 1;
     r->patterns = 1;
     const int64_t groups = ((int64_t)half + (hi - lo) + 3 + 63) / 64;   // rows may start 3 samples early
-    if (groups > 255 || groups * 256 > kSharedBuffer) return false;
+    if (groups > 255 || groups * 256 > kSharedRun) return false;
     r->groups = (int)groups;
-    const int most = (int)std::min<int64_t>(kSharedPatterns, kSharedBuffer / (groups * 256));
+    const int most = (int)std::min<int64_t>(kSharedPatterns, kSharedRun / (groups * 256));
     std::memset(r->pattern, 0, sizeof r->pattern);
     r->e[0][0] = 0;
     r->start[0] = lo;
@@ -104,7 +105,7 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
     const int td = sh.td(), ntiles = (ndm + td - 1) / td;
     if (td < 1 || td > kMaxTrials || nch < kSharedChans || nch > 65536 || ndm < 1) return false;
     const int max_runs = (kSharedBlock - 1) / sh.dw;   // rows of a chunk's runs fit the block
-    const size_t per_sub = 64 * sizeof(uint32_t) + kSharedChans * sizeof(int32_t);
+    const size_t per_sub = kTaps * sizeof(uint32_t) + kSharedChans * sizeof(int32_t);
     const size_t per_chunk = (size_t)kSumming * kSharedBlock * sizeof(int32_t);
     std::vector<SharedTile> tiles(ntiles);
     std::vector<SharedItem> items;
@@ -131,7 +132,7 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
             int lds = 0, chans = 0, groups = 0;
             for (size_t ri = 0; ri < in_chunk.size(); ++ri) {
                 const Run &r = in_chunk[ri];
-                const int sub = (int)(taps.size() / 64);
+                const int sub = (int)(taps.size() / kTaps);
                 const int rb = r.groups * 256;
                 // all 16 channels read exist: a run at the band's end moves up
                 const int col0 = std::min(r.c0, nch - kSharedChans), skip = r.c0 - col0;
@@ -145,12 +146,12 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
                 it.lds = lds;
                 first_item.push_back(it);
                 groups += r.groups;
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int p = lane & 15, q = lane >> 4;
+                for (int i = 0; i < kTaps; ++i) {
+                    const int q = i / 16, p = std::min(4 * (i % 4) + i / 4 % 4, r.patterns - 1);
                     uint32_t v = 0;
                     for (int u = 0; u < 4; ++u) {
                         const int c = 8 * (u >> 1) + 2 * q + (u & 1) - skip;
-                        if (p < r.patterns && c >= 0 && c < r.n) v |= 1u << (8 * u + r.e[p][c]);
+                        if (c >= 0 && c < r.n) v |= 1u << (24 + u) | 8u * r.e[p][c] << (6 * u);
                     }
                     taps.push_back(v);
                 }
@@ -161,26 +162,35 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
                 lds += r.patterns * rb;
                 chans += r.n;
             }
-            // the chunk's groups in np parts of nearly equal size, each as items of one run
-            std::vector<std::vector<SharedItem>> part(sh.np);
-            int run = 0, g = 0, rounds = 1;
-            for (int w = 0; w < sh.np; ++w) {
-                for (int left = groups / sh.np + (w < groups % sh.np); left > 0;) {
-                    const Run &r = in_chunk[run];
-                    const int ng = std::min(std::min(left, r.groups - g), sh.gp);
-                    SharedItem it = first_item[run];
-                    it.png = (int32_t)((uint32_t)r.patterns | (uint32_t)r.n << 8 | (uint32_t)g << 16 |
-                                       (uint32_t)ng << 24);
-                    it.lds += g * 256;
-                    part[w].push_back(it);
-                    left -= ng;
-                    g += ng;
-                    if (g == r.groups) {
-                        ++run;
-                        g = 0;
+            // the chunk's groups dealt to the staging wavefronts in items of one run each; an
+            // item costs its groups and about one more, `most` is the least that a wavefront
+            // can be asked for
+            std::vector<std::vector<SharedItem>> part;
+            int rounds = 1;
+            for (int most = 1 + groups / sh.np;; ++most) {
+                part.assign(sh.np, {});
+                rounds = 1;
+                size_t run = 0;
+                int g = 0;
+                for (int w = 0; w < sh.np; ++w) {
+                    for (int left = most; left > 1 && run < in_chunk.size();) {
+                        const Run &r = in_chunk[run];
+                        const int ng = std::min(std::min(left - 1, r.groups - g), sh.gp);
+                        SharedItem it = first_item[run];
+                        it.png = (int32_t)((uint32_t)r.patterns | (uint32_t)r.n << 8 | (uint32_t)g << 16 |
+                                           (uint32_t)ng << 24);
+                        it.lds += g * 256;
+                        part[w].push_back(it);
+                        left -= ng + 1;
+                        g += ng;
+                        if (g == r.groups) {
+                            ++run;
+                            g = 0;
+                        }
                     }
+                    rounds = std::max(rounds, (int)part[w].size());
                 }
-                rounds = std::max(rounds, (int)part[w].size());
+                if (run == in_chunk.size()) break;
             }
             for (int i = 0; i < rounds; ++i)
                 for (int w = 0; w < sh.np; ++w) {
@@ -192,9 +202,10 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
                 }
             buffer = std::max(buffer, lds);
             channels.push_back(chans);
-            // modelled clocks of a CU: the staging wavefronts take about 1400 per group and
-            // the chunk's hand-over 300 (the 4096-channel band: 5590 per chunk of 15.2 groups)
-            clocks += (double)groups / sh.np * 1400.0 + 300.0;
+            // modelled clocks of a CU: a staging wavefront takes about 650 per group, 690 per
+            // item and 470 for the chunk's hand-over (the 4096-channel band: 4850 per chunk of
+            // 21.8 groups in 1.16 rounds)
+            clocks += (double)groups / sh.np * 650.0 + rounds * 690.0 + 470.0;
             in_chunk.clear();
             used_bytes = 0;
         };
@@ -232,7 +243,7 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
                 blocks[((size_t)(tiles[k].chunk + j) * kSumming + w) * kSharedBlock] |= pending << 8;
             pending = 0;
         }
-        if ((taps.size() / 64) * per_sub + channels.size() * per_chunk +
+        if ((taps.size() / kTaps) * per_sub + channels.size() * per_chunk +
                 items.size() * sizeof(SharedItem) + ntiles * sizeof(SharedTile) + 256 >
             max_bytes)
             return false;
@@ -240,7 +251,7 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
     SharedTables &t = *out;
     t.shape = sh;
     t.ntiles = ntiles;
-    t.nsubs = (int)(taps.size() / 64);
+    t.nsubs = (int)(taps.size() / kTaps);
     t.nrounds = (int)(items.size() / sh.np);
     t.nchunks = (int)channels.size();
     t.buffer = buffer;
@@ -306,14 +317,19 @@ void decode_shared(const SharedTables &t, int nch, std::vector<int32_t> *out) {
                     int taken = 0;
                     for (int c = 0; c < kSharedChans && off >= 0 && p < np; ++c) {
                         const int q = (c % 8) / 2, u = 2 * (c / 8) + c % 2;
-                        const uint32_t hot = (taps[(size_t)it.sub * 64 + 16 * q + p] >> (8 * u)) & 255u;
-                        if (!hot) continue;
+                        auto tap = [&](int pattern) {
+                            const uint32_t v = taps[(size_t)it.sub * kTaps + 16 * q + 4 * (pattern % 4) + pattern / 4];
+                            const int at = (int)((v >> (6 * u)) & 63u);
+                            return !(v >> (24 + u) & 1u) ? -1 : at % 8 == 0 ? at / 8 : 99;
+                        };
+                        const int e = tap(p);
+                        bool same = true;   // the patterns past the last repeat it
+                        for (int past = np; past < kSharedPatterns && p + 1 == np; ++past) same = same && tap(past) == e;
+                        if (e < 0 && same) continue;
                         ++taken;
-                        int e = 0;
-                        while (!(hot >> e & 1)) ++e;
                         const int s = starts[(size_t)it.sub * 16 + 4 * q + u];
                         int32_t &o = (*out)[((size_t)k * td + d) * nch + it.c0 + c];
-                        const bool fine = good && o == -1 && (hot >> e) == 1 && e <= kSharedLate && !(off & 3) &&
+                        const bool fine = good && o == -1 && same && e <= kSharedLate && !(off & 3) &&
                                           !(s & 3) && shift * 4 + t.shape.half() * 4 <= it.row_bytes;
                         o = fine ? s + shift + e : -2;
                     }

@@ -2,7 +2,7 @@
 // over a few adjacent channels the trials of a tile have in common.
 //
 // The delays of a run of adjacent channels, taken relative to the run's first channel,
-// repeat from trial to trial: over the 64 trials of a tile some twelve channels of the
+// repeat from trial to trial: over the 64 trials of a tile some ten channels of the
 // 4096-channel band show fifteen different patterns.  A row of sums per pattern is formed
 // once per tile, and every trial then adds one row, shifted by the first channel's delay,
 // in place of the run's channels one by one.  The sums are the same integers.
@@ -36,6 +36,7 @@ constexpr int kSharedChans = 16;      // channels of a run
 constexpr int kSharedPatterns = 16;   // patterns of a run (rows of the matrix product)
 constexpr int kSharedLate = 4;        // samples a pattern may lie behind its channel's aligned start
 constexpr int kSharedBuffer = 79 * 1024;   // LDS bytes of one of the two row buffers
+constexpr int kSharedRun = kSharedBuffer / 2;   // LDS bytes of a run: two share a chunk
 constexpr int kSharedBlock = 64;      // int32 of a summing wavefront's block of a chunk
 
 // Staging item: one wavefront forms up to gp groups of 64 packed elements of every pattern
@@ -65,9 +66,10 @@ struct SharedTables {
     double clocks = 0;       // modelled clocks of a CU for one time tile of every DM tile
     std::vector<uint8_t> blob;
     // items [round][np wavefronts]; blocks [chunk][8 wavefronts][kSharedBlock]; taps
-    // [run][64 lanes] uint32: lane (p = lane % 16, q = lane / 16) holds pattern p's choice,
-    // a one-hot byte, for each of the channels 2q, 2q + 1, 8 + 2q, 9 + 2q; starts
-    // [run][4 q][4] those channels' first samples from t0 (multiples of 4)
+    // [run][4 q][4 p][4 k] uint32: of pattern 4 k + p (past the last: of the last) and the
+    // channels 2q, 2q + 1, 8 + 2q, 9 + 2q: in six bits from 6 u on 8 times the samples after
+    // the channel's start, bit 24 + u where the run has the channel; starts [run][4 q][4]
+    // those channels' first samples from t0 (multiples of 4)
     size_t off_items = 0, off_blocks = 0, off_taps = 0, off_starts = 0;
 };
 
