@@ -123,7 +123,10 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
             // raw[g][h][u]: the dword at 64 (group + g) + 4 n of channel u, h = 1: H samples
             // later, g up to the item's groups.  A buffer over the block from row c0 on bounds
             // the tiles at the rows' ends: what they read past a row is not needed, past the
-            // block (or before it, offsets then wrap) it reads as zero.  Groups that the item does not have load from an
+            // block it reads as zero.  Before the block's first sample (starts of -4 or -8, at
+            // t = 0) nothing is needed, but an offset that wraps must not be brought back by an
+            // instruction's own offset: offsets are held for the second group, and the first's
+            // are cut off at zero.  Groups that the item does not have load from an
             // empty buffer: with the same number of loads on every path a wait can be for
             // some of them, not all.
             struct Rows { const uint8_t *base; uint32_t bytes; int groups; };
@@ -140,12 +143,13 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
                     (void *)w.base, 0, g <= w.groups ? (int)w.bytes : 0, 0x00027000);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    raw[0][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o[u] + 64 * g), 0, 0);
-                    raw[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o[u] + H + 64 * g), 0, 0);
+                    const int at = (int)(g > 0 ? o[u] + 64 * (g - 1) : o[u] - min(o[u], 64u));
+                    raw[0][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0);
+                    raw[1][u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o[u] + H - 64 + 64 * g), 0, 0);
                 }
             };
             auto raw_offsets = [&](int d, const i32x4 &start, uint32_t l, uint32_t (&o)[4]) {
-                const uint32_t i0 = (uint32_t)(64 * ((field(d, 1) >> 16) & 255) + t0);
+                const uint32_t i1 = (uint32_t)(64 * ((field(d, 1) >> 16) & 255) + t0 + 64);
                 // kept out of the compiler's sight: it would hold four lane offsets in
                 // registers across the loop
                 uint32_t step = pitch;
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
                 const uint32_t lane_off = 2u * (l >> 4) * step + 4u * (l & 15);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    o[u] = lane_off + (uint32_t)start[u] + (uint32_t)(8 * (u >> 1) + (u & 1)) * step + i0;
+                    o[u] = lane_off + (uint32_t)start[u] + (uint32_t)(8 * (u >> 1) + (u & 1)) * step + i1;
             };
 
             // the dwords after an item's GP groups, those of (h, u) in lane n = 4 h + u
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
                     const uint32_t ou = o[u];
                     at = (l & 3) == (uint32_t)u ? ou : at;
                 }
-                return __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at - 4u * (l & 15) + (l & 4 ? H : 0) + 64u * GP), 0, 0);
+                return __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at - 4u * (l & 15) + (l & 4 ? H : 0) + 64u * (GP - 1)), 0, 0);
             };
 
             // RS groups' raw samples in registers: group g's are replaced as soon as it is formed

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2606_27262_amd import workloads as W
+from test_shared_sums import steps_before_the_first
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -38,7 +39,16 @@ def test_edges_equal_the_plain_sum(spl, name):
     p = W.make_plan(nch, lo, hi, 1.31072e-3, n_out, dm0, dm0 + step * ndm, ndm, (1, 4))
     if flip:
         p["fch1"], p["foff"] = p["fch1"] + (nch - 1) * p["foff"], -p["foff"]
-    plan = spl.Plan.from_dict(p)
+    check(spl, spl.Plan.from_dict(p))
+
+
+def test_no_row_starts_before_the_block(spl):
+    """Channels that would agree best on rows starting before the block's first sample."""
+    check(spl, spl.Plan(64, 750.0, -200.0 / 64, 1e-3, 1500, widths=(1,), delays=steps_before_the_first()))
+
+
+def check(spl, plan):
+    nch, ndm = plan.info["nchans"], plan.info["ndm"]
     batch = spl.Batch([plan], hit_capacity=1 << 20)
     for dw, j in ((4, 2), (2, 2), (4, 1)):
         try:
@@ -48,7 +58,7 @@ def test_edges_equal_the_plain_sum(spl, name):
             continue
     assert batch.shared_delays() is not None, "the plan is meant to share its rows"
     n_in, n_dd = plan.info["n_in"], plan.info["n_dd"]
-    rng = np.random.default_rng(len(name))
+    rng = np.random.default_rng(nch)
     x = rng.integers(0, 256, size=(nch, n_in), dtype=np.uint8)
     x[rng.random(nch) < 0.3] = 255   # whole channels at the largest byte
     block = spl.upload_block(x, pitch=(n_in + 15) // 16 * 16)

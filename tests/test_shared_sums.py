@@ -66,6 +66,25 @@ def test_arbitrary_delay_tables():
     assert shared >= 6
 
 
+def steps_before_the_first(nch=64, ndm=64):
+    """Delays whose channels would agree best on rows that start before the block: every
+    other channel steps from 1 to 5 over the trials, the ones between from 0 to 1."""
+    d = np.zeros((ndm, nch), np.int32)
+    d[:, 1::2] = (1 + np.arange(ndm) * 5 // ndm)[:, None]
+    d[:, 2::2] = (np.arange(ndm) * 2 // ndm)[:, None]
+    return d
+
+
+def test_no_row_starts_before_the_block():
+    """(a start before a row would be an offset that wraps)"""
+    d = steps_before_the_first()
+    plan = spl.Plan(64, 750.0, -200.0 / 64, 1e-3, 1500, widths=(1,), delays=d)
+    b = spl.Batch([plan], hit_capacity=1 << 16)
+    b.set_tiles(0, 4, 2, 0, waves=16)
+    got = b.shared_delays()
+    assert got is not None and np.array_equal(got, d)
+
+
 def test_plans_without_shared_patterns_stage_single_channels():
     plan = spl.Plan.from_dict(W.plan_c1())   # 88 samples from trial to trial at the lowest channel
     b = spl.Batch([plan], hit_capacity=1 << 16)
