@@ -30,125 +30,127 @@ __device__ inline uint16_t f2bf(float f) {   // round to nearest even (finite in
 __device__ inline float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ----------------------------------------------------------------- snippets
-// One workgroup (256 threads) per candidate.  Plane 0: rows d*-32..d*+31 of the DM
-// transform over t*-128..t*+127 (thread = column), each row standardised by the search's
-// own (mu, sigma) of the segment of t*.  Plane 1: 64 sub-bands of nch/64 adjacent
-// channels summed along the delays of trial d*, each standardised over its valid samples
-// with the same exact-moment recipe.  Values float((v - mu)/sigma) in binary64 -> BF16;
-// entries outside the DM range or outside [0, n_dd) are 0.
-// Plane 1 work split: thread (g = tid / 16, q = tid % 16) adds samples 16q .. 16q+15 of
-// channels g, g+16, ... of a sub-band, reading each channel's 16 bytes as five aligned
-// dwords and accumulating them as 16-bit pairs (as the dedispersion kernel does); the 16
-// channel groups are then summed through the LDS.
+// A channel's samples through a buffer that ends with the block (bytes past it, and
+// offsets before the row, which wrap, read as zero or as other samples of the block: the
+// entries they belong to are not valid).  An absent channel's buffer is empty.  A negative
+// offset must not be brought back by an instruction's own offset, which is added without
+// wrapping: apart() keeps the sum in a register.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t channel_rows(const DevBeam &B, int c, bool present) {
+    const uint64_t at = (uint64_t)c * (uint64_t)B.pitch, left = (uint64_t)B.nch * (uint64_t)B.pitch - at;
+    const uint32_t bytes = left >> 32 ? 0xFFFFFFFCu : (uint32_t)left;
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(B.x + at), 0, present ? (int)bytes : 0, 0x00027000);
+}
+
+__device__ __forceinline__ int apart(int offset) {
+    asm volatile("" : "+v"(offset));
+    return offset;
+}
+
+// whether a record names a (beam, trial, owned sample) of this batch
+__device__ inline bool in_batch(const spl_candidate &cd, const DevBeam *beams, int nbeams) {
+    return cd.beam >= 0 && cd.beam < nbeams && cd.dm_index >= 0 && cd.dm_index < beams[cd.beam].ndm &&
+           cd.t_sample >= 0 && cd.t_sample < beams[cd.beam].n_out;
+}
+
+// Plane 0: rows d*-32..d*+31 of the DM transform over t*-128..t*+127, each row
+// standardised by the search's own (mu, sigma) of the segment of t*.  Plane 1: 64
+// sub-bands of nch/64 adjacent channels summed along the delays of trial d*, each
+// standardised over its valid samples with the same exact-moment recipe.  Values
+// float((v - mu)/sigma) in binary64 -> BF16; entries outside the DM range or outside
+// [0, n_dd) are 0.
+//
+// One wavefront per row of the two planes: 64 per candidate, so a few candidates fill the
+// chip, and nothing waits for other wavefronts.  Plane 1: lane l adds samples 4l .. 4l+3
+// of a channel from two aligned dwords (a wavefront's dword load takes 5 clocks, an
+// unaligned one 16) as 16-bit pairs, moved to 32 bits every 256 channels; 16 loads are
+// under way at a time.  256 candidates of the 4096-channel band read 400 MB in lines of
+// 128 bytes: 72 us, where one workgroup per candidate with three barriers per sub-band
+// took 640 us.
 __global__ __launch_bounds__(256) void k_snippets(const DevBeam *__restrict__ beams, int nbeams,
                                                   const spl_candidate *__restrict__ cands, int64_t n,
                                                   uint16_t *__restrict__ out) {
     constexpr uint32_t kSelEven = 0x0C020C00u;   // bytes 0, 2 -> 16-bit fields
     constexpr uint32_t kSelOdd = 0x0C030C01u;    // bytes 1, 3 -> 16-bit fields
-    __shared__ int32_t red[16][256];
-    __shared__ int64_t sh[3][4];
-    const int col = threadIdx.x, lane = lane_id(), wave = wave_id();
-    const int g = col >> 4, q = col & 15;
-    for (int64_t c = blockIdx.x; c < n; c += gridDim.x) {
-        const spl_candidate cd = cands[c];
-        uint16_t *o0 = out + (size_t)c * 2 * 64 * 256;
+    const int lane = lane_id(), wave = wave_id();
+    for (int64_t item = blockIdx.x; item < n * 16; item += gridDim.x) {
+        const spl_candidate cd = cands[item >> 4];
+        const int k = 4 * (int)(item & 15) + wave;   // row of the planes
+        uint16_t *o0 = out + (size_t)(item >> 4) * 2 * 64 * 256 + k * 256;
         uint16_t *o1 = o0 + 64 * 256;
-        // a record that names no (beam, trial, owned sample) of this batch gives zero planes
-        const bool ok = cd.beam >= 0 && cd.beam < nbeams && cd.dm_index >= 0 &&
-                        cd.dm_index < beams[cd.beam < 0 || cd.beam >= nbeams ? 0 : cd.beam].ndm &&
-                        cd.t_sample >= 0 &&
-                        cd.t_sample < beams[cd.beam < 0 || cd.beam >= nbeams ? 0 : cd.beam].n_out;
-        if (!ok) {
-            for (int r = 0; r < 128; ++r) o0[r * 256 + col] = 0;
-            continue;   // uniform across the workgroup: no barrier is skipped by part of it
+        if (!in_batch(cd, beams, nbeams)) {   // zero planes
+            for (int j = 0; j < 4; ++j) o0[lane + 64 * j] = o1[lane + 64 * j] = 0;
+            continue;
         }
         const DevBeam &B = beams[cd.beam];
         const int ds = cd.dm_index, ts = cd.t_sample;
-        const int t = ts - 128 + col;
-        const bool valid = t >= 0 && t < B.n_dd;
-        const int seg = ts / B.L;
-        for (int r = 0; r < 64; ++r) {
-            const int d = ds - 32 + r;
-            float v = 0.f;
-            if (valid && d >= 0 && d < B.ndm) {
-                const size_t idx = (size_t)d * B.nseg + seg;
-                const double sg = B.sigma[idx];
-                if (sg > 0.0) v = (float)(((double)B.X[(size_t)d * B.xpitch + t] - B.mu[idx]) / sg);
+        {
+            const int d = ds - 32 + k;
+            const bool row = d >= 0 && d < B.ndm;
+            const size_t idx = row ? (size_t)d * B.nseg + ts / B.L : 0;
+            const double mu = B.mu[idx], sg = B.sigma[idx];
+            const int32_t *Xr = B.X + (row ? (size_t)d * B.xpitch : 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = ts - 128 + lane + 64 * j;
+                float v = 0.f;
+                if (row && sg > 0.0 && t >= 0 && t < B.n_dd) v = (float)(((double)Xr[t] - mu) / sg);
+                o0[lane + 64 * j] = f2bf(v);
             }
-            o0[r * 256 + col] = f2bf(v);
         }
         const int per = B.nch / 64;
-        const int32_t *drow = B.delays + (size_t)ds * B.nch;
-        const int ta = ts - 128 + 16 * q;   // the thread's first sample of plane 1
-        const bool all_valid = ta >= 0 && ta + 15 < B.n_dd;
-        const bool any_valid = ta + 15 >= 0 && ta < B.n_dd;
-        for (int k = 0; k < 64; ++k) {
-            uint32_t ae[4] = {0u, 0u, 0u, 0u}, ao[4] = {0u, 0u, 0u, 0u};
-            if (any_valid) {
-                for (int ch = k * per + g; ch < (k + 1) * per; ch += 16) {
-                    const uint8_t *row = B.x + (size_t)ch * B.pitch;
-                    const int64_t off = (int64_t)ta + drow[ch];
-                    uint32_t d4[4];
-                    if (all_valid && (off & ~(int64_t)3) + 20 <= B.pitch) {
-                        const uint32_t *w = (const uint32_t *)(row + (off & ~(int64_t)3));
-                        const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3], w4 = w[4];
-                        const uint32_t sa = (uint32_t)(off & 3);
-                        d4[0] = __builtin_amdgcn_alignbyte(w1, w0, sa);
-                        d4[1] = __builtin_amdgcn_alignbyte(w2, w1, sa);
-                        d4[2] = __builtin_amdgcn_alignbyte(w3, w2, sa);
-                        d4[3] = __builtin_amdgcn_alignbyte(w4, w3, sa);
-                    } else {
+        const cint32 *drow = as_const(B.delays) + (size_t)ds * B.nch + (size_t)k * per;
+        const int ta = ts - 128 + 4 * lane;   // the lane's first sample
+        int32_t sv[4] = {0, 0, 0, 0};
+        for (int c0 = 0; c0 < per; c0 += 256) {
+            uint32_t ae = 0u, ao = 0u;
+            const int c1 = min(per, c0 + 256);
+            for (int c = c0; c < c1; c += 8) {
+                uint32_t w[8][2], shift[8];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            uint32_t v = 0u;
+                for (int i = 0; i < 8; ++i) {
+                    const int ci = min(c + i, c1 - 1), off = ts - 128 + drow[ci];
+                    const __amdgpu_buffer_rsrc_t rs = channel_rows(B, k * per + ci, c + i < c1);
+                    w[i][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, (off & ~3) + 4 * lane, 0, 0);
+                    w[i][1] = __builtin_amdgcn_raw_buffer_load_b32(rs, apart((off & ~3) + 4 * lane + 4), 0, 0);
+                    shift[i] = (uint32_t)(off & 3);
+                }
 #pragma unroll
-                            for (int b = 0; b < 4; ++b) {
-                                const int tj = ta + 4 * i + b;
-                                if (tj >= 0 && tj < B.n_dd) v |= (uint32_t)row[off + 4 * i + b] << (8 * b);
-                            }
-                            d4[i] = v;
-                        }
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        ae[i] += __builtin_amdgcn_perm(d4[i], d4[i], kSelEven);
-                        ao[i] += __builtin_amdgcn_perm(d4[i], d4[i], kSelOdd);
-                    }
+                for (int i = 0; i < 8; ++i) {
+                    const uint32_t word = __builtin_amdgcn_alignbyte(w[i][1], w[i][0], shift[i]);
+                    ae += __builtin_amdgcn_perm(word, word, kSelEven);
+                    ao += __builtin_amdgcn_perm(word, word, kSelOdd);
                 }
             }
-            __syncthreads();   // the previous sub-band's partial sums are no longer read
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                red[g][16 * q + 4 * i + 0] = (int32_t)(ae[i] & 0xFFFFu);
-                red[g][16 * q + 4 * i + 2] = (int32_t)(ae[i] >> 16);
-                red[g][16 * q + 4 * i + 1] = (int32_t)(ao[i] & 0xFFFFu);
-                red[g][16 * q + 4 * i + 3] = (int32_t)(ao[i] >> 16);
-            }
-            __syncthreads();
-            int32_t sv = 0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) sv += red[j][col];
-            // exact moments of the sub-band over the valid columns
-            int64_t s1 = valid ? (int64_t)sv : 0, s2 = valid ? (int64_t)sv * sv : 0, nv = valid ? 1 : 0;
-            s1 = wave_sum(s1);
-            s2 = wave_sum(s2);
-            nv = wave_sum(nv);
-            if (lane == 0) {
-                sh[0][wave] = s1;
-                sh[1][wave] = s2;
-                sh[2][wave] = nv;
-            }
-            __syncthreads();
-            const int64_t S1 = sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3];
-            const int64_t S2 = sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3];
-            const int64_t NV = sh[2][0] + sh[2][1] + sh[2][2] + sh[2][3];
-            double mu = 0.0, sg = 0.0;
-            if (NV > 0) mu_sigma(NV, S1, S2, mu, sg);
-            float v = 0.f;
-            if (valid && sg > 0.0) v = (float)(((double)sv - mu) / sg);
-            o1[k * 256 + col] = f2bf(v);
+            sv[0] += (int32_t)(ae & 0xFFFFu);
+            sv[2] += (int32_t)(ae >> 16);
+            sv[1] += (int32_t)(ao & 0xFFFFu);
+            sv[3] += (int32_t)(ao >> 16);
         }
-        __syncthreads();   // sh and red are reused by the next candidate
+        // exact moments of the sub-band over the valid columns
+        int64_t s1 = 0, s2 = 0;
+        int nv = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (ta + j >= 0 && ta + j < B.n_dd) {
+                s1 += sv[j];
+                s2 += (int64_t)sv[j] * sv[j];
+                nv += 1;
+            }
+        }
+        s1 = wave_sum(s1);
+        s2 = wave_sum(s2);
+        nv = (int)wave_sum((int64_t)nv);
+        double mu = 0.0, sg = 0.0;
+        if (nv > 0) mu_sigma(nv, s1, s2, mu, sg);
+        uint16_t v16[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float v = 0.f;
+            if (ta + j >= 0 && ta + j < B.n_dd && sg > 0.0) v = (float)(((double)sv[j] - mu) / sg);
+            v16[j] = f2bf(v);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o1[4 * lane + j] = v16[j];
     }
 }
 
@@ -1060,7 +1062,7 @@ static unsigned grid_1d(int64_t n) {
 hipError_t launch_snippets(const DevBeam *beams, int nbeams, const spl_candidate *cands, int64_t n, uint16_t *out,
                            hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const unsigned g = (unsigned)(n < 65536 ? n : 65536);
+    const unsigned g = (unsigned)(n < 65536 ? 16 * n : 1048576);
     hipLaunchKernelGGL(k_snippets, dim3(g), dim3(256), 0, s, beams, nbeams, cands, n, out);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
