@@ -1537,8 +1537,7 @@ extern "C" spl_status spl_inject_quantised(uint8_t *d_block, int64_t pitch, int6
     return SPL_OK;
 }
 
-extern "C" spl_status spl_ranker_snippets(const spl_batch *B, const spl_candidate *d_cands, int64_t n,
-                                          uint16_t *d_out, hipStream_t stream) {
+static spl_status check_snippets(const spl_batch *B, const spl_candidate *d_cands, int64_t n, const uint16_t *d_out) {
     if (!B) return fail(SPL_E_INVALID_ARG, "batch is NULL");
     if (n < 0 || (n > 0 && (!d_cands || !d_out))) return fail(SPL_E_INVALID_ARG, "bad candidate or output buffer");
     if (!B->tables_uploaded) return fail(SPL_E_INVALID_ARG, "spl_batch_set_workspace was not called");
@@ -1548,6 +1547,12 @@ extern "C" spl_status spl_ranker_snippets(const spl_batch *B, const spl_candidat
                         B->plans[b]->nch);
         if (!B->cur_x[b]) return fail(SPL_E_INVALID_ARG, "the batch has not run: no block for beam %d", b);
     }
+    return SPL_OK;
+}
+
+extern "C" spl_status spl_ranker_snippets(const spl_batch *B, const spl_candidate *d_cands, int64_t n,
+                                          uint16_t *d_out, hipStream_t stream) {
+    if (spl_status st = check_snippets(B, d_cands, n, d_out); st != SPL_OK) return st;
     HIP_TRY(launch_snippets((const DevBeam *)(B->ws + B->off_beams), B->nb, d_cands, n, d_out, stream));
     return SPL_OK;
 }
@@ -1555,13 +1560,16 @@ extern "C" spl_status spl_ranker_snippets(const spl_batch *B, const spl_candidat
 extern "C" spl_status spl_ranker_snippets_fine(const spl_batch *B, const spl_candidate *d_cands, int64_t n,
                                                double keep, uint16_t *d_out, hipStream_t stream) {
     if (!(keep > 0.0 && keep < 1.0)) return fail(SPL_E_INVALID_ARG, "spl_ranker_snippets_fine: keep must be in (0, 1)");
-    const spl_status st = spl_ranker_snippets(B, d_cands, n, d_out, stream);
+    const spl_status st = check_snippets(B, d_cands, n, d_out);
     if (st != SPL_OK || n == 0) return st;
-    for (int b = 0; b < B->nb; ++b)
+    int min_nch = INT32_MAX;
+    for (int b = 0; b < B->nb; ++b) {
         if (B->plans[b]->nch > 16384)
             return fail(SPL_E_UNSUPPORTED, "fine-DM snippets need nchans <= 16384 (beam %d has %d)", b,
                         B->plans[b]->nch);
-    HIP_TRY(launch_fine_dm((const DevBeam *)(B->ws + B->off_beams), B->nb, d_cands, n, keep, d_out, stream));
+        min_nch = std::min(min_nch, B->plans[b]->nch);
+    }
+    HIP_TRY(launch_fine_dm((const DevBeam *)(B->ws + B->off_beams), B->nb, min_nch, d_cands, n, keep, d_out, stream));
     return SPL_OK;
 }
 

@@ -10,6 +10,8 @@
 // (padded with zeros to a multiple of 32), reading the activation directly.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ranker.h"
 #include "spl_device.h"
 #include "spl_internal.h"
@@ -57,7 +59,7 @@ __device__ inline bool in_batch(const spl_candidate &cd, const DevBeam *beams, i
 // sub-bands of nch/64 adjacent channels summed along the delays of trial d*, each
 // standardised over its valid samples with the same exact-moment recipe.  Values
 // float((v - mu)/sigma) in binary64 -> BF16; entries outside the DM range or outside
-// [0, n_dd) are 0.
+// [0, n_dd) are 0.  With `fine` plane 0 is another kernel's.
 //
 // One wavefront per row of the two planes: 64 per candidate, so a few candidates fill the
 // chip, and nothing waits for other wavefronts.  Plane 1: lane l adds samples 4l .. 4l+3
@@ -67,7 +69,7 @@ __device__ inline bool in_batch(const spl_candidate &cd, const DevBeam *beams, i
 // 128 bytes: 72 us, where one workgroup per candidate with three barriers per sub-band
 // took 640 us.
 __global__ __launch_bounds__(256) void k_snippets(const DevBeam *__restrict__ beams, int nbeams,
-                                                  const spl_candidate *__restrict__ cands, int64_t n,
+                                                  const spl_candidate *__restrict__ cands, int64_t n, bool fine,
                                                   uint16_t *__restrict__ out) {
     constexpr uint32_t kSelEven = 0x0C020C00u;   // bytes 0, 2 -> 16-bit fields
     constexpr uint32_t kSelOdd = 0x0C030C01u;    // bytes 1, 3 -> 16-bit fields
@@ -77,13 +79,13 @@ __global__ __launch_bounds__(256) void k_snippets(const DevBeam *__restrict__ be
         const int k = 4 * (int)(item & 15) + wave;   // row of the planes
         uint16_t *o0 = out + (size_t)(item >> 4) * 2 * 64 * 256 + k * 256;
         uint16_t *o1 = o0 + 64 * 256;
-        if (!in_batch(cd, beams, nbeams)) {   // zero planes
+        if (!in_batch(cd, beams, nbeams) || (fine && cd.width < 1)) {   // zero planes
             for (int j = 0; j < 4; ++j) o0[lane + 64 * j] = o1[lane + 64 * j] = 0;
             continue;
         }
         const DevBeam &B = beams[cd.beam];
         const int ds = cd.dm_index, ts = cd.t_sample;
-        {
+        if (!fine) {
             const int d = ds - 32 + k;
             const bool row = d >= 0 && d < B.ndm;
             const size_t idx = row ? (size_t)d * B.nseg + ts / B.L : 0;
@@ -166,208 +168,274 @@ __global__ __launch_bounds__(256) void k_snippets(const DevBeam *__restrict__ be
 // the highest and lowest frequency).  The plane is standardised by the exact moments
 // of its valid entries (one mu, sigma for all rows, so the S/N falling off away from
 // DM* stays visible), float((v - mu)/sigma) in binary64 -> BF16, invalid entries 0.
-// One workgroup of 1024 threads per candidate: thread (g = tid/64, q = tid%64) owns
-// samples 4q .. 4q+3 of rows g, g+16, g+32, g+48.  Channels go in chunks of 8: the
-// delays of the 64 rows are computed into the LDS, then each channel's window of the
-// block (the 256 samples plus the spread of its 64 delays) is staged as four copies
-// shifted by 0..3 bytes, so every 4-sample read of any row is one aligned LDS dword
-// (a wave's 64 lanes read 64 consecutive dwords: no bank conflicts).  The three steps
-// are pipelined over chunks (sums of chunk k, staging of k+1, delays of k+2) with one
-// barrier per chunk, so the waves of the one workgroup a CU holds overlap them.  Windows wider
-// than the staging buffer (wide pulses: dDM grows with the width) are read from the
-// block directly, two aligned dwords per 4 samples.  Sums go through 16-bit pairs,
-// flushed before they exceed 256 channels (< 2^16).
-constexpr int kFineChunk = 8;
-constexpr int kFineWords = 512;   // staged dwords per channel and copy (window <= 2 KiB)
-
 __device__ inline int64_t fine_delay(double dd, double k, double tsamp) {
     const double v = (dd * k) / tsamp;
     if (!(fabs(v) < 1.0e9)) return v > 0 ? (int64_t)1 << 40 : -((int64_t)1 << 40);
     return llround(v);
 }
 
-__device__ inline uint32_t block_dword(const uint8_t *row, int64_t t, int64_t n_in) {
-    if (t >= 0 && t + 4 <= n_in) return *(const uint32_t *)(row + t);   // t is a multiple of 4 here
-    uint32_t v = 0u;
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-        if (t + b >= 0 && t + b < n_in) v |= (uint32_t)row[t + b] << (8 * b);
-    return v;
+// The same within +-2^30 (beyond, no entry is valid).
+__device__ inline int32_t fine_delay32(double dd, double k, double tsamp) {
+    const int64_t v = fine_delay(dd, k, tsamp);
+    return (int32_t)(v > (1 << 30) ? (1 << 30) : (v < -(1 << 30) ? -(1 << 30) : v));
 }
 
-__global__ __launch_bounds__(1024) void k_fine_dm(const DevBeam *__restrict__ beams, int nbeams,
-                                                  const spl_candidate *__restrict__ cands, int64_t n, double keep,
-                                                  uint16_t *__restrict__ out) {
-    constexpr uint32_t kSelEven = 0x0C020C00u;
-    constexpr uint32_t kSelOdd = 0x0C030C01u;
+// DM of row 32 and step between the rows of a candidate's fine plane.
+__device__ inline void fine_range(const DevBeam &B, const spl_candidate &cd, double keep, double &dm_star, double &step) {
+    const double w_ms = ((double)cd.width * B.tsamp) * 1000.0;
+    const double nu = ((B.fref + B.flo) * 0.5) / 1000.0;
+    const double bw = (double)B.nch * fabs(B.foff);
+    const double half = (((0.88622692545275801365 / keep) * w_ms) * ((nu * nu) * nu)) / (6.91e-3 * bw);
+    step = half / 32.0;
+    dm_star = B.dms[cd.dm_index];
+}
+
+// The 64 x 256 sums of a candidate, kept as int32 where its two BF16 planes of the same
+// size will be.  A workgroup owns one slice of the channels, each of its 4 wavefronts 16
+// rows.  The window of a channel that the 64 rows read (256 samples and the spread of
+// their delays) is staged in the LDS once, as many channels together as fit 12 KB (1 to
+// 16), the next ones' loads under way meanwhile; lane l adds samples 4l .. 4l+3 of a row
+// from two adjacent dwords.  Read from the block instead, the rows of wide pulses take
+// 25 KB of cache lines a channel, and that is what they wait for.  Windows beyond 12 KB
+// are read from the block all the same.
+// Delays are held in registers, lane = channel, their division by tsamp done only where
+// a product leaves a doubt.
+// Sums: `all` adds the four bytes as one word, the carries between them included, `odd`
+// bytes 1 and 3 as 16-bit fields; bytes 0 and 2 are all - 256 odd, before the fields are
+// full (256 channels), when their high bytes move on.
+//
+// The slices' sums meet in integer atomics.  256 candidates of the 4096-channel band, 205
+// of them 256 samples wide: 1.4 ms (of 1 sample: 1.05 ms), bound by the five vector and
+// one LDS instruction of every (row, channel) and by 3 wavefronts a SIMD not hiding all of
+// the reads' latency.  6.0 ms before, with a workgroup of 1024 threads per candidate that
+// read windows beyond 2 KB sample by sample: as long as the widest one took.
+constexpr int kFineRows = 16;          // rows of a wavefront
+constexpr int kFineWindow = 12288;     // bytes of the windows of a chunk of channels
+
+template <bool kAligned>
+__device__ __forceinline__ void put_sum(uint16_t *p, uint32_t v, bool add) {
+    if (kAligned && add) {
+        atomicAdd((int32_t *)p, (int32_t)v);
+    } else if (kAligned) {
+        *(uint32_t *)p = v;
+    } else {
+        p[0] = (uint16_t)v;
+        p[1] = (uint16_t)(v >> 16);
+    }
+}
+
+template <bool kAligned>
+__global__ __launch_bounds__(256, 3) void k_fine_sums(const DevBeam *__restrict__ beams, int nbeams,
+                                                      const spl_candidate *__restrict__ cands, int64_t n, double keep,
+                                                      int slices, uint16_t *__restrict__ out) {
     constexpr double kD = 4148.8064239;   // Eq. (1), MHz^2 pc^-1 cm^3 s
-    // three-stage pipeline over channel chunks: while chunk k is summed from stage buffer
-    // k&1, chunk k+1 is staged into the other buffer and the delays of chunk k+2 are
-    // computed into delay set (k+2)%3; one barrier per chunk
-    __shared__ uint32_t stage[2][kFineChunk][4][kFineWords];
-    __shared__ int32_t sdel[3][64][kFineChunk];
-    __shared__ int64_t sgs[3][kFineChunk];
-    __shared__ int32_t snw[3][kFineChunk];
-    __shared__ int64_t sh[3][16];
+    constexpr uint32_t kFields = 0x00FF00FFu;
+    constexpr int R = kFineRows, P = kFineWindow / 16 / 256;   // 16-byte pieces of a thread
+    __shared__ __align__(16) uint8_t windows[2][kFineWindow];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    const int g = tid >> 6, q = tid & 63;
+    for (int64_t item = blockIdx.x; item < n * slices; item += gridDim.x) {
+        const int64_t ci = item / slices;
+        const int slice = (int)(item - ci * slices);
+        const spl_candidate cd = cands[ci];
+        if (!in_batch(cd, beams, nbeams) || cd.width < 1) continue;   // uniform across the workgroup
+        const DevBeam &B = beams[cd.beam];
+        double dm_star, step;
+        fine_range(B, cd, keep, dm_star, step);
+        const double fch1 = B.fch1, foff = B.foff, tsamp = B.tsamp, rate = 1.0 / tsamp, k_ref = 1.0 / (B.fref * B.fref);
+        const int t_first = cd.t_sample - 128;   // sample of column 0
+        const int64_t pitch = B.pitch;
+        const int nch = B.nch, nblk = nch / 64;
+        const int blk0 = (int)((int64_t)nblk * slice / slices), blk1 = (int)((int64_t)nblk * (slice + 1) / slices);
+        // bytes of a channel's window: the lowest channel's rows spread most
+        const double widest = ((kD * (63.0 * step)) * ((1.0 / (B.flo * B.flo)) - k_ref)) * rate;
+        const bool staged = widest < (double)(kFineWindow - 320) && pitch < ((int64_t)1 << 25);
+        // (rounding, 16-byte starts, 64 dwords and the next)
+        const int win = staged ? ((int)widest + 2 + 16 + 264 + 15) & ~15 : kFineWindow;
+        int per_chunk = 16;
+        while (per_chunk * win > kFineWindow) per_chunk >>= 1;
+        // piece i lies in channel i / (win / 16) of the chunk, by a product (i < 768 pieces)
+        const uint32_t pieces = (uint32_t)win / 16, inv = ((1u << 22) + pieces - 1) / pieces;
+
+        auto k_of = [&](int blk) {
+            const double f = fch1 + (double)(64 * blk + lane) * foff;
+            return (1.0 / (f * f)) - k_ref;
+        };
+        // windows' first samples, lane = channel: row 0 has the least delays (they are monotone)
+        auto window_start = [&](int blk) {
+            const int32_t v = fine_delay32(kD * (dm_star + -32.0 * step), k_of(blk), tsamp);
+            return (int32_t)((uint32_t)v + (uint32_t)t_first) & ~15;
+        };
+        u32x4 piece[P];
+        auto load = [&](int blk, int c0, int32_t start) {
+            const uint64_t at = (uint64_t)(64 * blk) * (uint64_t)pitch, left = (uint64_t)nch * (uint64_t)pitch - at;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(B.x + at), 0, left >> 32 ? (int)0xFFFFFFFCu : (int)(uint32_t)left, 0x00027000);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const uint32_t i = (uint32_t)(tid + 256 * j), cc = (i * inv) >> 22;
+                const int c = c0 + (int)min(cc, (uint32_t)per_chunk - 1);   // past the chunk: not used
+                const uint32_t o = (uint32_t)c * (uint32_t)pitch + (uint32_t)__shfl(start, c) + 16u * (i - cc * pieces);
+                piece[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o, 0, 0));
+            }
+        };
+        auto store = [&](int buf) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const uint32_t i = (uint32_t)(tid + 256 * j);
+                if (i < pieces * (uint32_t)per_chunk) *(u32x4 *)(windows[buf] + 16u * i) = piece[j];
+            }
+        };
+
+        uint32_t all[R], odd[R], high[R][2];
+#pragma unroll
+        for (int r = 0; r < R; ++r) all[r] = odd[r] = high[r][0] = high[r][1] = 0u;
+        int32_t start = 0, start_next = 0;
+        int buf = 0;
+        if (staged && blk0 < blk1) {
+            start = window_start(blk0);
+            load(blk0, 0, start);
+            store(0);
+        }
+        for (int blk = blk0; blk < blk1; ++blk) {
+            if (((blk - blk0) & 3) == 0) {   // a byte is left and 256 channels follow: < 2^16
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t even = all[r] - (odd[r] << 8);
+                    high[r][0] += (even >> 8) & kFields;
+                    high[r][1] += (odd[r] >> 8) & kFields;
+                    odd[r] &= kFields;
+                    all[r] = (even & kFields) + (odd[r] << 8);
+                }
+            }
+            const double kc = k_of(blk);
+            int32_t del[R];
+            double row0 = (double)(R * wave - 32);   // or the compiler holds 16 products across the loop
+            asm volatile("" : "+v"(row0));
+            // the product with the rounded 1 / tsamp is off by less than 1e-15 of it
+            bool doubt = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double q = ((kD * (dm_star + (row0 + r) * step)) * kc) * rate, whole = rint(q);
+                doubt |= !((fabs(q) < 0.9e9) & (fabs(fabs(q - whole) - 0.5) > 1.0e-15 * fabs(q)));
+                del[r] = (int32_t)whole;
+            }
+            if (__any(doubt)) {
+#pragma unroll 1
+                for (int r = 0; r < R; ++r) {
+                    const int32_t v = fine_delay32(kD * (dm_star + (row0 + r) * step), kc, tsamp);
+#pragma unroll
+                    for (int i = 0; i < R; ++i) del[i] = i == r ? v : del[i];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) del[r] = (int32_t)((uint32_t)del[r] + (uint32_t)t_first);   // the row's first sample
+            if (staged) {
+                if (blk + 1 < blk1) start_next = window_start(blk + 1);
+#pragma unroll
+                for (int r = 0; r < R; ++r) del[r] = max(0, min(del[r] - start, win - 264));
+                for (int c0 = 0; c0 < 64; c0 += per_chunk) {
+                    __syncthreads();   // the chunk is staged, the one before no longer read
+                    const bool last = c0 + per_chunk >= 64, more = !last || blk + 1 < blk1;
+                    if (more) load(last ? blk + 1 : blk, last ? 0 : c0 + per_chunk, last ? start_next : start);
+                    const uint8_t *base = windows[buf] + 4 * lane;
+#pragma unroll 1
+                    for (int c = c0; c < c0 + per_chunk; ++c, base += win) {
+#pragma unroll
+                        for (int r0 = 0; r0 < R; r0 += 8) {   // 8 rows' reads under way together
+                            uint32_t w[8][2];
+                            int at[8];
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) {
+                                at[r] = __builtin_amdgcn_readlane(del[r0 + r], c);
+                                const uint32_t *p = (const uint32_t *)(base + (at[r] & ~3));
+                                w[r][0] = p[0];
+                                w[r][1] = p[1];
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) {
+                                const uint32_t word = __builtin_amdgcn_alignbyte(w[r][1], w[r][0], (uint32_t)at[r]);
+                                all[r0 + r] += word;
+                                odd[r0 + r] += __builtin_amdgcn_perm(word, word, 0x0C030C01u);
+                            }
+                        }
+                    }
+                    buf ^= 1;
+                    if (more) store(buf);
+                }
+                start = start_next;
+            } else {
+#pragma unroll 1
+                for (int c = 0; c < 64; ++c) {
+                    const __amdgpu_buffer_rsrc_t rs = channel_rows(B, 64 * blk + c, true);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int at = __builtin_amdgcn_readlane(del[r], c), o = (at & ~3) + 4 * lane;
+                        const uint32_t w0 = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0);
+                        const uint32_t w1 = __builtin_amdgcn_raw_buffer_load_b32(rs, apart(o + 4), 0, 0);
+                        const uint32_t word = __builtin_amdgcn_alignbyte(w1, w0, (uint32_t)at);
+                        all[r] += word;
+                        odd[r] += __builtin_amdgcn_perm(word, word, 0x0C030C01u);
+                    }
+                }
+            }
+        }
+        __syncthreads();   // the windows are no longer read
+        uint16_t *o = out + (((size_t)ci * 64 + R * wave) * 256 + 4 * lane) * 2;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t even = all[r] - (odd[r] << 8);
+            put_sum<kAligned>(o + 512 * r, 256u * (high[r][0] & 0xFFFFu) + (even & 0xFFFFu), slices > 1);
+            put_sum<kAligned>(o + 512 * r + 2, 256u * (high[r][1] & 0xFFFFu) + (odd[r] & 0xFFFFu), slices > 1);
+            put_sum<kAligned>(o + 512 * r + 4, 256u * (high[r][0] >> 16) + (even >> 16), slices > 1);
+            put_sum<kAligned>(o + 512 * r + 6, 256u * (high[r][1] >> 16) + (odd[r] >> 16), slices > 1);
+        }
+    }
+}
+
+// The sums of a candidate standardised into its plane 0 (of 1024 threads, thread (g = tid / 64,
+// q = tid % 64) takes columns 4q .. 4q+3 of rows g, g + 16, g + 32, g + 48).
+template <bool kAligned>
+__global__ __launch_bounds__(1024) void k_fine_plane(const DevBeam *__restrict__ beams, int nbeams,
+                                                     const spl_candidate *__restrict__ cands, int64_t n, double keep,
+                                                     uint16_t *out) {
+    constexpr double kD = 4148.8064239;
+    __shared__ int64_t sh[3][16];
+    const int lane = lane_id(), wave = wave_id();
+    const int g = wave, q = lane;
     for (int64_t ci = blockIdx.x; ci < n; ci += gridDim.x) {
         const spl_candidate cd = cands[ci];
+        if (!in_batch(cd, beams, nbeams) || cd.width < 1) continue;   // uniform across the workgroup
         uint16_t *o0 = out + (size_t)ci * 2 * 64 * 256;
-        const int bsafe = cd.beam < 0 || cd.beam >= nbeams ? 0 : cd.beam;
-        const bool ok = cd.beam >= 0 && cd.beam < nbeams && cd.dm_index >= 0 && cd.dm_index < beams[bsafe].ndm &&
-                        cd.t_sample >= 0 && cd.t_sample < beams[bsafe].n_out && cd.width >= 1;
-        if (!ok) {   // both planes zero (plane 1 was written by the snippet kernel before)
-            for (int e = tid; e < 2 * 64 * 256; e += 1024) o0[e] = 0;
-            continue;   // uniform across the workgroup
-        }
         const DevBeam &B = beams[cd.beam];
-        const double w_ms = ((double)cd.width * B.tsamp) * 1000.0;
-        const double nu = ((B.fref + B.flo) * 0.5) / 1000.0;
-        const double bw = (double)B.nch * fabs(B.foff);
-        const double half = (((0.88622692545275801365 / keep) * w_ms) * ((nu * nu) * nu)) / (6.91e-3 * bw);
-        const double step = half / 32.0;
-        const double dm_star = B.dms[cd.dm_index];
+        double dm_star, step;
+        fine_range(B, cd, keep, dm_star, step);
         const double k_lo = (1.0 / (B.flo * B.flo)) - (1.0 / (B.fref * B.fref));
-        const int64_t t_first = (int64_t)cd.t_sample - 128;   // sample of column 0
-        const int64_t ta = t_first + 4 * q;                    // the thread's first sample
+        const int64_t ta = (int64_t)cd.t_sample - 128 + 4 * q;   // the thread's first sample
+        int32_t acc[4][4];
         // bit 4i + j: sample j (0..3) of row g + 16i is valid (ta + j + smin >= 0 and
         // ta + j + smax < n_in, the extremes of the row's delays)
         uint32_t vmask = 0u;
+        int64_t s1 = 0, s2 = 0, nv = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = g + 16 * i;
             const int64_t s_lo = fine_delay(kD * (dm_star + (double)(r - 32) * step), k_lo, B.tsamp);
             const int64_t smin = s_lo < 0 ? s_lo : 0, smax = s_lo > 0 ? s_lo : 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (ta + j + smin >= 0 && ta + j + smax < (int64_t)B.n_in) vmask |= 1u << (4 * i + j);
-        }
-        const int nchunks = (B.nch + kFineChunk - 1) / kFineChunk;
-
-        // delays of chunk `chunk` into set `set`: wavefront w (< kFineChunk) takes channel
-        // w, lane = row (Eq. (1) as a plan computes it).  The delays are monotone in the
-        // row, so rows 0 and 63 bound the channel's window; each lane then stores its
-        // row's LDS byte offset into the staged copies ((rel & 3) selects the copy,
-        // rel >> 2 the dword, rel = t_first + delay - window start), or the raw delay when
-        // the channel is read from the block (window too wide, or any offset out of range)
-        auto delays = [&](int chunk, int set) {
-            const int cc = wave, rr = lane;
-            const int c0 = chunk * kFineChunk, nc = min(kFineChunk, B.nch - c0);
-            const double f = B.fch1 + (double)(c0 + cc) * B.foff;
-            const double kc = cc < nc ? (1.0 / (f * f)) - (1.0 / (B.fref * B.fref)) : 0.0;
-            const int64_t sv = fine_delay(kD * (dm_star + (double)(rr - 32) * step), kc, B.tsamp);
-            const int64_t s0 = __shfl(sv, 0), s63 = __shfl(sv, 63);
-            const int64_t lo = s0 < s63 ? s0 : s63, hi = s0 < s63 ? s63 : s0;
-            const int64_t gs = (t_first + lo) & ~(int64_t)3;
-            const int64_t nw = ((t_first + 252 + hi - gs) >> 2) + 1;   // dwords holding every read
-            const int64_t rel = t_first + sv - gs;
-            const bool bad = rel < 0 || (rel >> 2) + 63 > nw - 1;
-            const bool staged = cc < nc && nw + 1 <= kFineWords && !__any(bad);
-            sdel[set][rr][cc] =
-                staged ? (int32_t)(cc * (4 * kFineWords * 4) + (int)(rel & 3) * (kFineWords * 4) + (int)(rel >> 2) * 4)
-                       : (int32_t)(sv > (1 << 30) ? (1 << 30) : (sv < -(1 << 30) ? -(1 << 30) : sv));
-            if (lane == 0) {
-                sgs[set][cc] = gs;
-                snw[set][cc] = staged ? (int32_t)nw : 0;   // 0: read the block
-            }
-        };
-        // the window of every channel of chunk `chunk` as four byte-shifted copies
-        auto stage_chunk = [&](int chunk, int set, int buf) {
-            const int c0 = chunk * kFineChunk;
-            for (int e = tid; e < kFineChunk * kFineWords; e += 1024) {
-                const int cc = e / kFineWords, i = e % kFineWords;
-                if (i < snw[set][cc]) {
-                    const uint8_t *row = B.x + (size_t)(c0 + cc) * B.pitch;
-                    const int64_t t = sgs[set][cc] + 4 * (int64_t)i;
-                    const uint32_t w0 = block_dword(row, t, B.n_in), w1 = block_dword(row, t + 4, B.n_in);
-                    stage[buf][cc][0][i] = w0;
-                    stage[buf][cc][1][i] = __builtin_amdgcn_alignbyte(w1, w0, 1);
-                    stage[buf][cc][2][i] = __builtin_amdgcn_alignbyte(w1, w0, 2);
-                    stage[buf][cc][3][i] = __builtin_amdgcn_alignbyte(w1, w0, 3);
-                }
-            }
-        };
-
-        int32_t acc[4][4];
-        uint32_t ae[4], ao[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            ae[i] = ao[i] = 0u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = 0;
-        }
-        int pending = 0;   // channels in the 16-bit pair sums
-
-        if (wave < kFineChunk) {
-            delays(0, 0);
-            if (nchunks > 1) delays(1, 1);
-        }
-        __syncthreads();
-        stage_chunk(0, 0, 0);
-        __syncthreads();
-        for (int k = 0; k < nchunks; ++k) {
-            const int set = k % 3, buf = k & 1;
-            const int c0 = k * kFineChunk, nc = min(kFineChunk, B.nch - c0);
-            if (pending + nc > 256) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[i][0] += (int32_t)(ae[i] & 0xFFFFu);
-                    acc[i][2] += (int32_t)(ae[i] >> 16);
-                    acc[i][1] += (int32_t)(ao[i] & 0xFFFFu);
-                    acc[i][3] += (int32_t)(ao[i] >> 16);
-                    ae[i] = ao[i] = 0u;
-                }
-                pending = 0;
-            }
-            pending += nc;
-            for (int cc = 0; cc < nc; ++cc) {
-                const int nw = snw[set][cc];   // the same for the whole workgroup
-                if (nw > 0) {
-                    const uint8_t *lbase = (const uint8_t *)&stage[buf][0][0][0] + 4 * q;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint32_t word = *(const uint32_t *)(lbase + sdel[set][g + 16 * i][cc]);
-                        ae[i] += __builtin_amdgcn_perm(word, word, kSelEven);
-                        ao[i] += __builtin_amdgcn_perm(word, word, kSelOdd);
-                    }
-                } else {
-                    const uint8_t *row = B.x + (size_t)(c0 + cc) * B.pitch;
-                    for (int i = 0; i < 4; ++i) {
-                        const int64_t t = ta + sdel[set][g + 16 * i][cc];
-                        const int64_t t4 = t & ~(int64_t)3;
-                        const uint32_t word = __builtin_amdgcn_alignbyte(block_dword(row, t4 + 4, B.n_in),
-                                                                         block_dword(row, t4, B.n_in),
-                                                                         (uint32_t)(t & 3));
-                        ae[i] += __builtin_amdgcn_perm(word, word, kSelEven);
-                        ao[i] += __builtin_amdgcn_perm(word, word, kSelOdd);
-                    }
-                }
-            }
-            if (k + 1 < nchunks) stage_chunk(k + 1, (k + 1) % 3, (k + 1) & 1);
-            if (k + 2 < nchunks && wave < kFineChunk) delays(k + 2, (k + 2) % 3);
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[i][0] += (int32_t)(ae[i] & 0xFFFFu);
-            acc[i][2] += (int32_t)(ae[i] >> 16);
-            acc[i][1] += (int32_t)(ao[i] & 0xFFFFu);
-            acc[i][3] += (int32_t)(ao[i] >> 16);
-        }
-        // exact moments of the plane's valid entries
-        int64_t s1 = 0, s2 = 0, nv = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
+            const uint16_t *p = o0 + 2 * (256 * r + 4 * q);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (vmask >> (4 * i + j) & 1u) {
+                acc[i][j] = kAligned ? *(const int32_t *)(p + 2 * j)
+                                     : (int32_t)((uint32_t)p[2 * j] | (uint32_t)p[2 * j + 1] << 16);
+                if (ta + j + smin >= 0 && ta + j + smax < (int64_t)B.n_in) {
+                    vmask |= 1u << (4 * i + j);
                     s1 += acc[i][j];
                     s2 += (int64_t)acc[i][j] * acc[i][j];
                     nv += 1;
                 }
             }
         }
+        // exact moments of the plane's valid entries
         s1 = wave_sum(s1);
         s2 = wave_sum(s2);
         nv = wave_sum(nv);
@@ -376,7 +444,7 @@ __global__ __launch_bounds__(1024) void k_fine_dm(const DevBeam *__restrict__ be
             sh[1][wave] = s2;
             sh[2][wave] = nv;
         }
-        __syncthreads();
+        __syncthreads();   // and every sum is read before the plane takes its place
         int64_t S1 = 0, S2 = 0, NV = 0;
         for (int k = 0; k < 16; ++k) {
             S1 += sh[0][k];
@@ -1059,22 +1127,44 @@ static unsigned grid_1d(int64_t n) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
-hipError_t launch_snippets(const DevBeam *beams, int nbeams, const spl_candidate *cands, int64_t n, uint16_t *out,
-                           hipStream_t s) {
-    if (n <= 0) return hipSuccess;
+static hipError_t launch_planes(const DevBeam *beams, int nbeams, const spl_candidate *cands, int64_t n, bool fine,
+                                uint16_t *out, hipStream_t s) {
     const unsigned g = (unsigned)(n < 65536 ? 16 * n : 1048576);
-    hipLaunchKernelGGL(k_snippets, dim3(g), dim3(256), 0, s, beams, nbeams, cands, n, out);
+    hipLaunchKernelGGL(k_snippets, dim3(g), dim3(256), 0, s, beams, nbeams, cands, n, fine, out);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_fine_dm(const DevBeam *beams, int nbeams, const spl_candidate *cands, int64_t n, double keep,
-                          uint16_t *out, hipStream_t s) {
+hipError_t launch_snippets(const DevBeam *beams, int nbeams, const spl_candidate *cands, int64_t n, uint16_t *out,
+                           hipStream_t s) {
+    return n <= 0 ? hipSuccess : launch_planes(beams, nbeams, cands, n, false, out, s);
+}
+
+hipError_t launch_fine_dm(const DevBeam *beams, int nbeams, int min_nch, const spl_candidate *cands, int64_t n,
+                          double keep, uint16_t *out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const unsigned g = (unsigned)(n < 65536 ? n : 65536);
-    hipLaunchKernelGGL(k_fine_dm, dim3(g), dim3(1024), 0, s, beams, nbeams, cands, n, keep, out);
+    const bool aligned = ((uintptr_t)out & 3) == 0;   // atomics, and whole words
+    // Slices of the channels: 1536 workgroups are two turns of the 3 that a CU holds (256
+    // candidates in 6 slices 1.39 ms, in 4 slices 1.51, in 8 1.40), but more than 24 atomics
+    // on one word cost more than they share (32 candidates: 8 slices 393 us, 16 320, 24 283,
+    // 48 407; 8 candidates: 24 slices 176 us, 64 205).
+    int64_t slices = aligned ? std::min<int64_t>(1536 / n, 24) : 1;
+    slices = std::max<int64_t>(1, std::min<int64_t>(slices, min_nch / 64));
+    if (slices > 1) {
+        if (hipError_t e = launch_zero_f32((float *)out, n * 64 * 256, s); e != hipSuccess) return e;
+    }
+    const unsigned g = (unsigned)std::min<int64_t>(n * slices, 1048576), gp = (unsigned)std::min<int64_t>(n, 65536);
+    if (aligned) {
+        hipLaunchKernelGGL(k_fine_sums<true>, dim3(g), dim3(256), 0, s, beams, nbeams, cands, n, keep, (int)slices, out);
+        SPL_HIP_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_fine_plane<true>, dim3(gp), dim3(1024), 0, s, beams, nbeams, cands, n, keep, out);
+    } else {
+        hipLaunchKernelGGL(k_fine_sums<false>, dim3(g), dim3(256), 0, s, beams, nbeams, cands, n, keep, (int)slices, out);
+        SPL_HIP_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_fine_plane<false>, dim3(gp), dim3(1024), 0, s, beams, nbeams, cands, n, keep, out);
+    }
     SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
+    return launch_planes(beams, nbeams, cands, n, true, out, s);   // plane 1, and the zero planes
 }
 
 hipError_t launch_gemm(const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float *C, int64_t ldc, int M,
