@@ -343,7 +343,7 @@ static bool shared_tables(PlanLayout &L) {
         double best = (double)p.ndm * p.nch / kRowAddsPerClock;   // clocks per output sample
         for (const SharedShape &s : shapes) {
             SharedTables t;
-            if (!build_shared(p.delays.data(), p.ndm, p.nch, s, table_bytes(p), &t)) continue;
+            if (!build_shared(p.delays.data(), p.ndm, p.nch, s, table_bytes(p), best * (2 * s.half()), &t)) continue;
             const double c = t.clocks / (2 * s.half());
             if (c < best) {
                 best = c;
@@ -444,6 +444,26 @@ static Tiles default_row_tiles(const spl_plan &p) {
     return t;
 }
 
+// The largest spread of a channel's delays over td consecutive trials.
+static int widest_tile(const spl_plan &p, int td) {
+    std::vector<int32_t> lo(p.nch), hi(p.nch);
+    int widest = 0;
+    for (int d0 = 0; d0 < p.ndm; d0 += td) {
+        const int32_t *row = p.delays.data() + (size_t)d0 * p.nch;
+        std::copy(row, row + p.nch, lo.begin());
+        std::copy(row, row + p.nch, hi.begin());
+        for (int d = d0 + 1; d < std::min(p.ndm, d0 + td); ++d) {
+            row += p.nch;
+            for (int c = 0; c < p.nch; ++c) {
+                lo[c] = std::min(lo[c], row[c]);
+                hi[c] = std::max(hi[c], row[c]);
+            }
+        }
+        for (int c = 0; c < p.nch; ++c) widest = std::max(widest, hi[c] - lo[c]);
+    }
+    return widest;
+}
+
 // The 16-wavefront tiles where shared rows are modelled to take less time than the row
 // staging of the tiles above on the whole chip (tiles per CU, rounded up, times the clocks
 // of one): a few large tiles leave CUs idle that many small ones would fill.
@@ -459,9 +479,11 @@ static Tiles default_tiles(PlanLayout &L, int64_t beams) {
     const double by_row = rounds(td, tt) * ((double)td * tt * p.nch / kRowAddsPerClock);
     const double by_sums = rounds(L.sh.shape.td(), ts) * (L.sh.clocks / L.sh.ntiles);
     if (by_sums < by_row) {
+        // (the row staging of the shape has to take the plan too: layout_plan's limits)
         static const int shapes[][2] = {{4, 2}, {2, 2}, {4, 1}};
         for (const auto &sh : shapes) {
-            if (!tile_fits(p, 16 * sh[0], sh[1])) continue;
+            const int bytes = 256 * sh[1] + 32 + (int)align_up((size_t)widest_tile(p, 16 * sh[0]), 16);
+            if (bytes > 2048 || !dedisp_shape_supported(sh[0], sh[1], 16, bytes <= 1024 ? 1 : 2, 1)) continue;
             Tiles t;
             t.dw = sh[0];
             t.j = sh[1];

@@ -3,7 +3,11 @@
 #include "shared_sums.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
+#include <new>
+#include <system_error>
+#include <thread>
 
 namespace spl {
 
@@ -99,176 +103,228 @@ bool make_run(const int32_t *const *rows, int td, int nch, int c0, const SharedS
     return true;
 }
 
-}  // namespace
-
-bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, SharedTables *out) {
-    const int td = sh.td(), ntiles = (ndm + td - 1) / td;
-    if (td < 1 || td > kMaxTrials || nch < kSharedChans || nch > 65536 || ndm < 1) return false;
-    const int max_runs = (kSharedBlock - 1) / sh.dw;   // rows of a chunk's runs fit the block
-    const size_t per_sub = kTaps * sizeof(uint32_t) + kSharedChans * sizeof(int32_t);
-    const size_t per_chunk = (size_t)kSumming * kSharedBlock * sizeof(int32_t);
-    std::vector<SharedTile> tiles(ntiles);
+// The tables of one tile, counted from its own first run.
+struct Tile {
     std::vector<SharedItem> items;
     std::vector<int32_t> blocks, starts;
     std::vector<uint32_t> taps;
     std::vector<int> channels;   // of every chunk
     int buffer = 0;
     double clocks = 0;
+    bool ok = false;
+};
+
+// (delay rows lie `stride` entries apart)
+void build_tile(const int32_t *delays, int stride, int ndm, int nch, const SharedShape &sh, int k, Tile *o) {
+    const int td = sh.td();
+    const int max_runs = (kSharedBlock - 1) / sh.dw;   // rows of a chunk's runs fit the block
     std::vector<Run> in_chunk;
     const int32_t *rows[kMaxTrials];
-    // the 16 channels ahead of a run, copied together (the delay rows lie nch entries apart)
+    // the channels ahead of a run, copied together
     std::vector<int32_t> block((size_t)kMaxTrials * 64);
-    for (int k = 0; k < ntiles; ++k) {
-        tiles[k].round = (int32_t)(items.size() / sh.np);
-        tiles[k].chunk = (int32_t)channels.size();
-        int used_bytes = 0;
-        auto close_chunk = [&]() {
-            if (in_chunk.empty()) return;
-            const size_t base = blocks.size();
-            blocks.resize(base + (size_t)kSumming * kSharedBlock, 0);
-            auto block = [&](int wave) { return blocks.data() + base + (size_t)wave * kSharedBlock; };
-            for (int w = 0; w < kSumming; ++w) block(w)[0] = (int32_t)in_chunk.size();
-            std::vector<SharedItem> first_item;   // of every run
-            int lds = 0, chans = 0, groups = 0;
-            for (size_t ri = 0; ri < in_chunk.size(); ++ri) {
-                const Run &r = in_chunk[ri];
-                const int sub = (int)(taps.size() / kTaps);
-                const int rb = r.groups * 256;
-                // all 16 channels read exist: a run at the band's end moves up
-                const int col0 = std::min(r.c0, nch - kSharedChans), skip = r.c0 - col0;
-                int32_t start[kSharedChans];
-                for (int c = 0; c < kSharedChans; ++c)
-                    start[c] = r.start[std::max(0, std::min(c - skip, r.n - 1))];
-                SharedItem it{};
-                it.sub = sub;
-                it.row_bytes = rb;
-                it.c0 = col0;
-                it.lds = lds;
-                first_item.push_back(it);
-                groups += r.groups;
-                for (int i = 0; i < kTaps; ++i) {
-                    const int q = i / 16, p = std::min(4 * (i % 4) + i / 4 % 4, r.patterns - 1);
-                    uint32_t v = 0;
-                    for (int u = 0; u < 4; ++u) {
-                        const int c = 8 * (u >> 1) + 2 * q + (u & 1) - skip;
-                        if (c >= 0 && c < r.n) v |= 1u << (24 + u) | 8u * r.e[p][c] << (6 * u);
-                    }
-                    taps.push_back(v);
+    int used_bytes = 0;
+    auto close_chunk = [&]() {
+        if (in_chunk.empty()) return;
+        const size_t base = o->blocks.size();
+        o->blocks.resize(base + (size_t)kSumming * kSharedBlock, 0);
+        auto block = [&](int wave) { return o->blocks.data() + base + (size_t)wave * kSharedBlock; };
+        for (int w = 0; w < kSumming; ++w) block(w)[0] = (int32_t)in_chunk.size();
+        std::vector<SharedItem> first_item;   // of every run
+        int lds = 0, chans = 0, groups = 0;
+        for (size_t ri = 0; ri < in_chunk.size(); ++ri) {
+            const Run &r = in_chunk[ri];
+            const int sub = (int)(o->taps.size() / kTaps);
+            const int rb = r.groups * 256;
+            // all 16 channels read exist: a run at the band's end moves up
+            const int col0 = std::min(r.c0, nch - kSharedChans), skip = r.c0 - col0;
+            int32_t start[kSharedChans];
+            for (int c = 0; c < kSharedChans; ++c)
+                start[c] = r.start[std::max(0, std::min(c - skip, r.n - 1))];
+            SharedItem it{};
+            it.sub = sub;
+            it.row_bytes = rb;
+            it.c0 = col0;
+            it.lds = lds;
+            first_item.push_back(it);
+            groups += r.groups;
+            for (int i = 0; i < kTaps; ++i) {
+                const int q = i / 16, p = std::min(4 * (i % 4) + i / 4 % 4, r.patterns - 1);
+                uint32_t v = 0;
+                for (int u = 0; u < 4; ++u) {
+                    const int c = 8 * (u >> 1) + 2 * q + (u & 1) - skip;
+                    if (c >= 0 && c < r.n) v |= 1u << (24 + u) | 8u * r.e[p][c] << (6 * u);
                 }
-                for (int q = 0; q < 4; ++q)
-                    for (int u = 0; u < 4; ++u) starts.push_back(start[8 * (u >> 1) + 2 * q + (u & 1)]);
-                for (int d = 0; d < td; ++d)
-                    block(d / sh.dw)[1 + ri * sh.dw + d % sh.dw] = lds + r.pattern[d] * rb + r.shift[d] * 4;
-                lds += r.patterns * rb;
-                chans += r.n;
+                o->taps.push_back(v);
             }
-            // the chunk's groups dealt to the staging wavefronts in items of one run each; an
-            // item costs its groups and about one more, `most` is the least that a wavefront
-            // can be asked for
-            std::vector<std::vector<SharedItem>> part;
-            int rounds = 1;
-            for (int most = 1 + groups / sh.np;; ++most) {
-                part.assign(sh.np, {});
-                rounds = 1;
-                size_t run = 0;
-                int g = 0;
-                for (int w = 0; w < sh.np; ++w) {
-                    for (int left = most; left > 1 && run < in_chunk.size();) {
-                        const Run &r = in_chunk[run];
-                        const int ng = std::min(std::min(left - 1, r.groups - g), sh.gp);
-                        SharedItem it = first_item[run];
-                        it.png = (int32_t)((uint32_t)r.patterns | (uint32_t)r.n << 8 | (uint32_t)g << 16 |
-                                           (uint32_t)ng << 24);
-                        it.lds += g * 256;
-                        part[w].push_back(it);
-                        left -= ng + 1;
-                        g += ng;
-                        if (g == r.groups) {
-                            ++run;
-                            g = 0;
-                        }
-                    }
-                    rounds = std::max(rounds, (int)part[w].size());
-                }
-                if (run == in_chunk.size()) break;
-            }
-            for (int i = 0; i < rounds; ++i)
-                for (int w = 0; w < sh.np; ++w) {
-                    // an empty item names an existing run: its tables are loaded all the same
-                    SharedItem it = i < (int)part[w].size() ? part[w][i] : part[w].empty() ? first_item[0] : part[w].back();
-                    if (i >= (int)part[w].size()) it.png &= 0xFFFFFF;
-                    it.last = i + 1 == rounds;
-                    items.push_back(it);
-                }
-            buffer = std::max(buffer, lds);
-            channels.push_back(chans);
-            // modelled clocks of a CU: a staging wavefront takes about 650 per group, 690 per
-            // item and 470 for the chunk's hand-over (the 4096-channel band: 4850 per chunk of
-            // 21.8 groups in 1.16 rounds)
-            clocks += (double)groups / sh.np * 650.0 + rounds * 690.0 + 470.0;
-            in_chunk.clear();
-            used_bytes = 0;
-        };
-        int c = 0, block_c0 = 0, block_n = 0;
-        while (c < nch) {
-            if (c + kSharedChans > block_c0 + block_n && block_c0 + block_n < nch) {
-                block_c0 = c;
-                block_n = std::min(64, nch - c);
-                for (int d = 0; d < td; ++d) {
-                    const int ds = std::min(k * td + d, ndm - 1);
-                    std::memcpy(block.data() + (size_t)d * 64, delays + (size_t)ds * nch + c,
-                                (size_t)block_n * sizeof(int32_t));
-                    rows[d] = block.data() + (size_t)d * 64;
-                }
-            }
-            Run r;
-            if (!make_run(rows, td, block_n, c - block_c0, sh, &r)) return false;
-            r.c0 = c;
-            const int bytes = r.patterns * r.groups * 256;
-            if (used_bytes + bytes > kSharedBuffer || (int)in_chunk.size() == max_runs) close_chunk();
-            used_bytes += bytes;
-            in_chunk.push_back(r);
-            c += r.n;
+            for (int q = 0; q < 4; ++q)
+                for (int u = 0; u < 4; ++u) o->starts.push_back(start[8 * (u >> 1) + 2 * q + (u & 1)]);
+            for (int d = 0; d < td; ++d)
+                block(d / sh.dw)[1 + ri * sh.dw + d % sh.dw] = lds + r.pattern[d] * rb + r.shift[d] * 4;
+            lds += r.patterns * rb;
+            chans += r.n;
         }
-        close_chunk();
-        tiles[k].nrounds = (int32_t)(items.size() / sh.np) - tiles[k].round;
-        tiles[k].nchunks = (int32_t)channels.size() - tiles[k].chunk;
-        // the 16-bit fields hold a low byte and 256 channels of 255: the high bytes move on
-        // before the chunk that would exceed that
-        const int *chans = channels.data() + tiles[k].chunk;
-        for (int j = 0, pending = 0; j < tiles[k].nchunks; ++j) {
-            pending += chans[j];
-            if (j + 1 < tiles[k].nchunks && pending + chans[j + 1] <= 256) continue;
-            for (int w = 0; w < kSumming; ++w)
-                blocks[((size_t)(tiles[k].chunk + j) * kSumming + w) * kSharedBlock] |= pending << 8;
-            pending = 0;
+        // the chunk's groups dealt to the staging wavefronts in items of one run each; an
+        // item costs its groups and about one more, `most` is the least that a wavefront
+        // can be asked for
+        std::vector<std::vector<SharedItem>> part;
+        int rounds = 1;
+        for (int most = 1 + groups / sh.np;; ++most) {
+            part.assign(sh.np, {});
+            rounds = 1;
+            size_t run = 0;
+            int g = 0;
+            for (int w = 0; w < sh.np; ++w) {
+                for (int left = most; left > 1 && run < in_chunk.size();) {
+                    const Run &r = in_chunk[run];
+                    const int ng = std::min(std::min(left - 1, r.groups - g), sh.gp);
+                    SharedItem it = first_item[run];
+                    it.png = (int32_t)((uint32_t)r.patterns | (uint32_t)r.n << 8 | (uint32_t)g << 16 |
+                                       (uint32_t)ng << 24);
+                    it.lds += g * 256;
+                    part[w].push_back(it);
+                    left -= ng + 1;
+                    g += ng;
+                    if (g == r.groups) {
+                        ++run;
+                        g = 0;
+                    }
+                }
+                rounds = std::max(rounds, (int)part[w].size());
+            }
+            if (run == in_chunk.size()) break;
         }
-        if ((taps.size() / kTaps) * per_sub + channels.size() * per_chunk +
-                items.size() * sizeof(SharedItem) + ntiles * sizeof(SharedTile) + 256 >
-            max_bytes)
-            return false;
+        for (int i = 0; i < rounds; ++i)
+            for (int w = 0; w < sh.np; ++w) {
+                // an empty item names an existing run: its tables are loaded all the same
+                SharedItem it = i < (int)part[w].size() ? part[w][i] : part[w].empty() ? first_item[0] : part[w].back();
+                if (i >= (int)part[w].size()) it.png &= 0xFFFFFF;
+                it.last = i + 1 == rounds;
+                o->items.push_back(it);
+            }
+        o->buffer = std::max(o->buffer, lds);
+        o->channels.push_back(chans);
+        // modelled clocks of a CU: a staging wavefront takes about 650 per group, 690 per
+        // item and 470 for the chunk's hand-over (the 4096-channel band: 4850 per chunk of
+        // 21.8 groups in 1.16 rounds)
+        o->clocks += (double)groups / sh.np * 650.0 + rounds * 690.0 + 470.0;
+        in_chunk.clear();
+        used_bytes = 0;
+    };
+    int c = 0, block_c0 = 0, block_n = 0;
+    while (c < nch) {
+        if (c + kSharedChans > block_c0 + block_n && block_c0 + block_n < nch) {
+            block_c0 = c;
+            block_n = std::min(64, nch - c);
+            for (int d = 0; d < td; ++d) {
+                const int ds = std::min(k * td + d, ndm - 1);
+                std::memcpy(block.data() + (size_t)d * 64, delays + (size_t)ds * stride + c,
+                            (size_t)block_n * sizeof(int32_t));
+                rows[d] = block.data() + (size_t)d * 64;
+            }
+        }
+        Run r;
+        if (!make_run(rows, td, block_n, c - block_c0, sh, &r)) return;
+        r.c0 = c;
+        const int bytes = r.patterns * r.groups * 256;
+        if (used_bytes + bytes > kSharedBuffer || (int)in_chunk.size() == max_runs) close_chunk();
+        used_bytes += bytes;
+        in_chunk.push_back(r);
+        c += r.n;
     }
+    close_chunk();
+    // the 16-bit fields hold a low byte and 256 channels of 255: the high bytes move on
+    // before the chunk that would exceed that
+    const int nchunks = (int)o->channels.size();
+    for (int j = 0, pending = 0; j < nchunks; ++j) {
+        pending += o->channels[j];
+        if (j + 1 < nchunks && pending + o->channels[j + 1] <= 256) continue;
+        for (int w = 0; w < kSumming; ++w) o->blocks[((size_t)j * kSumming + w) * kSharedBlock] |= pending << 8;
+        pending = 0;
+    }
+    o->ok = true;
+}
+
+}  // namespace
+
+bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, double max_clocks,
+                  SharedTables *out) {
+    const int td = sh.td(), ntiles = (ndm + td - 1) / td;
+    if (td < 1 || td > kMaxTrials || nch < kSharedChans || nch > 65536 || ndm < 1) return false;
+    std::vector<Tile> tiles(ntiles);
+    // 128 channels in the middle speak for the others: a plan far from worth it is not built
+    const int some = std::min(nch, 128);
+    Tile probe;
+    build_tile(delays + (nch - some) / 2, nch, ndm, some, sh, ntiles / 2, &probe);
+    if (!probe.ok || probe.clocks * nch / some * ntiles > 1.5 * max_clocks) return false;
+    std::atomic<int> next{0};
+    auto work = [&]() {
+        for (int k; (k = next.fetch_add(1)) < ntiles;) {
+            try {
+                build_tile(delays, nch, ndm, nch, sh, k, &tiles[k]);
+            } catch (const std::bad_alloc &) {   // not ok: no tables
+            }
+        }
+    };
+    // a tile of the 4096-channel band takes 2.5 ms: helpers from a few tiles of such size on
+    std::vector<std::thread> helpers;
+    const int64_t size = (int64_t)ntiles * td * nch;
+    const int n_help = size < (1 << 18) ? 0 : std::min({7, ntiles - 1, (int)std::thread::hardware_concurrency() - 1});
+    try {
+        for (int i = 0; i < n_help; ++i) helpers.emplace_back(work);
+    } catch (const std::system_error &) {   // fewer helpers
+    }
+    work();
+    for (std::thread &t : helpers) t.join();
+
+    size_t n_items = 0, n_blocks = 0, n_taps = 0, n_starts = 0;
     SharedTables &t = *out;
+    t.buffer = 0;
+    t.clocks = 0;
+    for (const Tile &o : tiles) {
+        if (!o.ok) return false;
+        n_items += o.items.size();
+        n_blocks += o.blocks.size();
+        n_taps += o.taps.size();
+        n_starts += o.starts.size();
+        t.buffer = std::max(t.buffer, o.buffer);
+        t.clocks += o.clocks;
+    }
     t.shape = sh;
     t.ntiles = ntiles;
-    t.nsubs = (int)(taps.size() / kTaps);
-    t.nrounds = (int)(items.size() / sh.np);
-    t.nchunks = (int)channels.size();
-    t.buffer = buffer;
-    t.clocks = clocks;
+    t.nsubs = (int)(n_taps / kTaps);
+    t.nrounds = (int)(n_items / sh.np);
+    t.nchunks = (int)(n_blocks / ((size_t)kSumming * kSharedBlock));
     auto up = [](size_t v) { return (v + 127) & ~(size_t)127; };
-    t.off_items = up(tiles.size() * sizeof(SharedTile));
-    t.off_blocks = up(t.off_items + items.size() * sizeof(SharedItem));
-    t.off_taps = up(t.off_blocks + blocks.size() * sizeof(int32_t));
-    t.off_starts = up(t.off_taps + taps.size() * sizeof(uint32_t));
-    const size_t bytes = up(t.off_starts + starts.size() * sizeof(int32_t));
+    t.off_items = up(ntiles * sizeof(SharedTile));
+    t.off_blocks = up(t.off_items + n_items * sizeof(SharedItem));
+    t.off_taps = up(t.off_blocks + n_blocks * sizeof(int32_t));
+    t.off_starts = up(t.off_taps + n_taps * sizeof(uint32_t));
+    const size_t bytes = up(t.off_starts + n_starts * sizeof(int32_t));
     if (bytes > max_bytes || bytes > INT32_MAX) return false;
     t.blob.assign(bytes, 0);
-    std::memcpy(t.blob.data(), tiles.data(), tiles.size() * sizeof(SharedTile));
-    std::memcpy(t.blob.data() + t.off_items, items.data(), items.size() * sizeof(SharedItem));
-    std::memcpy(t.blob.data() + t.off_blocks, blocks.data(), blocks.size() * sizeof(int32_t));
-    std::memcpy(t.blob.data() + t.off_taps, taps.data(), taps.size() * sizeof(uint32_t));
-    std::memcpy(t.blob.data() + t.off_starts, starts.data(), starts.size() * sizeof(int32_t));
+    SharedTile *tile = (SharedTile *)t.blob.data();
+    SharedItem *items = (SharedItem *)(t.blob.data() + t.off_items);
+    int32_t *blocks = (int32_t *)(t.blob.data() + t.off_blocks);
+    uint32_t *taps = (uint32_t *)(t.blob.data() + t.off_taps);
+    int32_t *starts = (int32_t *)(t.blob.data() + t.off_starts);
+    int round = 0, chunk = 0, sub = 0;
+    for (const Tile &o : tiles) {
+        tile->round = round;
+        tile->nrounds = (int32_t)(o.items.size() / sh.np);
+        tile->chunk = chunk;
+        tile->nchunks = (int32_t)o.channels.size();
+        round += tile->nrounds;
+        chunk += tile->nchunks;
+        ++tile;
+        for (SharedItem it : o.items) {
+            it.sub += sub;
+            *items++ = it;
+        }
+        sub += (int)(o.taps.size() / kTaps);
+        blocks = std::copy(o.blocks.begin(), o.blocks.end(), blocks);
+        taps = std::copy(o.taps.begin(), o.taps.end(), taps);
+        starts = std::copy(o.starts.begin(), o.starts.end(), starts);
+    }
     return true;
 }
 

@@ -74,9 +74,10 @@ struct SharedTables {
 };
 
 // Builds the tables for delays [ndm][nch] (rows past ndm repeat the last trial).  False
-// when nch is not in [16, 65536], a run of one channel does not fit the shape, or the tables exceed
-// max_bytes.
-bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape shape, size_t max_bytes, SharedTables *out);
+// when nch is not in [16, 65536], a run of one channel does not fit the shape, the tables exceed
+// max_bytes, or their clocks are seen to exceed max_clocks by far.
+bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape shape, size_t max_bytes, double max_clocks,
+                  SharedTables *out);
 
 // Delays [ntiles * td][nch] that the tables encode (for checking them on the host).
 void decode_shared(const SharedTables &t, int nch, std::vector<int32_t> *out);

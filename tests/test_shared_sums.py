@@ -85,6 +85,28 @@ def test_no_row_starts_before_the_block():
     assert got is not None and np.array_equal(got, d)
 
 
+@pytest.mark.parametrize("nch,f_lo,f_hi,ndm,step", [
+    (2048, 300.0, 500.0, 900, 0.5),      # rows of 1-2 KB for the 64-trial tiles
+    (4096, 300.0, 500.0, 640, 0.25),
+    (1024, 550.0, 750.0, 600, 2.0),
+    (777, 300.0, 500.0, 333, 0.3)])
+def test_default_tiles_take_every_plan(nch, f_lo, f_hi, ndm, step):
+    """Whatever the rule for default tiles picks, the batch is made."""
+    for n_out in (3000, 8192):
+        plan = band(nch, f_lo, f_hi, ndm, step, n_out=n_out)
+        b = spl.Batch([plan], hit_capacity=1 << 16)
+        got = b.shared_delays()
+        assert got is None or np.array_equal(got, plan.delays())
+
+
+def test_default_tiles_of_an_uneven_table():
+    """Delays shared by every channel but one, whose spread only row tiles of fewer trials take."""
+    d = np.repeat(np.arange(640, dtype=np.int32)[:, None] // 8, 1000, axis=1)
+    d[:, 501] = np.arange(640) * 14
+    plan = spl.Plan(1000, 750.0, -0.2, 1e-3, 9000, widths=(1,), delays=d)
+    spl.Batch([plan], hit_capacity=1 << 16)
+
+
 def test_plans_without_shared_patterns_stage_single_channels():
     plan = spl.Plan.from_dict(W.plan_c1())   # 88 samples from trial to trial at the lowest channel
     b = spl.Batch([plan], hit_capacity=1 << 16)
