@@ -545,8 +545,10 @@ static spl_status build_layout(spl_batch *B) {
     for (auto &L : B->layouts) {
         spl_status st = layout_plan(L);
         if (st != SPL_OK) return st;
-        // 4- and 8-wavefront workgroups share a CU (64 KiB each); a 16-wavefront one holds it
-        choose_chunk(L, L.tiles.nw >= 16 ? 160 * 1024 - 256 : 64 * 1024);
+        // workgroups share a CU as their registers allow, 16 wavefronts on it: a 16-wavefront one
+        // holds its LDS, two of 8 wavefronts have 80 KiB each (the 2048-channel 300-500 MHz band
+        // fits 8 channels in a chunk, 7.1 ms for two beams; with 64 KiB 4 channels and 7.7 ms)
+        choose_chunk(L, L.tiles.nw >= 16 ? 160 * 1024 - 256 : L.tiles.nw >= 8 ? 80 * 1024 - 256 : 64 * 1024);
     }
     const int nb = B->nb;
     B->row_base.assign(nb + 1, 0);

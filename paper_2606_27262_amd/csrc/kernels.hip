@@ -58,9 +58,16 @@ __global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
 // per (channel, trial) in the plan table; the chunk's slice of the table is staged in
 // LDS with the samples.  Per (trial, channel) a lane does one address add, per 256
 // samples one dword read (lanes read consecutive dwords: conflict-free, paired into
-// ds_read2st64_b32), and two v_perm that spread bytes (t, t+2) and (t+1, t+3) into
-// 16-bit fields, summed for two channels at a time with v_add3_u32 (exact for up to
-// 256 channels, then widened into int32 accumulators).  The LDS loads of the next
+// ds_read2st64_b32), and a v_perm that spreads bytes (t+1, t+3) into 16-bit fields; these
+// and the dwords as they are (carries between the bytes included) are summed for two
+// channels at a time with v_add3_u32.  Bytes (t, t+2) are what is left of the sum of the
+// dwords less 256 times the fields, exact for up to 256 channels; then both are widened
+// into int32 accumulators.  That is 4 instructions for 8 sums; spreading both pairs of
+// bytes took 6.  Registers are held to 128, so that a CU has 16 wavefronts of 4 SIMDs: the
+// 8-wavefront tiles of 256 x 2 samples took 131 and 145, and one workgroup a CU then
+// neither staged nor summed while it waited at its barriers (two beams of the 2048-channel
+// 300-500 MHz band: 12.1 ms in this kernel, 11.4 with fewer sums' instructions, 7.2 with
+// two workgroups a CU).  The LDS loads of the next
 // channel are in flight while the current one is summed, and the global loads of the
 // next chunk while the current chunk is summed.
 // SV: 16-byte input vectors staged per lane and row (rows of up to 1024*SV bytes).
@@ -73,7 +80,7 @@ __global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
 // SIMDs in turn, each SIMD holds two of each kind).
 // Each wavefront stages up to dedisp_stage_rows(NBUF) rows per chunk.
 template <int DW, int J, int NW, int SV, int NBUF>
-__global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ beams,
+__global__ __launch_bounds__(64 * NW, 4) void k_dedisp(const DevBeam *__restrict__ beams,
                                                     const DedispItem *__restrict__ items,
                                                     int item_lo, int item_hi, int *queue) {
     extern __shared__ __align__(16) uint8_t lds[];
@@ -85,7 +92,6 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
     constexpr int kStageVecs = SV;
     constexpr int kTabRows = kStageRows * NW + 4;   // chan_chunk rows + 4 rows of prefetch padding
     constexpr int kTabRegs = (kTabRows * TD + 64 * NW - 1) / (64 * NW);
-    constexpr uint32_t kSelEven = 0x0C020C00u;   // bytes 0, 2 -> 16-bit fields
     constexpr uint32_t kSelOdd = 0x0C030C01u;    // bytes 1, 3 -> 16-bit fields
 
     int it = item_lo + blockIdx.x;
@@ -112,13 +118,13 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
         const int buf_bytes = 4 * quarter + kTabRows * TD * 4;
 
         int32_t acc[DW][4 * J];
-        uint32_t ae[DW][J], ao[DW][J];
+        uint32_t aw[DW][J], ao[DW][J];   // sums of the dwords, of their bytes 1 and 3
 #pragma unroll
         for (int i = 0; i < DW; ++i) {
 #pragma unroll
             for (int k = 0; k < 4 * J; ++k) acc[i][k] = 0;
 #pragma unroll
-            for (int j = 0; j < J; ++j) ae[i][j] = ao[i][j] = 0u;
+            for (int j = 0; j < J; ++j) aw[i][j] = ao[i][j] = 0u;
         }
 
         // staging registers: rows wave + NW*m, vectors lane + 64*q, and the chunk's slice
@@ -236,8 +242,7 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
             for (int i = 0; i < DW; ++i)
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
-                    ae[i][j] += __builtin_amdgcn_perm(u[i][j], u[i][j], kSelEven) +
-                                __builtin_amdgcn_perm(v[i][j], v[i][j], kSelEven);
+                    aw[i][j] += u[i][j] + v[i][j];
                     ao[i][j] += __builtin_amdgcn_perm(u[i][j], u[i][j], kSelOdd) +
                                 __builtin_amdgcn_perm(v[i][j], v[i][j], kSelOdd);
                 }
@@ -280,11 +285,19 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
                 load_row(ta, na);
                 load_row(tb, nb);
                 add_rows(la, lb);
+                if constexpr (NBUF == 1) {
+                    add_rows(na, nb);
+                    return;
+                }
 #pragma unroll
                 for (int i = 0; i < DW; ++i)
 #pragma unroll
                     for (int j = 0; j < J; ++j) { da[i][j] = na[i][j]; db[i][j] = nb[i][j]; }
             } else {
+                if constexpr (NBUF == 1) {
+                    add_rows(la, lb);
+                    return;
+                }
 #pragma unroll
                 for (int i = 0; i < DW; ++i)
 #pragma unroll
@@ -298,11 +311,12 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
                 for (int i = 0; i < DW; ++i)
 #pragma unroll
                     for (int j = 0; j < J; ++j) {
-                        acc[i][4 * j + 0] += (int32_t)(ae[i][j] & 0xFFFFu);
-                        acc[i][4 * j + 2] += (int32_t)(ae[i][j] >> 16);
+                        const uint32_t even = aw[i][j] - (ao[i][j] << 8);
+                        acc[i][4 * j + 0] += (int32_t)(even & 0xFFFFu);
+                        acc[i][4 * j + 2] += (int32_t)(even >> 16);
                         acc[i][4 * j + 1] += (int32_t)(ao[i][j] & 0xFFFFu);
                         acc[i][4 * j + 3] += (int32_t)(ao[i][j] >> 16);
-                        ae[i][j] = ao[i][j] = 0u;
+                        aw[i][j] = ao[i][j] = 0u;
                     }
             }
         };
@@ -315,8 +329,7 @@ __global__ __launch_bounds__(64 * NW) void k_dedisp(const DevBeam *__restrict__ 
                 store_chunk(c0, 0);
                 if (c0 + cchunk < nch) load_chunk(c0 + cchunk);
                 __syncthreads();          // the chunk is staged
-                sum_chunk(cc, false);
-                add_rows(da, db);          // one buffer: no deferral (no VGPRs to spare)
+                sum_chunk(cc, false);      // (one buffer: no deferral, no VGPRs to spare)
                 widen(c0 + cc);
             }
         } else {
