@@ -14,15 +14,17 @@ hipError_t launch_snippets(const DevBeam *beams, int nbeams, const spl_candidate
                            hipStream_t s);
 hipError_t launch_gemm(const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float *C, int64_t ldc, int M,
                        int N, int K, int splits, bool accumulate, hipStream_t s);
-// Forward convolution (mode 0: first layer, NCHW 2 channels; 1: NHWC 32 channels) with
-// bias, ReLU and 2x2 max pool fused: pooled BF16 NHWC [N][H/2][W/2][32] and the pool
-// decisions; H even, W a multiple of 8, N*H*W a multiple of 64.
-hipError_t launch_conv_pool(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, int ldw,
-                            const float *bias, uint16_t *pooled, uint8_t *arg, hipStream_t s);
-// Implicit-GEMM convolution (mode 0: first layer, NCHW 2 channels; 1: forward, NHWC 32
-// channels; 2: input gradient, NHWC 32 channels, flipped taps) into C [N*H*W][32] FP32.
-hipError_t launch_conv(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, int ldw,
-                       float *C, hipStream_t s);
+// Forward convolutions with bias, ReLU and 2x2 max pool fused: pooled BF16 NHWC
+// [N][H/2][W/2][32] and the pool decisions.  First layer: NCHW, 2
+// channels (4-byte loads where X allows them), images n >= nvalid zero, H even, W a multiple of
+// 128, Wt [32][(ky*3 + kx)*2 + ci], 32 of them; the others: NHWC, 32 channels, W = 32, 64 or 128, H a
+// multiple of 256/W, Wt [32][(ky*3 + kx)*32 + ci].
+hipError_t launch_conv_first(const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, const float *bias,
+                             uint16_t *pooled, uint8_t *arg, hipStream_t s);
+hipError_t launch_conv_pool(const uint16_t *X, int N, int H, int W, const uint16_t *Wt, const float *bias,
+                            uint16_t *pooled, uint8_t *arg, hipStream_t s);
+// Input gradient of such a layer into dX [N*H*W][32] FP32 (Wt [ci][(ky*3 + kx)*32 + co]).
+hipError_t launch_conv_back(const uint16_t *dZ, int N, int H, int W, const uint16_t *Wt, float *dX, hipStream_t s);
 // Weight gradient partials part[nparts][K][32] (mode 0: K = 32, first layer; 1: K = 288).
 hipError_t launch_wgrad(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *dZ, float *part,
                         int nparts, hipStream_t s);

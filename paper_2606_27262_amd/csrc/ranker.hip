@@ -510,189 +510,203 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, in
 }
 
 // ------------------------------------------------------- implicit-GEMM convolution
-// Z[p][co] (FP32 [P][32]) = sum over taps t = ky*3 + kx and input channels ci of
-// X[src(p, t)][ci] * Wt[co][t*32 + ci], without an im2col buffer: with 32 input channels
-// each K-step of 32 is one tap, so the MFMA A operand of lane l is the 16 bytes of
-// channels 8(l/16) .. +7 of one source pixel, read straight from the NHWC activation.
-// MODE 0: the first layer: input NCHW with 2 channels (the snippet planes), K = 18 padded
-//         to one K-step of 32 (k = t*2 + ci), images n >= nvalid read as zero.
-// MODE 1: 32 input channels, NHWC, src = (h + ky - 1, w + kx - 1)   (forward).
-// MODE 2: 32 input channels, NHWC, src = (h - ky + 1, w - kx + 1)   (input gradient: the
-//         input is dZ and Wt the weights repacked as [ci][t*32 + co]).
-// Workgroup = 4 wavefronts; each wavefront computes kConvTiles tiles of 16 pixels x all 32
-// columns, so a tap's weight operands are loaded once for 64 pixels.  Tile T (of the
-// wavefront's T0 .. T0+3) is pixels 16T .. 16T+15, or with POOL (forward only) a 2 x 8
-// pixel patch (rows 2ph, 2ph+1, columns 8c .. 8c+7; patches row-major per image), so the
-// result holds four whole 2 x 2 windows: lane l keeps rows 4(l/16) .. +3, i.e. two
-// horizontal pairs of one image row, and lane l ^ 32 the pairs below them.  Bias, ReLU
-// and the max pool (with the window position of the first maximum, 255 when no element
-// is positive) then run in registers and only the pooled BF16 activation and the decision
-// bytes are written.
-constexpr int kConvTiles = 4;
-template <int MODE, bool POOL>
-__global__ __launch_bounds__(256) void k_conv(const uint16_t *__restrict__ X, int N, int nvalid, int H, int W,
-                                              const uint16_t *__restrict__ Wt, int ldw, float *__restrict__ C,
-                                              const float *__restrict__ bias, uint16_t *__restrict__ pooled,
-                                              uint8_t *__restrict__ arg) {
-    constexpr int MT = kConvTiles;
-    const int lane = lane_id(), wave = wave_id();
-    const int64_t P = (int64_t)N * H * W;
-    const int64_t t0 = ((int64_t)blockIdx.x * 4 + wave) * MT;
-    const int kq = 8 * (lane >> 4);
-    const int per_row = W >> 3, per_img = (H >> 1) * per_row;
-    int n[MT], h[MT], w[MT];
-    bool row_ok[MT];
+// Z[p][co] = sum over taps t = ky*3 + kx and input channels ci of X[src(p, t)][ci] *
+// Wt[co][t*32 + ci], without an im2col buffer: with 32 input channels each K-step of 32 is
+// one tap, and the MFMA A operand of lane l is the 16 bytes of channels 8(l/16) .. +7 of
+// one source pixel.
+//
+// A wavefront computes 4 tiles of 16 pixels x all 32 columns.  In the forward layers a tile is
+// a 2 x 8 pixel patch, so the result holds four whole 2 x 2 windows: lane l keeps rows
+// 4(l/16) .. +3, i.e. two horizontal pairs of one image row, and lane l ^ 32 the pairs below
+// them.  One exchange of half a wavefront gives lanes 0-31 both rows of columns 0-15 and
+// lanes 32-63 both rows of columns 16-31; bias, ReLU and the max pool (with the window
+// position of the first maximum, 255 when no element is positive) then run in registers,
+// and only the pooled BF16 activation and the decision bytes are written, 64 bytes a pixel.
+__device__ __forceinline__ void pool_tile(const f32x4 acc0, const f32x4 acc1, float bias,
+                                          uint16_t *__restrict__ pooled, uint8_t *__restrict__ arg, size_t o) {
+    float above[4], below[4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int64_t tile = t0 + mt;
-        int64_t p;
-        if constexpr (POOL) {
-            n[mt] = (int)(tile / per_img);
-            const int rem = (int)(tile - (int64_t)n[mt] * per_img);
-            const int r = lane & 15;
-            h[mt] = 2 * (rem / per_row) + (r >> 3);
-            w[mt] = 8 * (rem % per_row) + (r & 7);
-            p = ((int64_t)n[mt] * H + h[mt]) * W + w[mt];
-        } else {
-            p = tile * 16 + (lane & 15);
-            n[mt] = (int)(p / ((int64_t)H * W));
-            const int hw = (int)(p - (int64_t)n[mt] * H * W);
-            h[mt] = hw / W;
-            w[mt] = hw - h[mt] * W;
-        }
-        row_ok[mt] = p < P && n[mt] < nvalid;
+    for (int i = 0; i < 4; ++i) {
+        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc0[i]), __float_as_uint(acc1[i]), false, false);
+        above[i] = __uint_as_float(halves[0]);
+        below[i] = __uint_as_float(halves[1]);
     }
-    f32x4 acc0[MT], acc1[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc0[mt] = acc1[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    const uint16_t *b0p = Wt + (size_t)(lane & 15) * ldw + kq;
-    const uint16_t *b1p = b0p + (size_t)16 * ldw;
-    if constexpr (MODE == 0) {
-        u16x8 a[MT];
+    for (int k = 0; k < 2; ++k) {
+        const float z[4] = {above[2 * k] + bias, above[2 * k + 1] + bias, below[2 * k] + bias, below[2 * k + 1] + bias};
+        float best = 0.f;
+        int ba = 255;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) a[mt] = zero;
-        if constexpr (POOL) {
-            // the workgroup's 16 patches form one 2 x 128 strip of an image (W a multiple of
-            // 128): its input window, 2 channels x 4 rows x 130 columns with the zero
-            // padding, is staged in LDS once and every tap is read from there
-            constexpr int kWc = 8 * 4 * MT + 2;
-            __shared__ uint16_t win[2 * 4 * kWc];
-            const int64_t tw = (int64_t)blockIdx.x * 4 * MT;
-            const int n0 = (int)(tw / per_img);
-            const int rem0 = (int)(tw - (int64_t)n0 * per_img);
-            const int hb = 2 * (rem0 / per_row) - 1, wb = 8 * (rem0 % per_row) - 1;
-            for (int i = threadIdx.x; i < 2 * 4 * kWc; i += 256) {
-                const int ci = i / (4 * kWc), r = (i / kWc) & 3, c = i % kWc;
-                const int hs = hb + r, ws = wb + c;
-                uint16_t v = 0;
-                if (n0 < nvalid && hs >= 0 && hs < H && ws >= 0 && ws < W)
-                    v = X[(((size_t)n0 * 2 + ci) * H + hs) * W + ws];
-                win[i] = v;
+        for (int j = 0; j < 4; ++j) {
+            if (z[j] > best) {
+                best = z[j];
+                ba = j;
             }
-            __syncthreads();
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int base = (h[mt] - hb) * kWc + (w[mt] - wb);   // the pixel's place in the window
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = kq + j;
-                    if (k < 18) {
-                        const int t = k >> 1, ci = k & 1;
-                        const int ty = (t * 11) >> 5;        // t / 3 for t < 9
-                        a[mt][j] = win[ci * 4 * kWc + base + (ty - 1) * kWc + (t - 3 * ty - 1)];
-                    }
-                }
+        }
+        arg[o + 32 * k] = (uint8_t)ba;
+        pooled[o + 32 * k] = f2bf(best);
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma_bf16(u16x8 a, u16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The first layer: input NCHW with 2 channels (the snippet planes), images n >= nvalid read
+// as zero.  Workgroup = 4 wavefronts = a strip of 2 rows x 128 columns; its input window, 4
+// rows x 130 columns with the zero padding, is staged in the LDS with both channels of a
+// sample in one dword.  K = 32: k = 2 t + ci, so a lane's 8 values are the dwords of four
+// taps, read with no unpacking; taps past the ninth read zeros.  256 snippets:
+// 42 us, of which the activations and decisions written take 17; 92 with 8 two-byte LDS reads
+// a lane and tile and half of the lanes pooling.
+__global__ __launch_bounds__(256) void k_conv_first(const uint16_t *__restrict__ X, int nvalid, int H, int W,
+                                                    const uint16_t *__restrict__ Wt, const float *__restrict__ bias,
+                                                    uint16_t *__restrict__ pooled, uint8_t *__restrict__ arg) {
+    constexpr int kWc = 130, kZeros = 4 * kWc;   // columns of a staged row; then 32 zeros
+    __shared__ uint32_t win[kZeros + 32];
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int strips = W / 128;
+    const int64_t strip = blockIdx.x;
+    const int sc = (int)(strip % strips), ph = (int)(strip / strips % (H / 2));
+    const int64_t n = strip / strips / (H / 2);
+    {
+        const int row = tid >> 6, d = tid & 63, hs = 2 * ph - 1 + row;
+        const bool in = n < nvalid && hs >= 0 && hs < H;
+        const bool aligned = ((uintptr_t)X & 3) == 0;
+        const uint16_t *src = X + ((size_t)(in ? n : 0) * 2 * H + (in ? hs : 0)) * W + 128 * sc + 2 * d;
+        const size_t plane = (size_t)H * W;   // even
+        uint32_t v0 = 0u, v1 = 0u;
+        if (in) {
+            v0 = aligned ? *(const uint32_t *)src : (uint32_t)src[0] | (uint32_t)src[1] << 16;
+            v1 = aligned ? *(const uint32_t *)(src + plane) : (uint32_t)src[plane] | (uint32_t)src[plane + 1] << 16;
+        }
+        if (tid < 8) {   // the columns left and right of the strip
+            const int e_row = tid >> 1, e_ws = 128 * sc - 1 + 129 * (tid & 1), e_hs = 2 * ph - 1 + e_row;
+            uint32_t e = 0u;
+            if (n < nvalid && e_hs >= 0 && e_hs < H && e_ws >= 0 && e_ws < W) {
+                const uint16_t *p = X + ((size_t)n * 2 * H + e_hs) * W + e_ws;
+                e = (uint32_t)p[0] | (uint32_t)p[plane] << 16;
             }
-        } else {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = kq + j;
-                    if (k < 18 && row_ok[mt]) {
-                        const int t = k >> 1, ci = k & 1;
-                        const int hs = h[mt] + t / 3 - 1, ws = w[mt] + t % 3 - 1;
-                        if (hs >= 0 && hs < H && ws >= 0 && ws < W)
-                            a[mt][j] = X[(((size_t)n[mt] * 2 + ci) * H + hs) * W + ws];
-                    }
-                }
+            win[e_row * kWc + 129 * (tid & 1)] = e;
+        } else if (tid < 40) {
+            win[kZeros + tid - 8] = 0u;
         }
-        const u16x8 x0 = *(const u16x8 *)b0p, x1 = *(const u16x8 *)b1p;
+        win[row * kWc + 2 * d + 1] = (v0 & 0xFFFFu) | v1 << 16;
+        win[row * kWc + 2 * d + 2] = v0 >> 16 | (v1 & 0xFFFF0000u);
+    }
+    __syncthreads();
+    const int r = lane & 15, q = lane >> 4, co = r + 16 * (lane >> 5);
+    const u16x8 b0 = *(const u16x8 *)(Wt + (size_t)r * 32 + 8 * q), b1 = *(const u16x8 *)(Wt + (size_t)(r + 16) * 32 + 8 * q);
+    int at[4];   // of taps 4 q .. 4 q + 3, tile 0
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            acc0[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[mt]),
-                                                               __builtin_bit_cast(bf16x8, x0), acc0[mt], 0, 0, 0);
-            acc1[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[mt]),
-                                                               __builtin_bit_cast(bf16x8, x1), acc1[mt], 0, 0, 0);
+    for (int j = 0; j < 4; ++j) {
+        const int t = 4 * q + j, ky = (t * 11) >> 5;   // t / 3
+        at[j] = t < 9 ? ((r >> 3) + ky) * kWc + 32 * wave + (r & 7) + t - 3 * ky : kZeros;
+    }
+    const float b = bias[co];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+        typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+        const u32x4v a = {win[at[0] + 8 * mt], win[at[1] + 8 * mt], win[at[2] + 8 * mt], win[at[3] + 8 * mt]};
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        const f32x4 acc0 = mfma_bf16(__builtin_bit_cast(u16x8, a), b0, zero);
+        const f32x4 acc1 = mfma_bf16(__builtin_bit_cast(u16x8, a), b1, zero);
+        const size_t pw = 64 * sc + 16 * wave + 4 * mt + 2 * (q & 1);
+        pool_tile(acc0, acc1, b, pooled, arg, (((size_t)n * (H / 2) + ph) * (W / 2) + pw) * 32 + co);
+    }
+}
+
+// The layers of 32 input channels, NHWC.  Forward (pooled): src = (h + ky - 1, w + kx - 1).
+// BACK: input gradient, src = (h - ky + 1, w - kx + 1): the input is dZ, Wt the weights repacked as [ci][t*32 + co], the result FP32 [P][32].
+//
+// Workgroup = 4 wavefronts = 256 pixels, 256/W whole rows (W = 32, 64 or 128).  Read straight
+// from memory, a tile's nine taps and their weights took 54 KB of 16-byte loads per 64
+// pixels, 860 clocks of a CU (the products take 290); now the rows and the two around them are staged in
+// the LDS and the weights stay in registers (72) over the tiles of a workgroup.  A pixel's four
+// 16-byte pieces lie at places (piece ^ pixel / 4 mod 4), and rows W + 8 pixels apart, so the
+// 16 pixels of a tile meet no bank twice; a step of one row or 8 columns then changes an
+// address by a constant and bit 5.  256 snippets, the three
+// layers forward: 45 us, 108 before; back: 61, 100 before.
+template <bool BACK, int W>
+__global__ __launch_bounds__(256, 3) void k_conv32(const uint16_t *__restrict__ X, int64_t ntiles, int H,
+                                                   const uint16_t *__restrict__ Wt, float *__restrict__ C,
+                                                   const float *__restrict__ bias, uint16_t *__restrict__ pooled,
+                                                   uint8_t *__restrict__ arg) {
+    constexpr int R = 256 / W, LD = W + 8;         // rows of a tile; pixels of a staged row
+    constexpr int V = (R + 2) * W * 4 / 256;       // 16-byte pieces a thread stages
+    __shared__ __align__(16) uint8_t win[(R + 2) * LD * 64];
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int r = lane & 15, q = lane >> 4;
+    const u16x8 none = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int i = tid; i < (R + 2) * 8; i += 256) {   // the columns left and right of the image
+        const int row = i >> 3, side = (i >> 2) & 1;
+        *(u16x8 *)(win + (row * LD + side * (W + 1)) * 64 + (i & 3) * 16) = none;
+    }
+    u16x8 b0[9], b1[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        b0[t] = *(const u16x8 *)(Wt + (size_t)r * 288 + 32 * t + 8 * q);
+        b1[t] = *(const u16x8 *)(Wt + (size_t)(r + 16) * 288 + 32 * t + 8 * q);
+    }
+    const int rp = wave / (W / 32), cb = wave % (W / 32);   // the wavefront's two rows and 32 columns
+    // of kx: the pixel of tap (0, kx), tile 0
+    uint32_t at[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+        const int p = BACK ? 2 * rp * LD + 32 * cb + r + kx : (2 * rp + (r >> 3)) * LD + 32 * cb + (r & 7) + kx;
+        at[kx] = (uint32_t)(p * 64 + ((q ^ (p >> 2 & 3)) << 4));
+    }
+    const int co = r + 16 * (lane >> 5);
+    const float b = BACK ? 0.f : bias[co];
+    const int per_img = H / R;
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int64_t n = tile / per_img;
+        const int hb = (int)(tile - n * per_img) * R;
+        u16x8 v[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int i = tid + 256 * j, row = i / (W * 4), hs = hb + row - 1;
+            v[j] = none;
+            if (hs >= 0 && hs < H) v[j] = *(const u16x8 *)(X + ((size_t)n * H + hs) * (W * 32) + 8 * (i % (W * 4)));
         }
-    } else {
+        __syncthreads();   // the tile before is no longer read
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const int i = tid + 256 * j, p = i / (W * 4) * LD + (i / 4) % W + 1;
+            *(u16x8 *)(win + p * 64 + (((i & 3) ^ (p >> 2 & 3)) << 4)) = v[j];
+        }
+        __syncthreads();
+        f32x4 acc0[4], acc1[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc0[mt] = acc1[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
-            const int ky = t / 3, kx = t % 3;
-            const u16x8 x0 = *(const u16x8 *)(b0p + 32 * t), x1 = *(const u16x8 *)(b1p + 32 * t);
-            u16x8 a[MT];
+            const int ky = BACK ? 2 - t / 3 : t / 3, kx = BACK ? 2 - t % 3 : t % 3;   // place in the window
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int hs = MODE == 1 ? h[mt] + ky - 1 : h[mt] - ky + 1;
-                const int ws = MODE == 1 ? w[mt] + kx - 1 : w[mt] - kx + 1;
-                a[mt] = zero;
-                if (row_ok[mt] && hs >= 0 && hs < H && ws >= 0 && ws < W)
-                    a[mt] = *(const u16x8 *)(X + (((size_t)n[mt] * H + hs) * W + ws) * 32 + kq);
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc0[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[mt]),
-                                                                   __builtin_bit_cast(bf16x8, x0), acc0[mt], 0, 0, 0);
-                acc1[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[mt]),
-                                                                   __builtin_bit_cast(bf16x8, x1), acc1[mt], 0, 0, 0);
+            for (int mt = 0; mt < 4; ++mt) {
+                const int down = BACK ? ky + (mt >> 1) : ky, flip = BACK ? down & 1 : (ky + mt) & 1;
+                const int step = down * LD * 64 + (BACK ? (mt & 1) * 1024 : mt * 512);
+                const u16x8 a = *(const u16x8 *)(win + (at[kx] ^ (flip ? 32u : 0u)) + step);
+                acc0[mt] = mfma_bf16(a, b0[t], acc0[mt]);
+                acc1[mt] = mfma_bf16(a, b1[t], acc1[mt]);
             }
         }
-    }
+        if constexpr (BACK) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int64_t tile = t0 + mt;
-        if constexpr (POOL) {
-            // window k (0, 1) of this lane: own pair i = 2k, 2k+1 (window positions 0, 1),
-            // the partner lane's pair below it (positions 2, 3); positions tried in order
-            const int g = lane >> 4, co = lane & 15;
-            const int nn = (int)(tile / per_img);
-            const int rem = (int)(tile - (int64_t)nn * per_img);
-            const int ph = rem / per_row, pw0 = 4 * (rem % per_row) + 2 * (g & 1);
-            const int H2 = H >> 1, W2 = W >> 1;
+            for (int mt = 0; mt < 4; ++mt) {
+                float *o = C + (((size_t)n * H + hb + 2 * rp + (mt >> 1)) * W + 32 * cb + 16 * (mt & 1) + 4 * q) * 32 + r;
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const f32x4 av = half ? acc1[mt] : acc0[mt];
-                const float b = bias[co + 16 * half];
-                float below[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) below[i] = __shfl_xor(av[i], 32);
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const float z[4] = {av[2 * k] + b, av[2 * k + 1] + b, below[2 * k] + b, below[2 * k + 1] + b};
-                    float best = 0.f;
-                    int ba = 255;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (z[j] > best) {
-                            best = z[j];
-                            ba = j;
-                        }
-                    }
-                    if (g < 2 && tile * 16 < P) {
-                        const size_t o = (((size_t)nn * H2 + ph) * W2 + pw0 + k) * 32 + co + 16 * half;
-                        pooled[o] = f2bf(best);
-                        arg[o] = (uint8_t)ba;
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    o[32 * i] = acc0[mt][i];
+                    o[32 * i + 16] = acc1[mt][i];
                 }
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t m = tile * 16 + 4 * (lane >> 4) + i;
-                if (m >= P) continue;
-                C[m * 32 + (lane & 15)] = acc0[mt][i];
-                C[m * 32 + 16 + (lane & 15)] = acc1[mt][i];
+            for (int mt = 0; mt < 4; ++mt) {
+                const size_t pw = 16 * cb + 4 * mt + 2 * (q & 1);
+                pool_tile(acc0[mt], acc1[mt], b, pooled, arg,
+                          (((size_t)n * (H / 2) + hb / 2 + rp) * (W / 2) + pw) * 32 + co);
             }
         }
     }
@@ -1180,39 +1194,36 @@ hipError_t launch_gemm(const uint16_t *A, int64_t lda, const uint16_t *B, int64_
     return hipSuccess;
 }
 
-hipError_t launch_conv(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, int ldw,
-                       float *C, hipStream_t s) {
-    const int64_t P = (int64_t)N * H * W;
-    if (P <= 0 || (ldw & 7)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((P + 64 * kConvTiles - 1) / (64 * kConvTiles)));
-    float *nb = nullptr;
-    uint16_t *np = nullptr;
-    uint8_t *na = nullptr;
-    if (mode == 0)
-        hipLaunchKernelGGL((k_conv<0, false>), grid, dim3(256), 0, s, X, N, nvalid, H, W, Wt, ldw, C, nb, np, na);
-    else if (mode == 1)
-        hipLaunchKernelGGL((k_conv<1, false>), grid, dim3(256), 0, s, X, N, nvalid, H, W, Wt, ldw, C, nb, np, na);
+template <bool BACK>
+static hipError_t launch_conv32(const uint16_t *X, int N, int H, int W, const uint16_t *Wt, float *C, const float *bias,
+                                uint16_t *pooled, uint8_t *arg, hipStream_t s) {
+    if (N < 1 || (W != 32 && W != 64 && W != 128) || H < 256 / W || H % (256 / W)) return hipErrorInvalidValue;
+    const int64_t ntiles = (int64_t)N * H * W / 256;
+    const dim3 grid((unsigned)std::min<int64_t>(ntiles, 3 * 256));   // 3 workgroups a CU
+    if (W == 128)
+        hipLaunchKernelGGL((k_conv32<BACK, 128>), grid, dim3(256), 0, s, X, ntiles, H, Wt, C, bias, pooled, arg);
+    else if (W == 64)
+        hipLaunchKernelGGL((k_conv32<BACK, 64>), grid, dim3(256), 0, s, X, ntiles, H, Wt, C, bias, pooled, arg);
     else
-        hipLaunchKernelGGL((k_conv<2, false>), grid, dim3(256), 0, s, X, N, nvalid, H, W, Wt, ldw, C, nb, np, na);
+        hipLaunchKernelGGL((k_conv32<BACK, 32>), grid, dim3(256), 0, s, X, ntiles, H, Wt, C, bias, pooled, arg);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_conv_pool(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, int ldw,
-                            const float *bias, uint16_t *pooled, uint8_t *arg, hipStream_t s) {
-    const int64_t P = (int64_t)N * H * W;
-    // whole 2 x 8 patches, 4 x kConvTiles per workgroup
-    if (P <= 0 || (ldw & 7) || (H & 1) || (W & 7) || (P % (64 * kConvTiles)) || (mode != 0 && mode != 1))
-        return hipErrorInvalidValue;
-    if (mode == 0 && (W % (32 * kConvTiles))) return hipErrorInvalidValue;   // a workgroup's strip stays in one row
-    const dim3 grid((unsigned)(P / (64 * kConvTiles)));
-    float *nc = nullptr;
-    if (mode == 0)
-        hipLaunchKernelGGL((k_conv<0, true>), grid, dim3(256), 0, s, X, N, nvalid, H, W, Wt, ldw, nc, bias, pooled,
-                           arg);
-    else
-        hipLaunchKernelGGL((k_conv<1, true>), grid, dim3(256), 0, s, X, N, nvalid, H, W, Wt, ldw, nc, bias, pooled,
-                           arg);
+hipError_t launch_conv_back(const uint16_t *dZ, int N, int H, int W, const uint16_t *Wt, float *dX, hipStream_t s) {
+    return launch_conv32<true>(dZ, N, H, W, Wt, dX, nullptr, nullptr, nullptr, s);
+}
+
+hipError_t launch_conv_pool(const uint16_t *X, int N, int H, int W, const uint16_t *Wt, const float *bias,
+                            uint16_t *pooled, uint8_t *arg, hipStream_t s) {
+    return launch_conv32<false>(X, N, H, W, Wt, nullptr, bias, pooled, arg, s);
+}
+
+hipError_t launch_conv_first(const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *Wt, const float *bias,
+                             uint16_t *pooled, uint8_t *arg, hipStream_t s) {
+    const int64_t strips = (int64_t)N * (H / 2) * (W / 128);
+    if (N < 1 || (H & 1) || (W % 128) || strips > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_conv_first, dim3((unsigned)strips), dim3(256), 0, s, X, nvalid, H, W, Wt, bias, pooled, arg);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }

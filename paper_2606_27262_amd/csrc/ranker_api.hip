@@ -57,10 +57,13 @@ constexpr int kW[kLayers] = {256, 128, 64, 32};
 constexpr int kCin[kLayers] = {2, 32, 32, 32};
 constexpr int kKp[kLayers] = {32, 288, 288, 288};
 constexpr int kFcIn = 2048, kFcHidden = 64;
-// workgroups (and partial sums) of a weight-gradient pass: 32-channel layers use up to
-// kWgradParts, the first layer (a 32 x 32 result) up to kWgradPartsFirst in the same buffer
+// workgroups (and partial sums) of a weight-gradient pass: the buffer holds
+// kWgradParts of a 32-channel layer, the first layer (a 32 x 32 result) up to kWgradPartsFirst in the same buffer
 constexpr int kWgradParts = 2048;
 constexpr int kWgradPartsFirst = kWgradParts * 9;
+// partial sums of a 32-channel layer, 36 KB each to write and to sum: two workgroups a CU
+// (training step of 256 snippets 599 us, with four 605, with eight 622)
+constexpr int kWgradGroups = 512;
 
 // Offsets of the parameters in their fixed order.
 struct ParamOffsets {
@@ -228,15 +231,16 @@ hipError_t gemm(const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, 
     return launch_gemm(A, lda, B, ldb, C, ldc, M, N, K, splits, false, s);
 }
 
-spl_status forward(spl_ranker *R, const uint16_t *snip, int n, hipStream_t s) {
-    const int nb = R->nb;
+// nb images of which n are given (the others zero).
+spl_status forward(spl_ranker *R, const uint16_t *snip, int n, int nb, hipStream_t s) {
     const uint16_t *packed = R->at<uint16_t>(R->off_packed);
     const float *master = R->at<float>(R->off_master);
-    for (int k = 0; k < kLayers; ++k) {
-        const uint16_t *in = k == 0 ? snip : R->at<uint16_t>(R->off_X[k - 1]);
-        RK_TRY(launch_conv_pool(k == 0 ? 0 : 1, in, nb, k == 0 ? n : nb, kH[k], kW[k], packed + R->pk_wp[k], kKp[k],
-                                master + R->po.cb[k], R->at<uint16_t>(R->off_X[k]), R->at<uint8_t>(R->off_arg[k]), s));
-    }
+    RK_TRY(launch_conv_first(snip, nb, n, kH[0], kW[0], packed + R->pk_wp[0], master + R->po.cb[0],
+                             R->at<uint16_t>(R->off_X[0]), R->at<uint8_t>(R->off_arg[0]), s));
+    for (int k = 1; k < kLayers; ++k)
+        RK_TRY(launch_conv_pool(R->at<uint16_t>(R->off_X[k - 1]), nb, kH[k], kW[k], packed + R->pk_wp[k],
+                                master + R->po.cb[k], R->at<uint16_t>(R->off_X[k]), R->at<uint8_t>(R->off_arg[k]),
+                                s));
     RK_TRY(gemm(R->at<uint16_t>(R->off_X[3]), kFcIn, packed + R->pk_f1, kFcIn, R->at<float>(R->off_Hm), kFcHidden, nb,
                 kFcHidden, kFcIn, s));
     return SPL_OK;
@@ -266,12 +270,12 @@ spl_status backward(spl_ranker *R, const uint16_t *snip, int n, const float *lab
         const uint16_t *in = k == 0 ? snip : R->at<uint16_t>(R->off_X[k - 1]);
         RK_TRY(launch_unpool(dX, R->at<uint8_t>(R->off_arg[k]), nb, kH[k], kW[k], dZ, G + po.cb[k], s));
         // first layer: about 16 slabs of 32 pixels per wavefront; the others: one
-        // workgroup per slab up to kWgradParts
+        // workgroup per slab up to kWgradGroups
         const int parts = (int)std::max<int64_t>(
-            1, std::min<int64_t>(k == 0 ? kWgradPartsFirst : kWgradParts, k == 0 ? P / 32 / 64 : P / 32));
+            1, std::min<int64_t>(k == 0 ? kWgradPartsFirst : kWgradGroups, k == 0 ? P / 32 / 64 : P / 32));
         RK_TRY(launch_wgrad(k == 0 ? 0 : 1, in, nb, k == 0 ? n : nb, kH[k], kW[k], dZ, part, parts, s));
         RK_TRY(launch_sum_parts(part, parts, (int64_t)kKp[k] * kCout, gc + R->gc_w[k], R->at<float>(R->off_part2), s));
-        if (k > 0) RK_TRY(launch_conv(2, dZ, nb, nb, kH[k], kW[k], packed + R->pk_wd[k], 288, dX, s));
+        if (k > 0) RK_TRY(launch_conv_back(dZ, nb, kH[k], kW[k], packed + R->pk_wd[k], dX, s));
     }
     RK_TRY(launch_scatter_idx(gc, R->at<int32_t>(R->off_gc_idx), R->n_gc, G, s));
     return SPL_OK;
@@ -361,11 +365,11 @@ extern "C" spl_status spl_ranker_score(spl_ranker *R, const uint16_t *d_snip, in
     if (n < 0 || (n > 0 && (!d_snip || !d_logits))) return failf(SPL_E_INVALID_ARG, "bad snippet or logit buffer");
     for (int64_t i0 = 0; i0 < n; i0 += R->nb) {
         const int m = (int)std::min<int64_t>(R->nb, n - i0);
-        st = forward(R, d_snip + i0 * SPL_SNIPPET_ELEMS, m, stream);
+        st = forward(R, d_snip + i0 * SPL_SNIPPET_ELEMS, m, m, stream);   // a ragged pass is not padded
         if (st != SPL_OK) return st;
         const ParamOffsets &po = R->po;
         const float *master = R->at<float>(R->off_master);
-        RK_TRY(launch_head(R->at<float>(R->off_Hm), master + po.f1b, master + po.f2w, master + po.f2b, m, R->nb,
+        RK_TRY(launch_head(R->at<float>(R->off_Hm), master + po.f1b, master + po.f2w, master + po.f2b, m, m,
                            d_logits + i0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, stream));
     }
     return SPL_OK;
@@ -377,7 +381,7 @@ extern "C" spl_status spl_ranker_backward(spl_ranker *R, const uint16_t *d_snip,
     if (st != SPL_OK) return st;
     if (n < 1 || n > R->o.max_batch) return failf(SPL_E_INVALID_ARG, "n must be in [1, max_batch]");
     if (!d_snip || !d_labels || !d_loss) return failf(SPL_E_INVALID_ARG, "NULL argument");
-    st = forward(R, d_snip, (int)n, stream);
+    st = forward(R, d_snip, (int)n, R->nb, stream);
     if (st != SPL_OK) return st;
     return backward(R, d_snip, (int)n, d_labels, d_loss, stream);
 }
