@@ -25,9 +25,13 @@ hipError_t launch_conv_pool(const uint16_t *X, int N, int H, int W, const uint16
                             uint16_t *pooled, uint8_t *arg, hipStream_t s);
 // Input gradient of such a layer into dX [N*H*W][32] FP32 (Wt [ci][(ky*3 + kx)*32 + co]).
 hipError_t launch_conv_back(const uint16_t *dZ, int N, int H, int W, const uint16_t *Wt, float *dX, hipStream_t s);
-// Weight gradient partials part[nparts][K][32] (mode 0: K = 32, first layer; 1: K = 288).
-hipError_t launch_wgrad(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *dZ, float *part,
-                        int nparts, hipStream_t s);
+// Weight gradient partials part[nparts][288][32] of a 32-channel layer.
+hipError_t launch_wgrad(const uint16_t *X, int N, int H, int W, const uint16_t *dZ, float *part, int nparts,
+                        hipStream_t s);
+// Of the first layer, part[nparts][32][32], from the gradient of the pooled activation and
+// the pool decisions; the bias gradient is added to dbias.  H even, W a multiple of 32.
+hipError_t launch_wgrad_first(const uint16_t *X, int N, int nvalid, int H, int W, const float *dOut, const uint8_t *arg,
+                              float *part, int nparts, float *dbias, hipStream_t s);
 // Deterministic sum of nparts partial arrays of n floats; above 256 parts in two passes
 // through tmp (room for kSumPartsMaxGroups * n floats).
 constexpr int kSumPartsMaxGroups = 160;

@@ -787,17 +787,22 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *__restrict__ X, i
 
 // Weight gradient of the first layer (2 input channels, K = 18 used of 32):
 // part[blockIdx.x][k][co] = sum over the pixels p of the workgroup's slabs of
-// A[p][k] * dZ[p][co], k = t*2 + ci.  Each wavefront works alone on slabs of 32
-// consecutive pixels of one image row (W a multiple of 32): the input is NCHW, so the 32
-// values of row k are 32 neighbouring samples of one plane (shifted by the tap), read
-// straight into the LDS row; dZ (NHWC) is transposed into its LDS rows.  No workgroup
-// barrier in the loop: a wavefront's LDS writes and reads execute in order.  The four
-// wavefronts' sums are added in a fixed order at the end.
+// A[p][k] * dZ[p][co], k = t*2 + ci, dZ[p][co] = BF16 of dOut[pooled][co] at the window's arg
+// position, 0 elsewhere; the bias gradient (the sum of dOut over windows with a chosen
+// element) is added to dbias.  dZ, four times the size of dOut, is made in the LDS only: no
+// other kernel needs it (written out and read back, as the other layers' is, this layer took
+// 155 us for 256 snippets, and 62 now).  Each wavefront works alone on slabs of two rows x 32 columns, the two
+// rows of 16 windows (W a multiple of 32): the input is NCHW, so the 32 values of row k are
+// 32 neighbouring samples of one plane (shifted by the tap), read straight into the LDS
+// row.  No workgroup barrier in the loop: a wavefront's LDS writes and reads execute in
+// order.  The four wavefronts' sums are added in a fixed order at the end.
 __global__ __launch_bounds__(256) void k_wgrad_first(const uint16_t *__restrict__ X, int N, int nvalid, int H,
-                                                     int W, const uint16_t *__restrict__ dZ,
-                                                     float *__restrict__ part) {
+                                                     int W, const float *__restrict__ dOut,
+                                                     const uint8_t *__restrict__ arg, float *__restrict__ part,
+                                                     float *__restrict__ dbias) {
     constexpr int kLd = 40;
     __shared__ __align__(16) uint16_t lds[2 * 4 * 32 * kLd];   // per wave: A rows, then dZ^T rows
+    __shared__ float sb[4][32];
     const int lane = lane_id(), wave = wave_id();
     uint16_t *A = lds + wave * 2 * 32 * kLd, *Zt = A + 32 * kLd;
     for (int i = lane; i < 32 * kLd; i += 64) A[i] = 0;   // rows 18..31 stay zero
@@ -807,59 +812,84 @@ __global__ __launch_bounds__(256) void k_wgrad_first(const uint16_t *__restrict_
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint32_t HW = (uint32_t)(H * W);
-    const uint32_t nslab = (uint32_t)N * HW / 32u;
+    const uint32_t H2 = (uint32_t)H / 2u, W2 = (uint32_t)W / 2u, across = (uint32_t)W / 32u;
+    const uint32_t nslab = (uint32_t)N * H2 * across;
     const uint32_t nwaves = gridDim.x * 4u;
     const int kq = 8 * (lane >> 4);
-    // lane -> dZ: pixel lane/2, channels 16*(lane%2) .. +15; A: pixel lane%32, channel
-    // lane/32, all nine taps.  The next slab is loaded into registers while the current
-    // one is multiplied.
-    const int zpx = lane >> 1, zc0 = 16 * (lane & 1);
+    // lane -> dOut: window lane/4, channels 8*(lane%4) .. +7; A: pixel lane%32, channel
+    // lane/32, four rows and three columns.  The next slab is loaded into registers while
+    // the current one is multiplied.
+    const int win = lane >> 2, grp = lane & 3;
     const int apx = lane & 31, aci = lane >> 5;
-    uint4 z0, z1;
-    uint16_t av[9];
-    auto load = [&](uint32_t sl) {
-        const uint32_t p0 = sl * 32u;
-        const uint4 *src = (const uint4 *)(dZ + ((size_t)p0 + zpx) * 32 + zc0);
-        z0 = src[0];
-        z1 = src[1];
-        const uint32_t n = p0 / HW, rem = p0 - n * HW, h = rem / (uint32_t)W, w0 = rem - h * (uint32_t)W;
-        const bool img_ok = (int)n < nvalid;
-        const uint16_t *plane = X + ((size_t)n * 2 + aci) * HW;
+    float bias_part[8];
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int hs = (int)h + t / 3 - 1, ws = (int)w0 + apx + t % 3 - 1;
-            av[t] = (img_ok && hs >= 0 && hs < H && ws >= 0 && ws < W) ? plane[(size_t)hs * W + ws] : (uint16_t)0;
-        }
+    for (int c = 0; c < 8; ++c) bias_part[c] = 0.f;
+    float4 g0, g1;
+    uint2 at;
+    uint16_t av[4][3];
+    auto load = [&](uint32_t sl) {
+        const uint32_t n = sl / (H2 * across), rem = sl - n * (H2 * across), h2 = rem / across, w0 = 32u * (rem - h2 * across);
+        const size_t q = ((size_t)n * H2 + h2) * W2 + w0 / 2u + win;
+        g0 = *(const float4 *)(dOut + q * 32 + 8 * grp);
+        g1 = *(const float4 *)(dOut + q * 32 + 8 * grp + 4);
+        at = *(const uint2 *)(arg + q * 32 + 8 * grp);
+        const bool img_ok = (int)n < nvalid;
+        const uint16_t *plane = X + ((size_t)n * 2 + aci) * H * W;
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                const int hs = 2 * (int)h2 + y - 1, ws = (int)w0 + apx + x - 1;
+                av[y][x] = (img_ok && hs >= 0 && hs < H && ws >= 0 && ws < W) ? plane[(size_t)hs * W + ws] : (uint16_t)0;
+            }
     };
     uint32_t sl = blockIdx.x * 4u + (uint32_t)wave;
     if (sl < nslab) load(sl);
     for (; sl < nslab; sl += nwaves) {
-        const uint32_t w[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        uint32_t a[8], b[8];
+        uint16_t x[4][3];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            Zt[(zc0 + 2 * i) * kLd + zpx] = (uint16_t)(w[i] & 0xFFFFu);
-            Zt[(zc0 + 2 * i + 1) * kLd + zpx] = (uint16_t)(w[i] >> 16);
+        for (int c = 0; c < 8; ++c) {
+            a[c] = ((c < 4 ? at.x : at.y) >> (8 * (c & 3))) & 0xFFu;
+            b[c] = f2bf(g[c]);
+            if (a[c] != 255u) bias_part[c] += g[c];
         }
 #pragma unroll
-        for (int t = 0; t < 9; ++t) A[(2 * t + aci) * kLd + apx] = av[t];
-        __builtin_amdgcn_wave_barrier();
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) x[y][t] = av[y][t];
         if (sl + nwaves < nslab) load(sl + nwaves);
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            const u16x8 a = *(const u16x8 *)(A + (it * 16 + (lane & 15)) * kLd + kq);
+        for (int y = 0; y < 2; ++y) {   // the slab's two rows
 #pragma unroll
-            for (int jt = 0; jt < 2; ++jt) {
-                const u16x8 b = *(const u16x8 *)(Zt + (jt * 16 + (lane & 15)) * kLd + kq);
-                acc[it][jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                                      __builtin_bit_cast(bf16x8, b), acc[it][jt], 0,
-                                                                      0, 0);
+            for (int c = 0; c < 8; ++c)
+                *(uint32_t *)&Zt[(8 * grp + c) * kLd + 2 * win] =
+                    (a[c] == 2u * y ? b[c] : 0u) | (a[c] == 2u * y + 1u ? b[c] << 16 : 0u);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) A[(2 * t + aci) * kLd + apx] = x[y + t / 3][t % 3];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const u16x8 av8 = *(const u16x8 *)(A + (it * 16 + (lane & 15)) * kLd + kq);
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt)
+                    acc[it][jt] = mfma_bf16(av8, *(const u16x8 *)(Zt + (jt * 16 + (lane & 15)) * kLd + kq), acc[it][jt]);
             }
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        float v = bias_part[c];
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        if (lane < 4) sb[wave][8 * grp + c] = v;
     }
     // the four wavefronts' sums, added in a fixed order (the staging area is reused)
     __syncthreads();
+    if (threadIdx.x < 32)
+        atomicAdd(&dbias[threadIdx.x], sb[0][threadIdx.x] + sb[1][threadIdx.x] + sb[2][threadIdx.x] + sb[3][threadIdx.x]);
     float *red = (float *)lds;   // [4 waves][4 tiles][4][64]: 16 KiB of the 20 KiB
 #pragma unroll
     for (int it = 0; it < 2; ++it)
@@ -1228,16 +1258,20 @@ hipError_t launch_conv_first(const uint16_t *X, int N, int nvalid, int H, int W,
     return hipSuccess;
 }
 
-hipError_t launch_wgrad(int mode, const uint16_t *X, int N, int nvalid, int H, int W, const uint16_t *dZ, float *part,
-                        int nparts, hipStream_t s) {
+hipError_t launch_wgrad_first(const uint16_t *X, int N, int nvalid, int H, int W, const float *dOut, const uint8_t *arg,
+                              float *part, int nparts, float *dbias, hipStream_t s) {
+    const int64_t P = (int64_t)N * H * W;
+    if (P <= 0 || nparts < 1 || (H & 1) || (W & 31) || P >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_wgrad_first, dim3(nparts), dim3(256), 0, s, X, N, nvalid, H, W, dOut, arg, part, dbias);
+    SPL_HIP_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+hipError_t launch_wgrad(const uint16_t *X, int N, int H, int W, const uint16_t *dZ, float *part, int nparts,
+                        hipStream_t s) {
     const int64_t P = (int64_t)N * H * W;
     if (P <= 0 || (P & 31) || nparts < 1) return hipErrorInvalidValue;
-    if (mode == 0) {
-        if ((W & 31) || (int64_t)N * H * W >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_wgrad_first, dim3(nparts), dim3(256), 0, s, X, N, nvalid, H, W, dZ, part);
-    } else {
-        hipLaunchKernelGGL(k_wgrad, dim3(nparts), dim3(256), 0, s, X, N, H, W, dZ, part);
-    }
+    hipLaunchKernelGGL(k_wgrad, dim3(nparts), dim3(256), 0, s, X, N, H, W, dZ, part);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }

@@ -268,12 +268,17 @@ spl_status backward(spl_ranker *R, const uint16_t *snip, int n, const float *lab
     for (int k = kLayers - 1; k >= 0; --k) {
         const int64_t P = R->P(k);
         const uint16_t *in = k == 0 ? snip : R->at<uint16_t>(R->off_X[k - 1]);
-        RK_TRY(launch_unpool(dX, R->at<uint8_t>(R->off_arg[k]), nb, kH[k], kW[k], dZ, G + po.cb[k], s));
+        const uint8_t *arg = R->at<uint8_t>(R->off_arg[k]);
         // first layer: about 16 slabs of 32 pixels per wavefront; the others: one
         // workgroup per slab up to kWgradGroups
         const int parts = (int)std::max<int64_t>(
             1, std::min<int64_t>(k == 0 ? kWgradPartsFirst : kWgradGroups, k == 0 ? P / 32 / 64 : P / 32));
-        RK_TRY(launch_wgrad(k == 0 ? 0 : 1, in, nb, k == 0 ? n : nb, kH[k], kW[k], dZ, part, parts, s));
+        if (k == 0) {
+            RK_TRY(launch_wgrad_first(in, nb, n, kH[k], kW[k], dX, arg, part, parts, G + po.cb[k], s));
+        } else {
+            RK_TRY(launch_unpool(dX, arg, nb, kH[k], kW[k], dZ, G + po.cb[k], s));
+            RK_TRY(launch_wgrad(in, nb, kH[k], kW[k], dZ, part, parts, s));
+        }
         RK_TRY(launch_sum_parts(part, parts, (int64_t)kKp[k] * kCout, gc + R->gc_w[k], R->at<float>(R->off_part2), s));
         if (k > 0) RK_TRY(launch_conv_back(dZ, nb, kH[k], kW[k], packed + R->pk_wd[k], dX, s));
     }
