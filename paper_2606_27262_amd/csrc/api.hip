@@ -294,14 +294,13 @@ struct spl_batch {
     size_t off_beams = 0, off_items = 0;
     std::vector<size_t> off_X, off_S, off_mu, off_sigma, off_T;   // per beam
     size_t off_S_all = 0, bytes_S_all = 0;
-    size_t off_chunk_off = 0, off_block_sums = 0, off_row_start = 0, off_box_status = 0;
+    size_t off_chunk_off = 0, off_list_status = 0, off_row_start = 0, off_box_status = 0;
     size_t off_hits = 0, off_alive0 = 0, off_alive1 = 0, off_pos = 0, off_run = 0;
     size_t off_nms_blk = 0;   // block index of the hit rows [n_rows][nms_nblk] int32
     size_t off_hit_t = 0;     // the hits' times, packed int32 [hit_cap]
     size_t off_surv = 0;      // survivors of the first peak filter [hit_cap] Hit
     size_t off_surv_start = 0;   // their row starts [n_rows + 1] int64
     int nms_nblk = 0;
-    int n_block_sums = 0;
     std::vector<int> xpitch;
     std::vector<DevBeam> host_beams;
     DevBeam *staging = nullptr;            // pinned copy of host_beams for async upload
@@ -659,9 +658,8 @@ static spl_status build_layout(spl_batch *B) {
         B->off_T[b] = take((size_t)p.ndm * p.nseg * p.widths.size() * sizeof(int32_t));
     }
     B->off_chunk_off = take((size_t)B->n_chunks * sizeof(int64_t));
-    B->off_box_status = take(((size_t)B->n_chunks + 1) * sizeof(uint64_t));
-    B->n_block_sums = scan_blocks(B->hit_cap) + 1;
-    B->off_block_sums = take((size_t)B->n_block_sums * sizeof(int64_t));
+    B->off_box_status = take(((size_t)B->n_chunks + nb) * sizeof(uint64_t));   // one ticket word per beam range
+    B->off_list_status = take((size_t)(scan_blocks(B->hit_cap) + 1) * sizeof(uint64_t));
     B->off_row_start = take((size_t)(B->n_rows + 1) * sizeof(int64_t));
     {
         int n_out_max = 1;
@@ -942,8 +940,8 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
     const int row_lo = B->row_base[b_lo], row_hi = B->row_base[b_hi];
     const int chunk_lo = B->chunk_base[b_lo], chunk_hi = B->chunk_base[b_hi];
     int64_t *chunk_off = (int64_t *)(B->ws + B->off_chunk_off) + chunk_lo;
-    int64_t *block_sums = (int64_t *)(B->ws + B->off_block_sums);
-    uint64_t *box_status = (uint64_t *)(B->ws + B->off_box_status) + chunk_lo;
+    uint64_t *list_status = (uint64_t *)(B->ws + B->off_list_status);
+    uint64_t *box_status = (uint64_t *)(B->ws + B->off_box_status) + chunk_lo + b_lo;
     int64_t *row_start = (int64_t *)(B->ws + B->off_row_start) + row_lo;
     Hit *hits = (Hit *)(B->ws + B->off_hits);
     uint8_t *alive[2] = {(uint8_t *)(B->ws + B->off_alive0), (uint8_t *)(B->ws + B->off_alive1)};
@@ -983,18 +981,16 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
         max_nst = std::max(max_nst, B->plans[b]->nst);
     }
     StageTimer t_bc(B, s, SPL_STAGE_BOXCAR);
-    HIP_TRY(launch_boxcar_one_pass(beams, b_lo, b_hi, chunk_lo, chunk_hi, w_max, box_status, chunk_off, hits, cap,
-                                   &run->n_hits, &run->box_stall, s));
-    HIP_TRY(launch_row_start(beams, b_lo, b_hi, row_lo, row_hi, chunk_lo, chunk_off, &run->n_hits, cap, row_start,
-                             s));
+    int32_t *hit_t = (int32_t *)(B->ws + B->off_hit_t);
+    HIP_TRY(launch_boxcar_one_pass(beams, b_lo, b_hi, chunk_lo, chunk_hi, w_max, box_status, chunk_off, hits, hit_t,
+                                   cap, &run->n_hits, &run->box_stall, s));
     HIP_TRY(t_bc.stop());
     // 4. peak filters, then ordered compaction into candidate records
     StageTimer t_pk(B, s, SPL_STAGE_PEAKS);
     int32_t *blk = (int32_t *)(B->ws + B->off_nms_blk);
-    int32_t *hit_t = (int32_t *)(B->ws + B->off_hit_t);
     if (max_nst)
-        HIP_TRY(launch_nms_index(row_lo, row_hi - row_lo, hits, &run->n_hits, cap, row_start, blk, B->nms_nblk, hit_t,
-                                 s));
+        HIP_TRY(launch_rows_first(beams, b_lo, b_hi, row_lo, row_hi - row_lo, chunk_lo, chunk_off, &run->n_hits, cap,
+                                  row_start, hit_t, blk, B->nms_nblk, list_status, s));
     // The first filter runs over every hit.  The later ones (wider windows, over the few
     // survivors) run over the survivors compacted in order, with their own block index,
     // so that their searches and scans never meet a hit already filtered out.
@@ -1007,11 +1003,10 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
         if (k == 1) {
             Hit *surv = (Hit *)(B->ws + B->off_surv);
             int64_t *surv_start = (int64_t *)(B->ws + B->off_surv_start) + row_lo;
-            HIP_TRY(launch_scan_u8(in, &run->n_hits, cap, block_sums, pos, &run->n_surv, s));
-            HIP_TRY(launch_compact_hits(hits, &run->n_hits, cap, in, pos, surv, row_start, row_hi - row_lo,
-                                        &run->n_surv, surv_start, s));
-            HIP_TRY(launch_nms_index(row_lo, row_hi - row_lo, surv, &run->n_surv, cap, surv_start, blk,
-                                     B->nms_nblk, hit_t, s));
+            HIP_TRY(launch_compact(hits, &run->n_hits, cap, in, list_status, surv, hit_t, pos, &run->n_surv,
+                                   &run->box_stall, s));
+            HIP_TRY(launch_rows_survivors(row_hi - row_lo, row_start, pos, &run->n_hits, &run->n_surv, cap, surv_start,
+                                          hit_t, blk, B->nms_nblk, list_status, s));
             fh = surv;
             fn = &run->n_surv;
             fstart = surv_start;
@@ -1021,14 +1016,9 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
                            &run->n_alive[k], hit_t, s));
         in = o;
     }
-    if (max_nst) {
-        HIP_TRY(launch_scan_u8(in, fn, cap, block_sums, pos, &run->n_cand_beam, s));
-        HIP_TRY(launch_scatter(beams, b_lo, b_hi, fh, fn, cap, in, pos, &run->n_cand_total, cands, cand_cap, s));
-    } else {
-        HIP_TRY(launch_scatter(beams, b_lo, b_hi, hits, &run->n_hits, cap, nullptr, nullptr, &run->n_cand_total,
-                               cands, cand_cap, s));
-    }
-    HIP_TRY(launch_pass_end(run, stats, cap, max_nst, s));
+    HIP_TRY(launch_candidates(beams, b_lo, b_hi, fh, fn, cap, in, list_status, &run->n_cand_total, &run->n_cand_beam,
+                              &run->box_stall, cands, cand_cap, s));
+    HIP_TRY(launch_pass_end(run, stats, cap, max_nst, b_hi == B->nb, cand_cap, s));
     HIP_TRY(t_pk.stop());
     return SPL_OK;
 }
@@ -1036,8 +1026,9 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
 static spl_status enqueue_all(spl_batch *B, spl_candidate *cands, int64_t cap, spl_run_stats *stats,
                               hipStream_t s) {
     DevRun *run = (DevRun *)(B->ws + B->off_run);
-    HIP_TRY(launch_fill_u64((uint64_t *)run, (int64_t)(sizeof(DevRun) / 8), 0, s));
-    HIP_TRY(launch_fill_u64((uint64_t *)stats, (int64_t)(sizeof(spl_run_stats) / 8), 0, s));
+    HIP_TRY(launch_clear((uint64_t *)run, (int64_t)(sizeof(DevRun) / 8), (uint64_t *)stats,
+                         (int64_t)(sizeof(spl_run_stats) / 8), (uint64_t *)(B->ws + B->off_box_status),
+                         (int64_t)B->n_chunks + B->nb, s));
     if (B->mode == SPL_MODE_PERSISTENT_GRAPH) {
         spl_status st = enqueue_range(B, 0, B->nb, true, cands, cap, stats, s);
         if (st != SPL_OK) return st;
@@ -1047,7 +1038,6 @@ static spl_status enqueue_all(spl_batch *B, spl_candidate *cands, int64_t cap, s
             if (st != SPL_OK) return st;
         }
     }
-    HIP_TRY(launch_finalize(run, stats, cap, s));
     return SPL_OK;
 }
 

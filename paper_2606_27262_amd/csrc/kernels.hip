@@ -39,10 +39,14 @@ __device__ __forceinline__ int beam_of_row(const DevBeam *beams, int lo, int hi,
 }
 
 // ------------------------------------------------------------------- fill
-__global__ void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+// Zeroes up to three ranges of words in one launch (the start of a run).
+__global__ void k_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64_t *c, int64_t nc) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb + nc; i += stride) {
+        if (i < na) a[i] = 0;
+        else if (i < na + nb) b[i - na] = 0;
+        else c[i - na - nb] = 0;
+    }
 }
 
 // ------------------------------------------------------------- dedispersion
@@ -525,8 +529,8 @@ __device__ int64_t box_lookback(uint64_t *status, int idx, int64_t tot, int32_t 
 // give-up flag.
 __global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__ beams, int beam_lo,
                                                      int beam_hi, int chunk_lo, int n_chunks, int64_t *offsets,
-                                                     Hit *hits, int64_t cap, uint64_t *status, int64_t *n_total,
-                                                     int32_t *stall) {
+                                                     Hit *hits, int32_t *hit_t, int64_t cap, uint64_t *status,
+                                                     int64_t *n_total, int32_t *stall) {
     extern __shared__ __align__(16) uint32_t S[];
     __shared__ uint32_t sh32[2][kThreads / 64];
     __shared__ int64_t sh64[kThreads / 64];
@@ -716,154 +720,175 @@ __global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__
                 h.B = Bw;
                 h.snr = snr_of(Bw, w, B.mu[ms], B.sigma[ms]);   // the same binary64 value as above
                 hits[pos] = h;
+                hit_t[pos] = t;
             }
             ++pos;
         }
     }
 }
 
-// ------------------------------------------------------------------- scans
-// Exclusive scan of n elements (n read from *n_dev when given, else n_static) in
-// blocks of kScanPerBlock: per-block sums, one-workgroup scan of the sums, then the
-// per-block scan with its offset.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const T *in, const int64_t *n_dev, int64_t n_static,
-                                                          int64_t *block_sums) {
-    __shared__ int64_t sh[kThreads / 64];
-    const int64_t n = n_dev ? min(*n_dev, n_static) : n_static;
-    const int64_t b0 = (int64_t)blockIdx.x * kScanPerBlock;
-    int64_t s = 0;
-    if (b0 < n) {
-        for (int k = 0; k < kScanPerBlock / kThreads; ++k) {
-            const int64_t i = b0 + (int64_t)k * kThreads + threadIdx.x;
-            if (i < n) s += (int64_t)in[i];
-        }
-    }
-    int64_t tot;
-    (void)block_exclusive_scan<int64_t>(s, &tot, sh);
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = tot;
-}
+// ------------------------------------------------------- rows of a hit list
+// One wavefront per row: the row's first hit (clamped to the stored hits) and its block
+// index, blk[r][b] = index (within row r) of the first hit with t >= 64 b, or the row's hit
+// count, from the packed times (which the list's writer left beside the records: the peak
+// filter's searches and window scans read 4 bytes per hit in place of a 24-byte one).  Rows of
+// up to 64 hits, held one a lane, count the hits before each block; in longer ones every hit
+// writes the blocks between its predecessor's and its own.  Starts come from the boxcar's
+// chunk offsets (first list) or from the places of the first filter's survivors.  Also
+// clears the look-back words of the compaction that follows, as many as the list needs.
+// What bounds small searches here is launches of 4-5 us and chains of loads in few
+// workgroups: with row starts, fill, mark, suffix pass, three-kernel scans and compactions as
+// launches of their own a search had 25 where it has 12 now.  1 beam of 256 channels x 128
+// trials x 8192 samples: filters and lists 101 us -> 78, whole search 182 -> 156 us.
+__device__ __forceinline__ int64_t list_size(const int64_t *n, int64_t cap) { return min(*n, cap); }
 
-__global__ __launch_bounds__(1024) void k_scan_top(int64_t *block_sums, int nblocks, int64_t *total_out) {
-    __shared__ int64_t sh[16];
-    __shared__ int64_t s_carry;
-    const int tid = threadIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    for (int base = 0; base < nblocks; base += 1024) {
-        const int i = base + tid;
-        const int64_t v = i < nblocks ? block_sums[i] : 0;
-        const int64_t x = wave_inclusive_scan(v);
-        if (lane == 63) sh[wave] = x;
-        __syncthreads();
-        int64_t pre = 0, tot = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wave) pre += sh[w];
-            tot += sh[w];
-        }
-        const int64_t c = s_carry;
-        if (i < nblocks) block_sums[i] = c + pre + x - v;
-        __syncthreads();
-        if (tid == 0) s_carry = c + tot;
-        __syncthreads();
-    }
-    if (tid == 0 && total_out) *total_out = s_carry;
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_scan_down(const T *in, const int64_t *n_dev, int64_t n_static,
-                                                        const int64_t *block_offsets, int64_t *out) {
-    __shared__ int64_t sh[kThreads / 64];
-    const int64_t n = n_dev ? min(*n_dev, n_static) : n_static;
-    const int64_t b0 = (int64_t)blockIdx.x * kScanPerBlock;
-    if (b0 >= n) return;
-    int64_t carry = block_offsets[blockIdx.x];
-    for (int k = 0; k < kScanPerBlock / kThreads; ++k) {
-        const int64_t i = b0 + (int64_t)k * kThreads + threadIdx.x;
-        const int64_t v = i < n ? (int64_t)in[i] : 0;
-        int64_t tot;
-        const int64_t ex = block_exclusive_scan<int64_t>(v, &tot, sh);
-        if (i < n) out[i] = carry + ex;
-        carry += tot;
-    }
-}
-
-// First hit of every row (clamped to the stored hits) from the chunk offsets.
-__global__ void k_row_start(const DevBeam *__restrict__ beams, int beam_lo, int beam_hi, int row_lo,
-                            int row_hi, int chunk_lo, const int64_t *chunk_off, const int64_t *n_hits,
-                            int64_t cap, int64_t *row_start) {
-    const int r = row_lo + blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stored = min(*n_hits, cap);
-    if (r < row_hi) {
-        const DevBeam &B = beams[beam_of_row(beams, beam_lo, beam_hi, r)];
-        const int chunk = B.chunk_base + (r - B.row_base) * B.nchunk_t;
-        row_start[r - row_lo] = min(chunk_off[chunk - chunk_lo], stored);
-    }
-    if (r == row_hi) row_start[r - row_lo] = stored;
-}
-
-// ------------------------------------------------------- survivors of the first filter
-// The later peak filters see only the survivors of the first, compacted in order
-// (out[pos[p]] = hits[p] for alive p, pos the exclusive scan of the flags), with row
-// starts out_start[r] = pos[row_start[r]] (the count of survivors before the row).
-__global__ __launch_bounds__(kThreads) void k_compact_hits(const Hit *__restrict__ hits, const int64_t *n_hits,
-                                                           int64_t cap, const uint8_t *__restrict__ alive,
-                                                           const int64_t *__restrict__ pos, Hit *__restrict__ out) {
-    const int64_t n = min(*n_hits, cap);
-    for (int64_t p = blockIdx.x * (int64_t)kThreads + threadIdx.x; p < n; p += (int64_t)gridDim.x * kThreads)
-        if (alive[p]) out[pos[p]] = hits[p];
-}
-
-__global__ __launch_bounds__(kThreads) void k_compact_row_start(const int64_t *__restrict__ row_start, int n_rows,
-                                                                const int64_t *n_hits, int64_t cap,
-                                                                const int64_t *__restrict__ pos,
-                                                                const int64_t *n_surv, int64_t *out_start) {
-    const int r = blockIdx.x * kThreads + threadIdx.x;
-    if (r > n_rows) return;
-    const int64_t n = min(*n_hits, cap);
-    const int64_t i = row_start[r];
-    out_start[r] = (r < n_rows && i < n) ? pos[i] : *n_surv;
-}
-
-// ------------------------------------------------------- block index of hit rows
-// blk[r][b] = index (within row r) of the first hit with t >= 64 b, or the row's hit count.
-// k_nms_mark writes the first hit of every occupied block (the table holds INT32_MAX
-// elsewhere) and the hits' times as a packed int32 array (the peak filter's searches
-// and window scans read 4 bytes per hit instead of a 24-byte record); k_nms_suffix then
-// takes the suffix minimum along each row.
-__global__ __launch_bounds__(kThreads) void k_nms_mark(int row_lo, const Hit *__restrict__ hits,
-                                                       const int64_t *n_hits, int64_t cap,
-                                                       const int64_t *__restrict__ row_start, int32_t *blk,
-                                                       int nblk, int32_t *__restrict__ hit_t) {
-    const int64_t n = min(*n_hits, cap);
-    for (int64_t q = blockIdx.x * (int64_t)kThreads + threadIdx.x; q < n; q += (int64_t)gridDim.x * kThreads) {
-        const Hit h = hits[q];
-        hit_t[q] = h.t;
-        const int r = h.row - row_lo;
-        const int b = h.t >> kNmsBlockShift;
-        const bool first = q == 0 || hits[q - 1].row != h.row || (hits[q - 1].t >> kNmsBlockShift) != b;
-        if (first) blk[(int64_t)r * nblk + b] = (int32_t)(q - row_start[r]);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_nms_suffix(const int64_t *__restrict__ row_start, int n_rows,
-                                                         int32_t *blk, int nblk) {
+template <bool FIRST>
+__global__ __launch_bounds__(kThreads) void k_rows(const DevBeam *__restrict__ beams, int beam_lo, int beam_hi,
+                                                   int row_lo, int n_rows, int chunk_lo,
+                                                   const int64_t *__restrict__ chunk_off,
+                                                   const int64_t *__restrict__ start_before,
+                                                   const int64_t *__restrict__ pos, const int64_t *n_before,
+                                                   const int64_t *n_list, int64_t cap, int64_t *row_start,
+                                                   const int32_t *__restrict__ hit_t, int32_t *__restrict__ blk,
+                                                   int nblk, uint64_t *status, int64_t ticket) {
     const int lane = lane_id();
+    const int64_t n = list_size(n_list, cap), g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    for (int64_t i = g; i * kScanPerBlock < n; i += (int64_t)gridDim.x * kThreads) status[i] = 0;
+    if (g == 0) status[ticket] = 0;
     const int r = blockIdx.x * (kThreads / 64) + wave_id();
     if (r >= n_rows) return;   // uniform per wavefront
-    int32_t carry = (int32_t)(row_start[r + 1] - row_start[r]);
-    int32_t *row = blk + (int64_t)r * nblk;
-    for (int c = (nblk - 1) & ~63; c >= 0; c -= 64) {
-        const int b = c + lane;
-        int32_t v = b < nblk ? row[b] : INT_MAX;
-        v = min(v, carry);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t o = __shfl_down(v, off);
-            if (lane + off < 64) v = min(v, o);
+    int64_t at = n;
+    if (lane < 2 && r + lane < n_rows) {   // of this row and the next
+        const int rr = r + lane;
+        if constexpr (FIRST) {
+            const DevBeam &B = beams[beam_of_row(beams, beam_lo, beam_hi, row_lo + rr)];
+            at = min(chunk_off[B.chunk_base + (row_lo + rr - B.row_base) * B.nchunk_t - chunk_lo], n);
+        } else {
+            const int64_t i = start_before[rr];
+            if (i < list_size(n_before, cap)) at = min(pos[i], n);
         }
-        if (b < nblk) row[b] = v;
-        carry = __shfl(v, 0);
+    }
+    const int64_t s = __shfl(at, 0), e = __shfl(at, 1);
+    if (lane == 0) row_start[r] = s;
+    if (r == n_rows - 1 && lane == 1) row_start[n_rows] = e;
+    const int nh = (int)(e - s);
+    int32_t *row = blk + (int64_t)r * nblk;
+    if (nh <= 64) {
+        const int32_t t = lane < nh ? hit_t[s + lane] : 0;
+        for (int c = 0; c < nblk; c += 64) {
+            const int b = c + lane;
+            int before = 0;
+            for (int i = 0; i < nh; ++i) before += __builtin_amdgcn_readlane(t, i) < b << kNmsBlockShift ? 1 : 0;
+            if (b < nblk) row[b] = before;
+        }
+        return;
+    }
+    int done = -1;   // the block of the last hit so far
+    for (int i0 = 0; i0 < nh; i0 += 64) {
+        const int i = i0 + lane;
+        const int b = i < nh ? min(hit_t[s + i] >> kNmsBlockShift, nblk - 1) : INT_MAX;
+        int prev = __shfl_up(b, 1);
+        if (lane == 0) prev = done;
+        if (i < nh)
+            for (int x = prev + 1; x <= b; ++x) row[x] = i;
+        done = __shfl(b, min(63, nh - 1 - i0));
+    }
+    for (int x = done + 1 + lane; x < nblk; x += 64) row[x] = nh;
+}
+
+// ------------------------------------------------------- survivors of a peak filter
+// The survivors (alive[p] != 0) in order, each chunk of kScanPerBlock hits placed by a
+// look-back over the chunks before it (tickets follow the order in which workgroups take
+// them).  Chunks of 512 hits: 2 turns of loads a wavefront, and a few thousand hits meet
+// enough workgroups (4096: 14-18 us a launch on 1 beam of 128 trials, its 16 turns' dependent
+// loads one after another).  CANDS: as candidate records after `*base` earlier ones; else as the list that the
+// later, wider filters see, with its packed times, and pos[p] the survivors before p.
+struct Survivors {
+    const Hit *hits;
+    const int64_t *n_hits;
+    int64_t cap;
+    const uint8_t *alive;
+    uint64_t *status;
+    int64_t ticket;     // place of the ticket counter in status
+    int64_t *n_out;
+    int32_t *stall;
+};
+
+__device__ __forceinline__ void write_candidate(const DevBeam *__restrict__ beams, int beam_lo, int beam_hi, const Hit &h,
+                                                spl_candidate *cand) {
+    const DevBeam &B = beams[beam_of_row(beams, beam_lo, beam_hi, h.row)];
+    spl_candidate c;
+    c.beam = B.beam;
+    c.dm_index = h.row - B.row_base;
+    c.t_sample = h.t;
+    c.width = h.w;
+    c.boxcar_sum = h.B;
+    c.snr = (float)h.snr;
+    c.dm = (float)B.dms[c.dm_index];
+    c.flags = 0u;
+    *cand = c;
+}
+
+template <bool CANDS>
+__global__ __launch_bounds__(kThreads) void k_survivors(Survivors v, Hit *__restrict__ out, int32_t *__restrict__ hit_t,
+                                                        int64_t *__restrict__ pos, const DevBeam *__restrict__ beams,
+                                                        int beam_lo, int beam_hi, const int64_t *base,
+                                                        spl_candidate *cands, int64_t cand_cap) {
+    __shared__ int64_t s_idx, s_base;
+    __shared__ int s_tot[kThreads / 64];
+    constexpr int kTurns = kScanPerBlock / kThreads;   // of 64 hits a wavefront
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int64_t n = list_size(v.n_hits, v.cap);
+    if (n == 0 && blockIdx.x == 0 && tid == 0) *v.n_out = 0;
+    for (;;) {
+        __syncthreads();   // the chunk before is placed
+        if (tid == 0) s_idx = (int64_t)atomicAdd((unsigned long long *)&v.status[v.ticket], 1ull);
+        __syncthreads();
+        const int64_t idx = s_idx, p0 = idx * kScanPerBlock + wave * (kTurns * 64) + lane;
+        if (idx * kScanPerBlock >= n) break;   // uniform
+        uint64_t alive[kTurns];
+        int mine = 0;
+#pragma unroll
+        for (int k = 0; k < kTurns; ++k) {
+            const int64_t p = p0 + 64 * k;
+            alive[k] = __ballot(p < n && v.alive[p] != 0);
+            mine += __builtin_popcountll(alive[k]);
+        }
+        if (lane == 0) s_tot[wave] = mine;
+        __syncthreads();
+        int tot = 0, before = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) {
+            if (w < wave) before += s_tot[w];
+            tot += s_tot[w];
+        }
+        if (tid == 0) box_publish_count(v.status, (int)idx, tot);
+        if (wave == 0) {
+            const int64_t excl = box_lookback(v.status, (int)idx, tot, v.stall);
+            if (lane == 0) {
+                s_base = excl;
+                if ((idx + 1) * kScanPerBlock >= n) *v.n_out = excl + tot;
+            }
+        }
+        __syncthreads();
+        int64_t first = s_base + before;
+        if constexpr (CANDS) first += *base;
+#pragma unroll
+        for (int k = 0; k < kTurns; ++k) {
+            const int64_t p = p0 + 64 * k, o = first + __builtin_popcountll(alive[k] & ((1ull << lane) - 1));
+            const bool mine_alive = alive[k] >> lane & 1;
+            if constexpr (CANDS) {
+                if (mine_alive && o < cand_cap) write_candidate(beams, beam_lo, beam_hi, v.hits[p], cands + o);
+            } else {
+                if (p < n) pos[p] = o;
+                if (mine_alive) {
+                    const Hit h = v.hits[p];
+                    out[o] = h;
+                    hit_t[o] = h.t;
+                }
+            }
+            first += __builtin_popcountll(alive[k]);
+        }
     }
 }
 
@@ -872,8 +897,7 @@ __global__ __launch_bounds__(kThreads) void k_nms_suffix(const int64_t *__restri
 // alive hit of its beam within |dd| <= rd, |dt| <= rt beats it.  Rows of a beam are
 // contiguous in the hit list and sorted by t; a neighbour row's window starts at the
 // first hit with t >= t_p - rt, found by bisection between the row's first hits of that
-// 64-sample block and of the next (the block index, built once per run by k_nms_mark and
-// k_nms_suffix): at most 6 dependent loads instead of one per halving of the row.  A row
+// 64-sample block and of the next (the block index, built for the list by k_rows): at most 6 dependent loads instead of one per halving of the row.  A row
 // holds at most one hit per sample, so in p's own row the window starts no more than rt
 // entries before p and needs no search.  Searches and scans read the packed times; a
 // hit's S/N is loaded only when it lies in the window.
@@ -970,36 +994,20 @@ __global__ __launch_bounds__(kThreads) void k_nms(const DevBeam *__restrict__ be
     if (threadIdx.x == 0 && tot) atomicAdd((unsigned long long *)n_alive, (unsigned long long)tot);
 }
 
-// Candidate records of the survivors, in hit order, after `*base` earlier records.
-__global__ __launch_bounds__(kThreads) void k_scatter(const DevBeam *__restrict__ beams, int beam_lo, int beam_hi,
-                                                      const Hit *__restrict__ hits, const int64_t *n_hits,
-                                                      int64_t cap, const uint8_t *alive, const int64_t *pos,
-                                                      const int64_t *base, spl_candidate *cands,
-                                                      int64_t cand_cap) {
-    const int64_t n = min(*n_hits, cap);
-    const int64_t b0 = *base;
-    for (int64_t p = blockIdx.x * (int64_t)kThreads + threadIdx.x; p < n; p += (int64_t)gridDim.x * kThreads) {
-        if (alive && !alive[p]) continue;
-        const int64_t o = b0 + (pos ? pos[p] : p);
-        if (o >= cand_cap) continue;
-        const Hit h = hits[p];
-        const DevBeam &B = beams[beam_of_row(beams, beam_lo, beam_hi, h.row)];
-        spl_candidate c;
-        c.beam = B.beam;
-        c.dm_index = h.row - B.row_base;
-        c.t_sample = h.t;
-        c.width = h.w;
-        c.boxcar_sum = h.B;
-        c.snr = (float)h.snr;
-        c.dm = (float)B.dms[c.dm_index];
-        c.flags = 0u;
-        cands[o] = c;
-    }
+// Candidate records of all hits (plans without a peak filter), after `*base` earlier records.
+__global__ __launch_bounds__(kThreads) void k_all_hits(const DevBeam *__restrict__ beams, int beam_lo, int beam_hi,
+                                                       const Hit *__restrict__ hits, const int64_t *n_hits,
+                                                       int64_t cap, const int64_t *base, spl_candidate *cands,
+                                                       int64_t cand_cap) {
+    const int64_t n = list_size(n_hits, cap), b0 = *base;
+    for (int64_t p = blockIdx.x * (int64_t)kThreads + threadIdx.x; p < n; p += (int64_t)gridDim.x * kThreads)
+        if (b0 + p < cand_cap) write_candidate(beams, beam_lo, beam_hi, hits[p], cands + b0 + p);
 }
 
 // End of the launch sequence of a beam range: fold the range's counts into the run
-// statistics; the next range's candidates go after this one's.
-__global__ void k_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst) {
+// statistics; the next range's candidates go after this one's.  The last range's end
+// closes the statistics.
+__global__ void k_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, bool last, int64_t cand_cap) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     stats->n_hits += run->n_hits;
     if (run->n_hits > hit_cap && stats->hit_overflow == 0) stats->hit_overflow = 1;
@@ -1009,10 +1017,7 @@ __global__ void k_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, i
         run->n_alive[k] = 0;
     }
     run->n_cand_total += nst ? run->n_cand_beam : min(run->n_hits, hit_cap);
-}
-
-__global__ void k_finalize(DevRun *run, spl_run_stats *stats, int64_t cand_cap) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    if (!last) return;
     stats->n_candidates = run->n_cand_total;
     stats->cand_overflow = run->n_cand_total > cand_cap ? 1 : 0;
 }
@@ -1100,15 +1105,6 @@ hipError_t launch_dedisp(int dw, int j, int nw, int sv, int nbuf, const DevBeam 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    int64_t blocks = (n + kThreads - 1) / kThreads;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)blocks), dim3(kThreads), 0, s, p, n, v);
-    SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
 hipError_t launch_thresholds(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo, int row_hi, hipStream_t s) {
     const int n = row_hi - row_lo;
     if (n <= 0) return hipSuccess;
@@ -1117,52 +1113,29 @@ hipError_t launch_thresholds(const DevBeam *beams, int beam_lo, int beam_hi, int
     return hipSuccess;
 }
 
+hipError_t launch_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64_t *c, int64_t nc, hipStream_t s) {
+    const int64_t n = na + nb + nc;
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, s, a, na, b, nb, c,
+                       nc);
+    SPL_HIP_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
 hipError_t launch_boxcar_one_pass(const DevBeam *beams, int beam_lo, int beam_hi, int chunk_lo, int chunk_hi,
-                                  int w_max, uint64_t *status, int64_t *offsets, Hit *hits, int64_t cap,
-                                  int64_t *n_total, int32_t *stall, hipStream_t s) {
+                                  int w_max, uint64_t *status, int64_t *offsets, Hit *hits, int32_t *hit_t,
+                                  int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s) {
     const int n = chunk_hi - chunk_lo;
-    if (!status || !offsets || !hits || !n_total || !stall) return hipErrorInvalidValue;
-    if (n <= 0) return launch_fill_u64((uint64_t *)n_total, 1, 0, s);
-    // the look-back words of the range and its ticket counter start at zero
-    hipError_t e = launch_fill_u64(status, (int64_t)n + 1, 0, s);
-    if (e != hipSuccess) return e;
+    if (!status || !offsets || !hits || !hit_t || !n_total || !stall) return hipErrorInvalidValue;
+    if (n <= 0) return launch_clear((uint64_t *)n_total, 1, nullptr, 0, nullptr, 0, s);
     const size_t lds = (size_t)(kBoxTile + w_max + 8) * sizeof(uint32_t);
     hipLaunchKernelGGL(k_boxcar, dim3(n), dim3(kThreads), lds, s, beams, beam_lo, beam_hi, chunk_lo, n, offsets,
-                       hits, cap, status, n_total, stall);
+                       hits, hit_t, cap, status, n_total, stall);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
 
 int scan_blocks(int64_t n_max) { return (int)((n_max + kScanPerBlock - 1) / kScanPerBlock); }
-
-template <typename T>
-static hipError_t launch_scan_t(const T *in, const int64_t *n_dev, int64_t n_max, int64_t *block_sums,
-                                int64_t *out, int64_t *total, hipStream_t s) {
-    const int nb = scan_blocks(n_max);
-    if (nb <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scan_reduce<T>, dim3(nb), dim3(kThreads), 0, s, in, n_dev, n_max, block_sums);
-    SPL_HIP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, block_sums, nb, total);
-    SPL_HIP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_scan_down<T>, dim3(nb), dim3(kThreads), 0, s, in, n_dev, n_max, block_sums, out);
-    SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_scan_u8(const uint8_t *in, const int64_t *n_dev, int64_t n_max, int64_t *block_sums,
-                          int64_t *out, int64_t *total, hipStream_t s) {
-    return launch_scan_t<uint8_t>(in, n_dev, n_max, block_sums, out, total, s);
-}
-
-hipError_t launch_row_start(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo, int row_hi, int chunk_lo,
-                            const int64_t *chunk_off, const int64_t *n_hits, int64_t cap, int64_t *row_start,
-                            hipStream_t s) {
-    const int n = row_hi - row_lo + 1;
-    hipLaunchKernelGGL(k_row_start, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, s, beams, beam_lo,
-                       beam_hi, row_lo, row_hi, chunk_lo, chunk_off, n_hits, cap, row_start);
-    SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
-}
 
 static int grid_for(int64_t cap) {
     int64_t g = (cap + kThreads - 1) / kThreads;
@@ -1171,29 +1144,53 @@ static int grid_for(int64_t cap) {
     return (int)g;
 }
 
-hipError_t launch_compact_hits(const Hit *hits, const int64_t *n_hits, int64_t cap, const uint8_t *alive,
-                               const int64_t *pos, Hit *out, const int64_t *row_start, int n_rows,
-                               const int64_t *n_surv, int64_t *out_start, hipStream_t s) {
-    hipLaunchKernelGGL(k_compact_hits, dim3(grid_for(cap)), dim3(kThreads), 0, s, hits, n_hits, cap, alive, pos, out);
-    SPL_HIP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_compact_row_start, dim3((n_rows + 1 + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
-                       row_start, n_rows, n_hits, cap, pos, n_surv, out_start);
+hipError_t launch_rows_first(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo, int n_rows, int chunk_lo,
+                             const int64_t *chunk_off, const int64_t *n_hits, int64_t cap, int64_t *row_start,
+                             const int32_t *hit_t, int32_t *blk, int nblk, uint64_t *status, hipStream_t s) {
+    if (n_rows <= 0) return hipErrorInvalidValue;
+    const int waves = kThreads / 64;
+    hipLaunchKernelGGL(k_rows<true>, dim3((unsigned)((n_rows + waves - 1) / waves)), dim3(kThreads), 0, s, beams, beam_lo,
+                       beam_hi, row_lo, n_rows, chunk_lo, chunk_off, (const int64_t *)nullptr, (const int64_t *)nullptr,
+                       (const int64_t *)nullptr, n_hits, cap, row_start, hit_t, blk, nblk, status,
+                       (int64_t)scan_blocks(cap));
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_nms_index(int row_lo, int n_rows, const Hit *hits, const int64_t *n_hits, int64_t cap,
-                            const int64_t *row_start, int32_t *blk, int nblk, int32_t *hit_t, hipStream_t s) {
-    if (n_rows <= 0) return hipSuccess;
-    if (nblk & 1) return hipErrorInvalidValue;   // filled in 8-byte words
-    hipError_t e = launch_fill_u64((uint64_t *)blk, (int64_t)n_rows * nblk / 2, 0x7FFFFFFF7FFFFFFFull, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_nms_mark, dim3(grid_for(cap)), dim3(kThreads), 0, s, row_lo, hits, n_hits, cap, row_start,
-                       blk, nblk, hit_t);
-    SPL_HIP_LAUNCH_CHECK();
+hipError_t launch_rows_survivors(int n_rows, const int64_t *start_before, const int64_t *pos, const int64_t *n_before,
+                                 const int64_t *n_list, int64_t cap, int64_t *row_start, const int32_t *hit_t,
+                                 int32_t *blk, int nblk, uint64_t *status, hipStream_t s) {
+    if (n_rows <= 0) return hipErrorInvalidValue;
     const int waves = kThreads / 64;
-    hipLaunchKernelGGL(k_nms_suffix, dim3((unsigned)((n_rows + waves - 1) / waves)), dim3(kThreads), 0, s, row_start,
-                       n_rows, blk, nblk);
+    hipLaunchKernelGGL(k_rows<false>, dim3((unsigned)((n_rows + waves - 1) / waves)), dim3(kThreads), 0, s,
+                       (const DevBeam *)nullptr, 0, 0, 0, n_rows, 0, (const int64_t *)nullptr, start_before, pos, n_before,
+                       n_list, cap, row_start, hit_t, blk, nblk, status, (int64_t)scan_blocks(cap));
+    SPL_HIP_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+static dim3 survivor_grid(int64_t cap) { return dim3((unsigned)std::max(1, std::min(scan_blocks(cap), 1024))); }
+
+hipError_t launch_compact(const Hit *hits, const int64_t *n_hits, int64_t cap, const uint8_t *alive, uint64_t *status,
+                          Hit *out, int32_t *hit_t, int64_t *pos, int64_t *n_out, int32_t *stall, hipStream_t s) {
+    const Survivors v{hits, n_hits, cap, alive, status, (int64_t)scan_blocks(cap), n_out, stall};
+    hipLaunchKernelGGL(k_survivors<false>, survivor_grid(cap), dim3(kThreads), 0, s, v, out, hit_t, pos,
+                       (const DevBeam *)nullptr, 0, 0, (const int64_t *)nullptr, (spl_candidate *)nullptr, (int64_t)0);
+    SPL_HIP_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+hipError_t launch_candidates(const DevBeam *beams, int beam_lo, int beam_hi, const Hit *hits, const int64_t *n_hits,
+                             int64_t cap, const uint8_t *alive, uint64_t *status, const int64_t *base, int64_t *n_out,
+                             int32_t *stall, spl_candidate *cands, int64_t cand_cap, hipStream_t s) {
+    if (!alive) {
+        hipLaunchKernelGGL(k_all_hits, dim3(grid_for(cap)), dim3(kThreads), 0, s, beams, beam_lo, beam_hi, hits, n_hits,
+                           cap, base, cands, cand_cap);
+    } else {
+        const Survivors v{hits, n_hits, cap, alive, status, (int64_t)scan_blocks(cap), n_out, stall};
+        hipLaunchKernelGGL(k_survivors<true>, survivor_grid(cap), dim3(kThreads), 0, s, v, (Hit *)nullptr,
+                           (int32_t *)nullptr, (int64_t *)nullptr, beams, beam_lo, beam_hi, base, cands, cand_cap);
+    }
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -1208,23 +1205,9 @@ hipError_t launch_nms(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo
     return hipSuccess;
 }
 
-hipError_t launch_scatter(const DevBeam *beams, int beam_lo, int beam_hi, const Hit *hits, const int64_t *n_hits,
-                          int64_t cap, const uint8_t *alive, const int64_t *pos, const int64_t *base,
-                          spl_candidate *cands, int64_t cand_cap, hipStream_t s) {
-    hipLaunchKernelGGL(k_scatter, dim3(grid_for(cap)), dim3(kThreads), 0, s, beams, beam_lo, beam_hi, hits,
-                       n_hits, cap, alive, pos, base, cands, cand_cap);
-    SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, hipStream_t s) {
-    hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, run, stats, hit_cap, nst);
-    SPL_HIP_LAUNCH_CHECK();
-    return hipSuccess;
-}
-
-hipError_t launch_finalize(DevRun *run, spl_run_stats *stats, int64_t cand_cap, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, run, stats, cand_cap);
+hipError_t launch_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, bool last, int64_t cand_cap,
+                           hipStream_t s) {
+    hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, run, stats, hit_cap, nst, last, cand_cap);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
