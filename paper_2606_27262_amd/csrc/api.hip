@@ -248,6 +248,7 @@ struct PlanLayout {
     bool shared_tried = false;       // sh was built, or found not to pay, for this plan
     SharedTables sh;                 // sh.ntiles = 0: row staging
     size_t off_dcm = 0, off_base = 0, off_dms = 0, off_delays = 0;
+    bool direct() const { return !shared && dedisp_direct(tiles.dw, tiles.j, tiles.nw); }   // nothing staged
 };
 
 struct Region {
@@ -323,9 +324,9 @@ struct spl_batch {
     bool tables_uploaded = false;
 };
 
-// Clocks of a CU per added sample of the row-staging kernel (measured: 53 of 64 lanes add
-// in a clock on the 4096-channel band, 37 on the 2048-channel 300-500 MHz band).
-static constexpr double kRowAddsPerClock = 50.0;
+// Samples that a CU adds in a clock (of 64 lanes; 34 billion over 512 trials x 1024 channels):
+// rows staged in tiles of 32 trials 50, of 16 trials 40-44; read directly 35.
+static constexpr double kRowAddsPerClock = 50.0, kDirectAddsPerClock = 35.0;
 
 // Reserved bytes of a plan's offset table: room for the widest padding (64 trials).
 static size_t table_bytes(const spl_plan &p) {
@@ -392,7 +393,7 @@ static spl_status layout_plan(PlanLayout &L) {
         L.row_bytes[k] = TT + 32 + (int)align_up((size_t)span, 16);
     }
     const int rmax = *std::max_element(L.row_bytes.begin(), L.row_bytes.end());
-    L.tiles.sv = rmax <= 1024 ? 1 : 2;
+    L.tiles.sv = rmax <= 1024 || L.direct() ? 1 : 2;
     if (rmax > 2048 || !dedisp_shape_supported(L.tiles.dw, L.tiles.j, L.tiles.nw, L.tiles.sv, L.tiles.nb))
         return fail(SPL_E_UNSUPPORTED, "a DM tile spans %d bytes of staged row: too wide for this tile shape "
                     "(use fewer trials per tile)", rmax);
@@ -401,46 +402,6 @@ static spl_status layout_plan(PlanLayout &L) {
     L.ntile_d = (p.ndm + L.tile_trials - 1) / L.tile_trials;
     L.ntile_t = (p.n_dd + L.tile_samples - 1) / L.tile_samples;
     return SPL_OK;
-}
-
-// Default tiling: 8 wavefronts x 4 trials x 512 samples, smaller tiles when the plan
-// gives too few work items to fill 256 compute units, fewer trials per tile when the
-// delay spread of a tile would not fit the staged rows.
-static bool tile_fits(const spl_plan &p, int td, int j) {
-    // widest delay spread over td consecutive trials, any channel
-    int worst = 0;
-    for (int c = 0; c < p.nch; c += std::max(1, p.nch / 64)) {
-        for (int d0 = 0; d0 < p.ndm; d0 += td) {
-            const int d1 = std::min(p.ndm, d0 + td) - 1;
-            worst = std::max(worst, std::abs(p.delays[(size_t)d1 * p.nch + c] - p.delays[(size_t)d0 * p.nch + c]));
-        }
-    }
-    const int c = p.nch - 1;
-    for (int d0 = 0; d0 < p.ndm; d0 += td) {
-        const int d1 = std::min(p.ndm, d0 + td) - 1;
-        worst = std::max(worst, std::abs(p.delays[(size_t)d1 * p.nch + c] - p.delays[(size_t)d0 * p.nch + c]));
-    }
-    return 256 * j + 32 + (int)align_up((size_t)worst + 64, 16) <= 2048;
-}
-
-static Tiles default_row_tiles(const spl_plan &p) {
-    static const int shapes[][3] = {{4, 2, 8}, {4, 1, 8}, {2, 2, 8}, {4, 1, 4}};   // (trials/wave, groups, waves)
-    for (const auto &sh : shapes) {
-        Tiles t;
-        t.dw = sh[0];
-        t.j = sh[1];
-        t.nw = sh[2];
-        const int td = t.dw * t.nw;
-        const int64_t items = (int64_t)((p.ndm + td - 1) / td) * ((p.n_dd + 256 * t.j - 1) / (256 * t.j));
-        if (items < 1024 && &sh != &shapes[3]) continue;
-        if (!tile_fits(p, td, t.j)) continue;
-        return t;
-    }
-    Tiles t;
-    t.dw = 4;
-    t.j = 1;
-    t.nw = 4;
-    return t;
 }
 
 // The largest spread of a channel's delays over td consecutive trials.
@@ -463,6 +424,31 @@ static int widest_tile(const spl_plan &p, int td) {
     return widest;
 }
 
+// Default tiling without shared rows: 8 wavefronts of 4 (2) trials x 512 samples where the
+// plan gives them work items for the chip and a tile's rows are short enough to be staged by
+// one load a lane; else 16 trials x 256 samples, read where they are.  512 trials of 1024
+// channels over 4 x 16384 samples, whatever the spread of the delays: 1.58 ms read directly;
+// staged in tiles of 32 trials 1.12 ms with rows up to 1 KB and 1.56-1.83 ms with longer ones,
+// of 16 trials 1.27-1.40 and 2.09 ms.  With few work items the staged tiles leave CUs idle and
+// one workgroup's chunks take turns with their loads: 128 trials x 256 channels x 8192 samples
+// 36 us directly, 39-57 us staged; 64 trials x 1024 channels x 4096 samples 53 and 129-259 us.
+static Tiles default_row_tiles(const spl_plan &p) {
+    static const int shapes[][3] = {{4, 2, 8}, {2, 2, 8}};   // (trials/wave, groups, waves)
+    Tiles t;
+    for (const auto &sh : shapes) {
+        t.dw = sh[0];
+        t.j = sh[1];
+        t.nw = sh[2];
+        const int td = t.dw * t.nw;
+        const int64_t items = (int64_t)((p.ndm + td - 1) / td) * ((p.n_dd + 256 * t.j - 1) / (256 * t.j));
+        if (items >= 1024 && 256 * t.j + 32 + (int)align_up((size_t)widest_tile(p, td), 16) <= 1024) return t;
+    }
+    t.dw = 4;
+    t.j = 1;
+    t.nw = 4;
+    return t;
+}
+
 // The 16-wavefront tiles where shared rows are modelled to take less time than the row
 // staging of the tiles above on the whole chip (tiles per CU, rounded up, times the clocks
 // of one): a few large tiles leave CUs idle that many small ones would fill.
@@ -475,7 +461,8 @@ static Tiles default_tiles(PlanLayout &L, int64_t beams) {
         return (double)((n + 255) / 256);
     };
     const int td = row.dw * row.nw, tt = 256 * row.j, ts = 2 * L.sh.shape.half();
-    const double by_row = rounds(td, tt) * ((double)td * tt * p.nch / kRowAddsPerClock);
+    const double rate = row.nw == 4 ? kDirectAddsPerClock : kRowAddsPerClock;
+    const double by_row = rounds(td, tt) * ((double)td * tt * p.nch / rate);
     const double by_sums = rounds(L.sh.shape.td(), ts) * (L.sh.clocks / L.sh.ntiles);
     if (by_sums < by_row) {
         // (the row staging of the shape has to take the plan too: layout_plan's limits)
@@ -510,7 +497,7 @@ static void choose_chunk(PlanLayout &L, size_t lds_budget) {
     L.tiles.cc = p2;
     L.quarter = (p2 + 1) * rmax;   // chan_chunk rows + the zero row
     L.dtab.clear();
-    if (L.shared) return;
+    if (L.shared || L.direct()) return;
     const spl_plan &p = *L.plan;
     L.dtab.resize((size_t)p.nch * L.ndm_pad);
     constexpr int kBlock = 32;   // channels by trials, transposed in blocks that stay in cache
@@ -817,7 +804,7 @@ static spl_status copy_tables(spl_batch *B) {
     for (auto &L : B->layouts) {
         if (L.shared) {
             HIP_TRY(hipMemcpy(B->ws + L.off_dcm, L.sh.blob.data(), L.sh.blob.size(), hipMemcpyHostToDevice));
-        } else {
+        } else if (!L.direct()) {
             HIP_TRY(hipMemcpy(B->ws + L.off_dcm, L.dtab.data(), L.dtab.size() * sizeof(int32_t),
                               hipMemcpyHostToDevice));
             HIP_TRY(hipMemcpy(B->ws + L.off_base, L.tile_base.data(), L.tile_base.size() * sizeof(int32_t),
@@ -1381,7 +1368,7 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
                 L.tiles.nb = sh[3];
                 L.tiles.cc = cc;
                 if (build_layout(B) != SPL_OK) continue;
-                if (L.shared && 2 * cc <= dedisp_stage_rows(sh[3]) * sh[2]) continue;   // the same kernel for every cc
+                if ((L.shared || L.direct()) && 2 * cc <= dedisp_stage_rows(sh[3]) * sh[2]) continue;   // the same kernel for every cc
                 if (row_lds_bytes(L) > 160 * 1024 - 256) continue;
                 spl_status st = upload_tables(B);
                 if (st != SPL_OK) { result = st; break; }

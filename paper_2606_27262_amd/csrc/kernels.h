@@ -18,6 +18,9 @@ bool dedisp_shape_supported(int dw, int j, int nw, int sv, int nbuf);
 hipError_t prepare_dedisp(int dw, int j, int nw, int sv, int nbuf, size_t lds_bytes, int *blocks_per_cu);
 hipError_t launch_dedisp(int dw, int j, int nw, int sv, int nbuf, const DevBeam *beams, const DedispItem *items,
                          int item_lo, int item_hi, int *queue, int grid, size_t lds_bytes, hipStream_t s);
+// The shape whose kernel reads the samples where they are: it stages no rows, and chan_chunk
+// and lds_bytes mean nothing to it.
+constexpr bool dedisp_direct(int dw, int j, int nw) { return dw == 4 && j == 1 && nw == 4; }
 // The shared-row kernel; lds_bytes holds both row buffers.
 bool shared_shape_supported(const SharedShape &s);
 hipError_t prepare_dedisp_shared(const SharedShape &s, size_t lds_bytes, int *blocks_per_cu);

@@ -390,6 +390,202 @@ __global__ __launch_bounds__(64 * NW, 4) void k_dedisp(const DevBeam *__restrict
     }
 }
 
+// 16 trials x 256 samples without staging: every trial's samples are read where they are.
+// Workgroup = 16 wavefronts; wavefront w sums trials d0 + 4 (w & 3) ... + 3 over the channels
+// of its quarter w >> 2.  Lane l holds trial l >> 4 and the 16 samples from t0 + 16 (l & 15):
+// of a channel one 16-byte load from the dword below them, shifted into place with the next
+// lane's first dword (the last lane's is a load of its own, one address per trial).  The
+// quarters' sums meet in the LDS.  Bound by the loads: one 16-byte load from an address that
+// is no multiple of 4 takes as long as four dwords (60.8 us in place of 35.8 below).  Nothing
+// depends on the delays' spread, and the quarters give a plan of few tiles four times the
+// loads in flight.  1 beam of 256 channels x 128 trials x 8192 samples over 0-500: 71 us
+// staged in tiles of the same size, 36 us now; 64 trials x 1024 channels x 4096 samples 160
+// and 53; 4 x 34 billion sums 2.24 ms (long rows) and 1.58 ms, 35 adds a clock and CU.
+constexpr int kDirectGroup = 4;   // channels in flight while as many are summed (8 spill at 128 registers)
+typedef uint32_t u32x4_word __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i32x4_word __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) const u32x4_word gu32x4_word;
+typedef __attribute__((address_space(1))) const i32x4_word gi32x4_word;
+typedef __attribute__((address_space(1))) const int32_t gi32;
+
+__global__ __launch_bounds__(1024, 4) void k_dedisp_direct(const DevBeam *__restrict__ beams,
+                                                           const DedispItem *__restrict__ items, int item_lo,
+                                                           int item_hi, int *queue) {
+    __shared__ int32_t s_sum[4][4][3][4][64];   // trials of a wavefront, samples 4 j.., the other quarters'
+    __shared__ int s_item;
+    constexpr uint32_t kSelOdd = 0x0C030C01u;   // bytes 1, 3 -> 16-bit fields
+    constexpr int G = kDirectGroup;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int quad = __builtin_amdgcn_readfirstlane(wave_id() & 3), quarter = __builtin_amdgcn_readfirstlane(wave_id() >> 2);
+
+    int it = item_lo + blockIdx.x;
+    for (;;) {
+        if (queue) {
+            __syncthreads();
+            if (tid == 0) s_item = item_lo + atomicAdd(queue, 1);
+            __syncthreads();
+            it = __builtin_amdgcn_readfirstlane(s_item);
+        }
+        if (it >= item_hi) break;
+        const DedispItem item = items[it];
+        const DevBeam &B = beams[item.beam];
+        const int nch = B.nch, ndm = B.ndm, n_dd = B.n_dd;
+        const int64_t pitch = B.pitch;
+        const uint8_t *__restrict__ x = B.x;
+        const int d = item.d0 + 4 * quad + (lane >> 4), t = item.t0 + 16 * (lane & 15);
+        const gi32 *delays = (const gi32 *)B.delays + (size_t)min(d, ndm - 1) * nch;
+        // this quarter's channels; those whose loads could pass the end of the block (its last
+        // channel, in the last time tile) are read byte by byte
+        const int per = (nch + 4 * G - 1) / (4 * G) * G;
+        const int c_lo = min(nch, quarter * per), c_hi = min(nch, c_lo + per);
+        const int64_t past = (int64_t)item.t0 + 260 + (B.n_in - n_dd) - pitch;
+        const int c_safe = (int)max((int64_t)0, past > 0 ? nch - (past + pitch - 1) / pitch : (int64_t)nch);
+        const int c_wide = min(c_hi, max(c_lo, c_safe));
+
+        int32_t acc[16];
+        uint32_t aw[4], ao[4];   // sums of the dwords, of their bytes 1 and 3
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc[k] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) aw[j] = ao[j] = 0u;
+        auto load_delays = [&](int g, int32_t (&dl)[G]) {
+#pragma unroll
+            for (int k = 0; k < G; k += 4) {
+                const i32x4_word v = *(gi32x4_word *)(delays + c_lo + g * G + k);
+                dl[k] = v.x;
+                dl[k + 1] = v.y;
+                dl[k + 2] = v.z;
+                dl[k + 3] = v.w;
+            }
+        };
+        auto load_row = [&](const uint8_t *row, int32_t delay, u32x4 &v, uint32_t &end) {
+            const uint32_t o = (uint32_t)(item.t0 + (delay & ~3));
+            v = *(gu32x4_word *)((const gu8 *)row + o + 16 * (lane & 15));
+            end = *(gu32 *)((const gu8 *)row + o + 256);
+        };
+        auto load_samples = [&](int g, const int32_t (&dl)[G], u32x4 (&v)[G], uint32_t (&end)[G], uint32_t (&sh)[G]) {
+            const uint8_t *row = x + (size_t)(c_lo + g * G) * pitch;
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                load_row(row, dl[k], v[k], end[k]);
+                sh[k] = (uint32_t)dl[k];
+                row += pitch;
+            }
+        };
+        // the 16 samples of a lane from its dwords and the next one, the next lane's first
+        auto samples = [&](const u32x4 &v, uint32_t end, uint32_t sh) {
+            const uint32_t next = __builtin_amdgcn_update_dpp(end, v[0], 0x101, 0xF, 0xF, false);   // row_shl:1
+            u32x4 r;
+            r[0] = __builtin_amdgcn_alignbyte(v[1], v[0], sh);
+            r[1] = __builtin_amdgcn_alignbyte(v[2], v[1], sh);
+            r[2] = __builtin_amdgcn_alignbyte(v[3], v[2], sh);
+            r[3] = __builtin_amdgcn_alignbyte(next, v[3], sh);
+            return r;
+        };
+        auto add = [&](const u32x4 (&v)[G], const uint32_t (&end)[G], const uint32_t (&sh)[G]) {
+#pragma unroll
+            for (int k = 0; k < G; k += 2) {
+                const u32x4 p = samples(v[k], end[k], sh[k]), q = samples(v[k + 1], end[k + 1], sh[k + 1]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    aw[j] += p[j] + q[j];
+                    ao[j] += __builtin_amdgcn_perm(p[j], p[j], kSelOdd) + __builtin_amdgcn_perm(q[j], q[j], kSelOdd);
+                }
+            }
+        };
+        auto widen = [&]() {   // at most every 256 channels
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t even = aw[j] - (ao[j] << 8);
+                acc[4 * j + 0] += (int32_t)(even & 0xFFFFu);
+                acc[4 * j + 2] += (int32_t)(even >> 16);
+                acc[4 * j + 1] += (int32_t)(ao[j] & 0xFFFFu);
+                acc[4 * j + 3] += (int32_t)(ao[j] >> 16);
+                aw[j] = ao[j] = 0u;
+            }
+        };
+        const int n = (c_wide - c_lo) / G;
+        if (n > 0) {
+            int32_t da[G], db[G];
+            u32x4 va[G], vb[G];
+            uint32_t ea[G], eb[G], sa[G], sb[G];
+            load_delays(0, da);
+            load_delays(min(1, n - 1), db);
+            load_samples(0, da, va, ea, sa);
+            int g = 0;
+            for (; g + 2 < n; g += 2) {   // a group's delays are asked for before the samples of the one ahead of it
+                load_delays(g + 2, da);
+                load_samples(g + 1, db, vb, eb, sb);
+                add(va, ea, sa);
+                load_delays(min(g + 3, n - 1), db);
+                load_samples(g + 2, da, va, ea, sa);
+                add(vb, eb, sb);
+                if ((g + 2) % (256 / G) == 0) widen();
+            }
+            if (g + 1 < n) {
+                load_samples(g + 1, db, vb, eb, sb);
+                add(va, ea, sa);
+                add(vb, eb, sb);
+            } else {
+                add(va, ea, sa);
+            }
+            widen();
+        }
+        int c = c_lo + n * G;
+        if (c < c_wide) {   // fewer than G channels: the others' places hold zeros
+            u32x4 v[G];
+            int32_t dl[G];
+            uint32_t end[G], sh[G];
+#pragma unroll
+            for (int k = 0; k < G; ++k) dl[k] = delays[min(c + k, c_wide - 1)];
+#pragma unroll
+            for (int k = 0; k < G; ++k) load_row(x + (size_t)min(c + k, c_wide - 1) * pitch, dl[k], v[k], end[k]);
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                sh[k] = (uint32_t)dl[k];
+                if (c + k >= c_wide) v[k] = (u32x4)0, end[k] = 0;
+            }
+            add(v, end, sh);
+            widen();
+            c = c_wide;
+        }
+        for (; c < c_hi; ++c) {
+            const gu8 *row = (const gu8 *)(x + (size_t)c * pitch) + delays[c];
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                if (t + k < n_dd) acc[k] += row[t + k];
+        }
+
+        // the quarters' sums: quarter j ends with samples 4 j ... of every lane
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j != quarter)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s_sum[quad][j][(quarter - j - 1) & 3][e][lane] = acc[4 * j + e];
+        int32_t r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            r[e] = quarter < 2 ? (quarter == 0 ? acc[e] : acc[4 + e]) : (quarter == 2 ? acc[8 + e] : acc[12 + e]);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] += s_sum[quad][quarter][q][e][lane];
+        const int to = t + 4 * quarter;
+        if (d < ndm) {
+            int32_t *Xr = B.X + (size_t)d * B.xpitch;
+            if (to + 3 < n_dd) {
+                *(int4 *)(Xr + to) = make_int4(r[0], r[1], r[2], r[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (to + e < n_dd) Xr[to + e] = r[e];
+            }
+        }
+        if (!queue) break;
+    }
+}
+
 // ------------------------------------------------------- moments + thresholds
 // One workgroup per DM row: exact moments n, S1 = sum X, S2 = sum X^2 of every
 // segment of the owned samples, then mu, sigma and, for every width w, the smallest
@@ -1051,20 +1247,27 @@ __global__ void k_mu_sigma(const int64_t *n, const int64_t *s1, const int64_t *s
 
 template <int DW, int J, int NW, int SV, int NBUF>
 static hipError_t prepare_dedisp_t(size_t lds_bytes, int *blocks_per_cu) {
-    if (lds_bytes > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_dedisp<DW, J, NW, SV, NBUF>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
+    if constexpr (dedisp_direct(DW, J, NW)) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_dedisp_direct, 1024, 0);
+    } else {
+        if (lds_bytes > 64 * 1024) {
+            hipError_t e = hipFuncSetAttribute((const void *)k_dedisp<DW, J, NW, SV, NBUF>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+            if (e != hipSuccess) return e;
+        }
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_dedisp<DW, J, NW, SV, NBUF>, 64 * NW,
+                                                            lds_bytes);
     }
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_dedisp<DW, J, NW, SV, NBUF>, 64 * NW,
-                                                        lds_bytes);
 }
 
 template <int DW, int J, int NW, int SV, int NBUF>
 static hipError_t launch_dedisp_t(const DevBeam *beams, const DedispItem *items, int item_lo, int item_hi,
                                   int *queue, int grid, size_t lds_bytes, hipStream_t s) {
-    hipLaunchKernelGGL((k_dedisp<DW, J, NW, SV, NBUF>), dim3(grid), dim3(64 * NW), lds_bytes, s, beams, items,
-                       item_lo, item_hi, queue);
+    if constexpr (dedisp_direct(DW, J, NW))
+        hipLaunchKernelGGL(k_dedisp_direct, dim3(grid), dim3(1024), 0, s, beams, items, item_lo, item_hi, queue);
+    else
+        hipLaunchKernelGGL((k_dedisp<DW, J, NW, SV, NBUF>), dim3(grid), dim3(64 * NW), lds_bytes, s, beams, items,
+                           item_lo, item_hi, queue);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -1075,7 +1278,7 @@ static hipError_t launch_dedisp_t(const DevBeam *beams, const DedispItem *items,
 // per CU, so that no other workgroup sums while one stages.
 #define SPL_DEDISP_SHAPES(X)                                                                                 \
     X(2, 2, 8, 1, 1) X(4, 1, 4, 1, 1) X(4, 2, 4, 1, 1) X(4, 1, 8, 1, 1) X(4, 2, 8, 1, 1) X(8, 1, 4, 1, 1)   \
-    X(8, 1, 8, 1, 1) X(2, 2, 8, 2, 1) X(4, 1, 4, 2, 1) X(4, 1, 8, 2, 1) X(4, 2, 8, 2, 1) X(4, 1, 16, 1, 1)  \
+    X(8, 1, 8, 1, 1) X(2, 2, 8, 2, 1) X(4, 1, 8, 2, 1) X(4, 2, 8, 2, 1) X(4, 1, 16, 1, 1)                  \
     X(4, 2, 16, 1, 1) X(2, 2, 16, 1, 1) X(2, 2, 16, 2, 1) X(4, 1, 16, 1, 2) X(4, 2, 16, 1, 2)              \
     X(2, 2, 16, 1, 2) X(2, 2, 16, 2, 2)
 
