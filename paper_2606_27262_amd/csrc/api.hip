@@ -326,7 +326,7 @@ struct spl_batch {
 
 // Samples that a CU adds in a clock (of 64 lanes; 34 billion over 512 trials x 1024 channels):
 // rows staged in tiles of 32 trials 50, of 16 trials 40-44; read directly 35.
-static constexpr double kRowAddsPerClock = 50.0, kDirectAddsPerClock = 35.0;
+static constexpr double kRowAddsPerClock = 50.0, kRow16AddsPerClock = 42.0, kDirectAddsPerClock = 35.0;
 
 // Reserved bytes of a plan's offset table: room for the widest padding (64 trials).
 static size_t table_bytes(const spl_plan &p) {
@@ -424,29 +424,38 @@ static int widest_tile(const spl_plan &p, int td) {
     return widest;
 }
 
-// Default tiling without shared rows: 8 wavefronts of 4 (2) trials x 512 samples where the
-// plan gives them work items for the chip and a tile's rows are short enough to be staged by
-// one load a lane; else 16 trials x 256 samples, read where they are.  512 trials of 1024
-// channels over 4 x 16384 samples, whatever the spread of the delays: 1.58 ms read directly;
-// staged in tiles of 32 trials 1.12 ms with rows up to 1 KB and 1.56-1.83 ms with longer ones,
-// of 16 trials 1.27-1.40 and 2.09 ms.  With few work items the staged tiles leave CUs idle and
-// one workgroup's chunks take turns with their loads: 128 trials x 256 channels x 8192 samples
-// 36 us directly, 39-57 us staged; 64 trials x 1024 channels x 4096 samples 53 and 129-259 us.
-static Tiles default_row_tiles(const spl_plan &p) {
-    static const int shapes[][3] = {{4, 2, 8}, {2, 2, 8}};   // (trials/wave, groups, waves)
-    Tiles t;
+// Clocks that the chip needs for `beams` beams of a plan in tiles of td trials x tt samples, of
+// which a CU holds `held` at once and adds `rate` samples in a clock; per channel.
+static double tile_clocks(const spl_plan &p, int64_t beams, int td, int tt, int held, double rate) {
+    const int64_t n = beams * ((p.ndm + td - 1) / td) * ((p.n_dd + tt - 1) / tt);
+    return (double)((n + 256 * held - 1) / (256 * held)) * held * td * tt / rate;
+}
+
+// Default tiling without shared rows: 8 wavefronts of 4 (2) trials x 512 samples, two
+// workgroups on a CU, where a tile's rows are short enough to be staged by one load a lane; or
+// 16 trials x 256 samples, read where they are.  512 trials of 1024 channels over 4 x 16384
+// samples, whatever the spread of the delays: 1.58 ms read directly; staged in tiles of 32
+// trials 1.12 ms with rows up to 1 KB and 1.56-1.83 ms with longer ones, of 16 trials 1.27-1.40
+// and 2.09 ms.  With few work items the large tiles leave CUs idle (the rounds of tiles that the
+// chip takes are counted): 128 trials x 256 channels x 8192 samples 36 us directly, 39-57 us
+// staged; 64 trials x 1024 channels x 4096 samples 53 and 129-259 us.  *clocks: of one channel.
+static Tiles default_row_tiles(const spl_plan &p, int64_t beams, double *clocks) {
+    static const struct { int dw, j, nw; double rate; } shapes[] = {{4, 2, 8, kRowAddsPerClock}, {2, 2, 8, kRow16AddsPerClock}};
+    Tiles best;
+    best.dw = 4;
+    best.j = 1;
+    best.nw = 4;
+    *clocks = tile_clocks(p, beams, 16, 256, 1, kDirectAddsPerClock);
     for (const auto &sh : shapes) {
-        t.dw = sh[0];
-        t.j = sh[1];
-        t.nw = sh[2];
-        const int td = t.dw * t.nw;
-        const int64_t items = (int64_t)((p.ndm + td - 1) / td) * ((p.n_dd + 256 * t.j - 1) / (256 * t.j));
-        if (items >= 1024 && 256 * t.j + 32 + (int)align_up((size_t)widest_tile(p, td), 16) <= 1024) return t;
+        const int td = sh.dw * sh.nw, tt = 256 * sh.j;
+        const double c = tile_clocks(p, beams, td, tt, 2, sh.rate);
+        if (c >= *clocks || tt + 32 + (int)align_up((size_t)widest_tile(p, td), 16) > 1024) continue;
+        *clocks = c;
+        best.dw = sh.dw;
+        best.j = sh.j;
+        best.nw = sh.nw;
     }
-    t.dw = 4;
-    t.j = 1;
-    t.nw = 4;
-    return t;
+    return best;
 }
 
 // The 16-wavefront tiles where shared rows are modelled to take less time than the row
@@ -454,16 +463,12 @@ static Tiles default_row_tiles(const spl_plan &p) {
 // of one): a few large tiles leave CUs idle that many small ones would fill.
 static Tiles default_tiles(PlanLayout &L, int64_t beams) {
     const spl_plan &p = *L.plan;
-    const Tiles row = default_row_tiles(p);
+    double by_row = 0;
+    const Tiles row = default_row_tiles(p, beams, &by_row);
     if (!shared_tables(L)) return row;
-    auto rounds = [&](int td, int tt) {
-        const int64_t n = beams * ((p.ndm + td - 1) / td) * ((p.n_dd + tt - 1) / tt);
-        return (double)((n + 255) / 256);
-    };
-    const int td = row.dw * row.nw, tt = 256 * row.j, ts = 2 * L.sh.shape.half();
-    const double rate = row.nw == 4 ? kDirectAddsPerClock : kRowAddsPerClock;
-    const double by_row = rounds(td, tt) * ((double)td * tt * p.nch / rate);
-    const double by_sums = rounds(L.sh.shape.td(), ts) * (L.sh.clocks / L.sh.ntiles);
+    by_row *= p.nch;
+    const int td = L.sh.shape.td(), ts = 2 * L.sh.shape.half();
+    const double by_sums = tile_clocks(p, beams, td, ts, 1, td * ts / (L.sh.clocks / L.sh.ntiles));
     if (by_sums < by_row) {
         // (the row staging of the shape has to take the plan too: layout_plan's limits)
         static const int shapes[][2] = {{4, 2}, {2, 2}, {4, 1}};
