@@ -656,8 +656,8 @@ __global__ __launch_bounds__(kThreads) void k_thresholds(const DevBeam *__restri
 
 // ------------------------------------------------------------------- boxcars
 // Workgroup = one row chunk of kBoxTile owned samples.  The LDS holds the inclusive
-// prefix sums S[i] = X[t0] + ... + X[t0+i] at index i + 1 (index 0 holds 0) as wrapping
-// uint32; a window sum S[t+w-1] - S[t-1] is exact because every true sum is below 2^31.
+// prefix sums S[i] = X[t0] + ... + X[t0+i-1] as wrapping uint32; a window sum S[t+w] - S[t] is
+// exact because every true sum is below 2^31.
 // Thread k evaluates the 4 consecutive samples 4k + 1024q + {0..3} of each quarter q, so
 // its LDS reads are 16-byte vectors at consecutive addresses across lanes.  Hits of a
 // sample form a bitmask over the widths; only samples with hits evaluate the binary64
@@ -665,6 +665,12 @@ __global__ __launch_bounds__(kThreads) void k_thresholds(const DevBeam *__restri
 // workgroups take chunks in order from a ticket counter, publish their hit count, find
 // their offset by looking back over the counts and prefixes their predecessors
 // published (decoupled look-back), and write their hits from registers.
+// Bound by the chain of one chunk (ticket, loads, scan, widths, look-back; ~25 us with 5
+// workgroups on a CU): per sample and width three instructions, one barrier for all stripes
+// of the scan and polls that leave the status lines alone took 15 % off 2048 x 16384 samples
+// (173 -> 152 us) and 22 % off 128 x 8192 (25.8 -> 20.2).  Chunks of 8192 or 16384 samples in
+// as many more threads are slower (171, 184 us), as are look-backs over 256 or 512 chunks at
+// once (173, 179 us).
 __device__ __forceinline__ uint32_t lds_u32(const uint32_t *S, int i) { return S[i]; }
 
 // Look-back status words: flag in the top two bits, value below.
@@ -707,7 +713,7 @@ __device__ int64_t box_lookback(uint64_t *status, int idx, int64_t tot, int32_t 
                 if (lane == 0) atomicOr(stall, 1);
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_s_sleep(16);   // (polls of 64 clocks take the status lines from the publishers)
             continue;
         }
         excl += wave_sum<int64_t>(lane <= first ? (int64_t)(v & kStatValue) : 0);
@@ -723,12 +729,12 @@ __device__ int64_t box_lookback(uint64_t *status, int idx, int64_t tot, int32_t 
 // status: n_chunks + 1 zeroed words (the last is the ticket counter); offsets gets each
 // chunk's first hit index, n_total the range's hit count and stall the look-back's
 // give-up flag.
-__global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__ beams, int beam_lo,
+__global__ __launch_bounds__(kThreads, 5) void k_boxcar(const DevBeam *__restrict__ beams, int beam_lo,
                                                      int beam_hi, int chunk_lo, int n_chunks, int64_t *offsets,
                                                      Hit *hits, int32_t *hit_t, int64_t cap, uint64_t *status,
                                                      int64_t *n_total, int32_t *stall) {
     extern __shared__ __align__(16) uint32_t S[];
-    __shared__ uint32_t sh32[2][kThreads / 64];
+    __shared__ __align__(16) uint32_t sh32[5][kThreads / 64];   // kPre stripes' wavefront totals
     __shared__ int64_t sh64[kThreads / 64];
     __shared__ int64_t s_base;
     __shared__ int s_idx;
@@ -746,17 +752,15 @@ __global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__
     const int nvalid = min(M, B.n_dd - t0);
     const int32_t *Xr = B.X + (size_t)d * B.xpitch + t0;
 
-    // prefix sums in stripes of 1024 (4 consecutive per thread).  The global loads of up
-    // to kPre stripes are issued together; the wave totals of consecutive stripes
-    // alternate between two slots, so one barrier per stripe suffices (a slot is written
-    // again two stripes later, after every thread has passed the barrier in between).
+    // prefix sums in stripes of 1024 (4 consecutive per thread), S[i] the sum before i: the
+    // loads and the wavefronts' scans of up to kPre stripes run together, one barrier for all
+    // of them, and each thread's four entries are one 16-byte store.
     constexpr int kPre = 5;
     constexpr int kStripe = 4 * kThreads;
-    if (tid == 0) S[0] = 0u;
     uint32_t carry = 0;
-    int stripe = 0;
-    for (int s0 = 0; s0 < M; s0 += kPre * kStripe) {
-        uint32_t v[kPre][4];
+    int s0 = 0;
+    for (; s0 < M; s0 += kPre * kStripe) {
+        uint32_t v[kPre][4], x[kPre];
 #pragma unroll
         for (int k = 0; k < kPre; ++k) {
             // one unconditional 16-byte load per thread and stripe (no branch, so the
@@ -771,30 +775,29 @@ __global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__
             v[k][2] = i0 + 2 < nvalid ? q4.z : 0u;
             v[k][3] = i0 + 3 < nvalid ? q4.w : 0u;
         }
+        if (s0 > 0) __syncthreads();   // the totals before are read
 #pragma unroll
-        for (int k = 0; k < kPre; ++k, ++stripe) {
-            const int i0 = s0 + k * kStripe + 4 * tid;
-            if (s0 + k * kStripe >= M) break;   // uniform
+        for (int k = 0; k < kPre; ++k) {
             v[k][1] += v[k][0];
             v[k][2] += v[k][1];
             v[k][3] += v[k][2];
-            const uint32_t x = wave_inclusive_scan(v[k][3]);
-            uint32_t *tw = sh32[stripe & 1];
-            if (lane == 63) tw[wave] = x;
-            __syncthreads();
-            uint32_t pre = carry, tot = 0;
+            x[k] = wave_inclusive_scan(v[k][3]);
+            if (lane == 63) sh32[k][wave] = x[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPre; ++k) {
+            uint32_t pre = carry + x[k] - v[k][3];
 #pragma unroll
             for (int w = 0; w < kThreads / 64; ++w) {
-                if (w < wave) pre += tw[w];
-                tot += tw[w];
+                if (w < wave) pre += sh32[k][w];
+                carry += sh32[k][w];
             }
-            pre += x - v[k][3];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (i0 + e < M) S[i0 + e + 1] = pre + v[k][e];
-            carry += tot;
+            const int i0 = s0 + k * kStripe + 4 * tid;
+            if (i0 <= M) *(uint4 *)&S[i0] = make_uint4(pre, pre + v[k][0], pre + v[k][1], pre + v[k][2]);
         }
     }
+    if (tid == 0 && s0 <= M) S[s0] = carry;   // the entry after the last stripe
     __syncthreads();   // every prefix entry is written
 
     const int nw = B.nw, L = B.L, nseg = B.nseg;
@@ -806,38 +809,52 @@ __global__ __launch_bounds__(kThreads) void k_boxcar(const DevBeam *__restrict__
         for (int e = 0; e < 4; ++e) mask[q][e] = 0u;
 
     if (tend > t0) {
+        uint32_t lo[kQ][4];
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const uint4 l4 = *(const uint4 *)&S[1024 * q + 4 * tid];
+            lo[q][0] = l4.x; lo[q][1] = l4.y; lo[q][2] = l4.z; lo[q][3] = l4.w;
+        }
         // segments spanned by the chunk (usually one); thresholds of a segment are uniform
         for (int sg = t0 / L; sg <= (tend - 1) / L; ++sg) {
             const int s_lo = max(sg * L, t0) - t0, s_hi = min((sg + 1) * L, tend) - t0;
             const cint32 *Tp = as_const(B.T + ((size_t)d * nseg + sg) * nw);
+            // Sums and thresholds lie in [0, 2^31), so the sign of their difference says which is
+            // larger; it is shifted in from the right, width by width.
+            uint32_t below[kQ][4];
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                const int li = 1024 * q + 4 * tid;   // local index of the first of 4 samples
-                const uint4 lo = *(const uint4 *)&S[li];
-                const uint4 nx = *(const uint4 *)&S[li + 4];
-                const uint32_t s0[8] = {lo.x, lo.y, lo.z, lo.w, nx.x, nx.y, nx.z, nx.w};
-                for (int j = 0; j < nw; ++j) {
-                    const int w = B.widths[j];
-                    const int32_t T = Tp[j];
-                    uint32_t hw[4];
-                    if (w < 4) {
+            for (int q = 0; q < kQ; ++q)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) hw[e] = w == 1 ? s0[e + 1] : (w == 2 ? s0[e + 2] : s0[e + 3]);
-                    } else if ((w & 3) == 0) {
-                        const uint4 h = *(const uint4 *)&S[li + w];
-                        hw[0] = h.x; hw[1] = h.y; hw[2] = h.z; hw[3] = h.w;
-                    } else {
+                for (int e = 0; e < 4; ++e) below[q][e] = 0u;
+            for (int j = 0; j < nw; ++j) {
+                const int w = B.widths[j];
+                const uint32_t T = (uint32_t)Tp[j];
+                uint32_t hi[kQ][4];
+                if ((w & 3) == 0) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) hw[e] = lds_u32(S, li + w + e);
+                    for (int q = 0; q < kQ; ++q) {
+                        const uint4 h = *(const uint4 *)&S[1024 * q + 4 * tid + w];
+                        hi[q][0] = h.x; hi[q][1] = h.y; hi[q][2] = h.z; hi[q][3] = h.w;
                     }
+                } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int lt = li + e;
-                        const bool in = lt >= s_lo && lt < s_hi;
-                        if (in && (int32_t)(hw[e] - s0[e]) >= T) mask[q][e] |= 1u << j;
-                    }
+                    for (int q = 0; q < kQ; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) hi[q][e] = lds_u32(S, 1024 * q + 4 * tid + w + e);
                 }
+#pragma unroll
+                for (int q = 0; q < kQ; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        below[q][e] = __builtin_amdgcn_alignbit(below[q][e], hi[q][e] - lo[q][e] - T, 31);
             }
+#pragma unroll
+            for (int q = 0; q < kQ; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int lt = 1024 * q + 4 * tid + e;
+                    if (lt >= s_lo && lt < s_hi) mask[q][e] = __builtin_bitreverse32(~below[q][e]) >> (32 - nw);
+                }
         }
     }
     // hits are emitted in t order: quarter by quarter, thread by thread within a quarter.
