@@ -10,8 +10,8 @@
 // ~10^5-10^6 values per beam.
 //
 // The transition row is never formed.  The cumulative row sum up to state k is the mass
-// of [e_{n-1}, min(e_n, e_k - S)) over the mass of state n, monotone in k, so SAMPLE
-// mode binary-searches the first k where it exceeds u; ARGMAX compares the masses of the
+// of [e_{n-1}, min(e_n, e_k - S)) over the mass of state n, monotone in k: SAMPLE mode
+// takes the first k where it exceeds u; ARGMAX compares the masses of the
 // candidate states, successive differences of that cumulative mass.  Only states whose
 // shifted interval can meet state n are visited: from n + floor(S/w) - 1 to
 // n + floor(S/w) + 2 (w the state width), one state of slack on each side for rounding;

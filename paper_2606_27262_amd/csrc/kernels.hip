@@ -1,15 +1,16 @@
 // HIP kernels (gfx950) of the single-pulse search hot path.
 //
 //  k_dedisp      brute-force incoherent dedispersion (dedispersion section, Eq. (1)
-//                delays) into the int32 DM transform
+//                delays) into the int32 DM transform, rows staged in the LDS;
+//  k_dedisp_direct  the same without staging, for small or coarse plans
 //  k_thresholds  exact moments, mean / sigma per (DM row, segment) and the smallest
 //                boxcar sum reaching the S/N threshold per width (single pulse search)
 //  k_boxcar      boxcar filters via wrapping 32-bit prefix sums, threshold test, best
 //                width; writes the hits in (row, t) order, each tile's offset found by
 //                decoupled look-back over the tiles before it
+//  k_rows        row starts and block index of a hit list
 //  k_nms         peak filter over the sorted hit list (3x3, then 11x11 windows)
-//  k_scan_*      device-wide exclusive scans used for ordered compaction
-//  k_scatter     candidate records from the peak-filter survivors
+//  k_survivors   its survivors in order: the next list, or candidate records
 //
 // All integer work is exact; binary64 is evaluated with contraction disabled so
 // every rounding is the one written in the expression.
