@@ -37,7 +37,7 @@ hipError_t launch_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64
 hipError_t launch_boxcar_one_pass(const DevBeam *beams, int beam_lo, int beam_hi, int chunk_lo, int chunk_hi,
                                   int w_max, uint64_t *status, int64_t *offsets, Hit *hits, int32_t *hit_t,
                                   int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s);
-// kScanPerBlock-hit chunks of a list: the look-back words of launch_compact and launch_candidates are
+// Chunks of kScanPerBlock hits in a list (the shortest in use): the look-back words of launch_compact and launch_candidates are
 // one more (the ticket counter), and are cleared by the launch_rows call of the list before.
 int scan_blocks(int64_t n_max);
 // Row starts of the boxcar's hits, or of launch_compact's survivors (start_before, pos and

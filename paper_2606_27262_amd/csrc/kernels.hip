@@ -953,7 +953,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_boxcar(const DevBeam *__restric
 // What bounds small searches here is launches of 4-5 us and chains of loads in few
 // workgroups: with row starts, fill, mark, suffix pass, three-kernel scans and compactions as
 // launches of their own a search had 25 where it has 12 now.  1 beam of 256 channels x 128
-// trials x 8192 samples: filters and lists 101 us -> 78, whole search 182 -> 156 us.
+// trials x 8192 samples: filters and lists 101 us -> 59 (with the chunks of k_survivors below).
 __device__ __forceinline__ int64_t list_size(const int64_t *n, int64_t cap) { return min(*n, cap); }
 
 template <bool FIRST>
@@ -1011,11 +1011,13 @@ __global__ __launch_bounds__(kThreads) void k_rows(const DevBeam *__restrict__ b
 }
 
 // ------------------------------------------------------- survivors of a peak filter
-// The survivors (alive[p] != 0) in order, each chunk of kScanPerBlock hits placed by a
+// The survivors (alive[p] != 0) in order, each chunk of hits placed by a
 // look-back over the chunks before it (tickets follow the order in which workgroups take
-// them).  Chunks of 512 hits: 2 turns of loads a wavefront, and a few thousand hits meet
-// enough workgroups (4096: 14-18 us a launch on 1 beam of 128 trials, its 16 turns' dependent
-// loads one after another).  CANDS: as candidate records after `*base` earlier ones; else as the list that the
+// them).  Bound by the tickets (one address, 10-15 ns each) and, in a short list, by a chunk's
+// dependent loads: chunks of 512 hits, 2 turns a wavefront, while every chunk has its
+// workgroup (the others take no ticket), of 4096 in longer lists.  The two launches of 1 beam
+// of 128 trials 14 and 14 -> 6 and 4 us against a ticket for each of 1024 workgroups; 18
+// million hits 486 -> 169 us against chunks of 512.  CANDS: as candidate records after `*base` earlier ones; else as the list that the
 // later, wider filters see, with its packed times, and pos[p] the survivors before p.
 struct Survivors {
     const Hit *hits;
@@ -1043,23 +1045,23 @@ __device__ __forceinline__ void write_candidate(const DevBeam *__restrict__ beam
     *cand = c;
 }
 
-template <bool CANDS>
-__global__ __launch_bounds__(kThreads) void k_survivors(Survivors v, Hit *__restrict__ out, int32_t *__restrict__ hit_t,
-                                                        int64_t *__restrict__ pos, const DevBeam *__restrict__ beams,
-                                                        int beam_lo, int beam_hi, const int64_t *base,
-                                                        spl_candidate *cands, int64_t cand_cap) {
+template <bool CANDS, int TURNS>
+__device__ __forceinline__ void place_survivors(const Survivors &v, int64_t n, Hit *__restrict__ out,
+                                                int32_t *__restrict__ hit_t, int64_t *__restrict__ pos,
+                                                const DevBeam *__restrict__ beams, int beam_lo, int beam_hi,
+                                                const int64_t *base, spl_candidate *cands, int64_t cand_cap) {
     __shared__ int64_t s_idx, s_base;
     __shared__ int s_tot[kThreads / 64];
-    constexpr int kTurns = kScanPerBlock / kThreads;   // of 64 hits a wavefront
+    constexpr int kTurns = TURNS, kChunk = TURNS * kThreads;   // turns of 64 hits a wavefront
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    const int64_t n = list_size(v.n_hits, v.cap);
-    if (n == 0 && blockIdx.x == 0 && tid == 0) *v.n_out = 0;
-    for (;;) {
+    const int64_t n_chunks = (n + kChunk - 1) / kChunk;
+    if (blockIdx.x >= n_chunks) return;
+    do {
         __syncthreads();   // the chunk before is placed
         if (tid == 0) s_idx = (int64_t)atomicAdd((unsigned long long *)&v.status[v.ticket], 1ull);
         __syncthreads();
-        const int64_t idx = s_idx, p0 = idx * kScanPerBlock + wave * (kTurns * 64) + lane;
-        if (idx * kScanPerBlock >= n) break;   // uniform
+        const int64_t idx = s_idx, p0 = idx * kChunk + wave * (kTurns * 64) + lane;
+        if (idx * kChunk >= n) break;   // uniform
         uint64_t alive[kTurns];
         int mine = 0;
 #pragma unroll
@@ -1081,7 +1083,7 @@ __global__ __launch_bounds__(kThreads) void k_survivors(Survivors v, Hit *__rest
             const int64_t excl = box_lookback(v.status, (int)idx, tot, v.stall);
             if (lane == 0) {
                 s_base = excl;
-                if ((idx + 1) * kScanPerBlock >= n) *v.n_out = excl + tot;
+                if ((idx + 1) * kChunk >= n) *v.n_out = excl + tot;
             }
         }
         __syncthreads();
@@ -1103,7 +1105,20 @@ __global__ __launch_bounds__(kThreads) void k_survivors(Survivors v, Hit *__rest
             }
             first += __builtin_popcountll(alive[k]);
         }
-    }
+    } while (n_chunks > gridDim.x);   // (else a chunk each: no further ticket)
+}
+
+template <bool CANDS>
+__global__ __launch_bounds__(kThreads) void k_survivors(Survivors v, Hit *__restrict__ out, int32_t *__restrict__ hit_t,
+                                                        int64_t *__restrict__ pos, const DevBeam *__restrict__ beams,
+                                                        int beam_lo, int beam_hi, const int64_t *base,
+                                                        spl_candidate *cands, int64_t cand_cap) {
+    const int64_t n = list_size(v.n_hits, v.cap);
+    if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) *v.n_out = 0;
+    if (n <= (int64_t)kScanPerBlock * gridDim.x)
+        place_survivors<CANDS, kScanPerBlock / kThreads>(v, n, out, hit_t, pos, beams, beam_lo, beam_hi, base, cands, cand_cap);
+    else
+        place_survivors<CANDS, 16>(v, n, out, hit_t, pos, beams, beam_lo, beam_hi, base, cands, cand_cap);
 }
 
 // ---------------------------------------------------------------- peak filter

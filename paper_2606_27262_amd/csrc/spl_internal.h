@@ -11,7 +11,7 @@ constexpr int kMaxStencils = 4;
 constexpr int kBoxTile = 4096;        // owned samples per boxcar workgroup (multiple of 1024)
 constexpr int kThreads = 256;         // threads per workgroup of every kernel
 constexpr int kNmsBlockShift = 6;     // the peak filter indexes hit rows in blocks of 64 samples
-constexpr int kScanPerBlock = 512;    // hits per chunk of a list compaction
+constexpr int kScanPerBlock = 512;    // hits per chunk of a short list's compaction
 constexpr int kMaxWmax = 8192;
 constexpr int kMaxShapeGroups = 4;  // distinct row-staging tile shapes per batch
 constexpr int kMaxSharedShapes = 4; // shapes of the shared-row kernel (a group of each may join them)
