@@ -603,7 +603,10 @@ spl_status spl_debug_shared_delays(const spl_batch *batch, int32_t beam, int32_t
  * last pass, for parity tests: bytes [Nb][H/2][W/2][32] (Nb = max_batch rounded up to
  * 32; H x W the layer's input size: 64x256, 32x128, 16x64, 8x32), each the window
  * position (row-major 0..3) of the first maximum of ReLU(conv + bias), or 255 when that
- * maximum is 0 (no gradient flows through the window). */
+ * maximum is 0 (no gradient flows through the window).  Images past the ones given to the
+ * pass are zero images; after a scoring pass they are made by this call (and by
+ * spl_ranker_debug_fc_preact), which then waits for the device, so the view is to be taken
+ * after the pass that it shows. */
 spl_status spl_ranker_debug_pool_args(const spl_ranker *r, int32_t layer, const uint8_t **d_arg);
 
 /* Device view of the first fully connected layer's output before its bias, FP32

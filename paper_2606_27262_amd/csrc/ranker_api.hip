@@ -100,6 +100,7 @@ struct spl_ranker {
     size_t ws_bytes = 0;
     bool have_weights = false;
     int64_t step = 0;
+    mutable int fresh = 0;  // images that the last pass left in the per-pass buffers; the rest up to nb are an earlier pass's
     // persistent parts
     size_t off_master = 0, off_m = 0, off_v = 0, off_g = 0;
     size_t off_packed = 0, off_pack_idx = 0, off_gc = 0, off_gc_idx = 0;
@@ -231,18 +232,36 @@ hipError_t gemm(const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, 
     return launch_gemm(A, lda, B, ldb, C, ldc, M, N, K, splits, false, s);
 }
 
-// nb images of which n are given (the others zero).
-spl_status forward(spl_ranker *R, const uint16_t *snip, int n, int nb, hipStream_t s) {
+// Images first .. first + nb - 1 of the per-pass buffers, the first n of them from snip (the
+// others zero).
+spl_status forward(const spl_ranker *R, const uint16_t *snip, int n, int first, int nb, hipStream_t s) {
     const uint16_t *packed = R->at<uint16_t>(R->off_packed);
     const float *master = R->at<float>(R->off_master);
-    RK_TRY(launch_conv_first(snip, nb, n, kH[0], kW[0], packed + R->pk_wp[0], master + R->po.cb[0],
-                             R->at<uint16_t>(R->off_X[0]), R->at<uint8_t>(R->off_arg[0]), s));
+    uint16_t *X[kLayers];
+    uint8_t *arg[kLayers];
+    for (int k = 0; k < kLayers; ++k) {
+        const size_t pooled = (size_t)first * (kH[k] / 2) * (kW[k] / 2) * kCout;
+        X[k] = R->at<uint16_t>(R->off_X[k]) + pooled;
+        arg[k] = R->at<uint8_t>(R->off_arg[k]) + pooled;
+    }
+    RK_TRY(launch_conv_first(snip, nb, n, kH[0], kW[0], packed + R->pk_wp[0], master + R->po.cb[0], X[0], arg[0], s));
     for (int k = 1; k < kLayers; ++k)
-        RK_TRY(launch_conv_pool(R->at<uint16_t>(R->off_X[k - 1]), nb, kH[k], kW[k], packed + R->pk_wp[k],
-                                master + R->po.cb[k], R->at<uint16_t>(R->off_X[k]), R->at<uint8_t>(R->off_arg[k]),
-                                s));
-    RK_TRY(gemm(R->at<uint16_t>(R->off_X[3]), kFcIn, packed + R->pk_f1, kFcIn, R->at<float>(R->off_Hm), kFcHidden, nb,
-                kFcHidden, kFcIn, s));
+        RK_TRY(launch_conv_pool(X[k - 1], nb, kH[k], kW[k], packed + R->pk_wp[k], master + R->po.cb[k], X[k], arg[k], s));
+    RK_TRY(gemm(X[3], kFcIn, packed + R->pk_f1, kFcIn, R->at<float>(R->off_Hm) + (size_t)first * kFcHidden, kFcHidden,
+                nb, kFcHidden, kFcIn, s));
+    return SPL_OK;
+}
+
+// The images that a ragged scoring pass did not fill, as the zero images they stand for: only
+// the debug views show them, so they are made when one is asked for (or when the pass's
+// weights are about to go).
+spl_status complete_pass(const spl_ranker *R) {
+    if (R->fresh == R->nb) return SPL_OK;
+    RK_TRY(hipDeviceSynchronize());   // the pass may be under way on any stream
+    const spl_status st = forward(R, nullptr, 0, R->fresh, R->nb - R->fresh, nullptr);
+    if (st != SPL_OK) return st;
+    RK_TRY(hipDeviceSynchronize());
+    R->fresh = R->nb;
     return SPL_OK;
 }
 
@@ -334,6 +353,7 @@ extern "C" spl_status spl_ranker_set_workspace(spl_ranker *R, void *d_ws, size_t
     R->ws = (char *)d_ws;
     R->have_weights = false;
     R->step = 0;
+    R->fresh = R->nb;   // no pass yet
     RK_TRY(hipMemcpy(R->ws + R->off_pack_idx, R->pack_idx.data(), R->pack_idx.size() * 4, hipMemcpyHostToDevice));
     RK_TRY(hipMemcpy(R->ws + R->off_gc_idx, R->gc_idx.data(), R->gc_idx.size() * 4, hipMemcpyHostToDevice));
     return SPL_OK;
@@ -342,6 +362,7 @@ extern "C" spl_status spl_ranker_set_workspace(spl_ranker *R, void *d_ws, size_t
 extern "C" spl_status spl_ranker_set_weights(spl_ranker *R, const float *host_params) {
     if (!R || !host_params) return failf(SPL_E_INVALID_ARG, "NULL argument");
     if (!R->ws) return failf(SPL_E_INVALID_ARG, "spl_ranker_set_workspace was not called");
+    if (const spl_status st = complete_pass(R); st != SPL_OK) return st;
     const int64_t np = R->po.total;
     RK_TRY(hipMemcpy(R->ws + R->off_master, host_params, np * 4, hipMemcpyHostToDevice));
     RK_TRY(launch_zero_f32(R->at<float>(R->off_m), np, nullptr));
@@ -370,7 +391,8 @@ extern "C" spl_status spl_ranker_score(spl_ranker *R, const uint16_t *d_snip, in
     if (n < 0 || (n > 0 && (!d_snip || !d_logits))) return failf(SPL_E_INVALID_ARG, "bad snippet or logit buffer");
     for (int64_t i0 = 0; i0 < n; i0 += R->nb) {
         const int m = (int)std::min<int64_t>(R->nb, n - i0);
-        st = forward(R, d_snip + i0 * SPL_SNIPPET_ELEMS, m, m, stream);   // a ragged pass is not padded
+        R->fresh = m;   // a ragged pass is not padded
+        st = forward(R, d_snip + i0 * SPL_SNIPPET_ELEMS, m, 0, m, stream);
         if (st != SPL_OK) return st;
         const ParamOffsets &po = R->po;
         const float *master = R->at<float>(R->off_master);
@@ -386,7 +408,8 @@ extern "C" spl_status spl_ranker_backward(spl_ranker *R, const uint16_t *d_snip,
     if (st != SPL_OK) return st;
     if (n < 1 || n > R->o.max_batch) return failf(SPL_E_INVALID_ARG, "n must be in [1, max_batch]");
     if (!d_snip || !d_labels || !d_loss) return failf(SPL_E_INVALID_ARG, "NULL argument");
-    st = forward(R, d_snip, (int)n, R->nb, stream);
+    R->fresh = R->nb;
+    st = forward(R, d_snip, (int)n, 0, R->nb, stream);
     if (st != SPL_OK) return st;
     return backward(R, d_snip, (int)n, d_labels, d_loss, stream);
 }
@@ -418,6 +441,8 @@ extern "C" spl_status spl_ranker_debug_pool_args(const spl_ranker *R, int32_t la
     spl_status st = check_ready(R);
     if (st != SPL_OK) return st;
     if (layer < 0 || layer >= kLayers || !d_arg) return failf(SPL_E_INVALID_ARG, "bad layer or NULL argument");
+    st = complete_pass(R);
+    if (st != SPL_OK) return st;
     *d_arg = R->at<uint8_t>(R->off_arg[layer]);
     return SPL_OK;
 }
@@ -426,6 +451,8 @@ extern "C" spl_status spl_ranker_debug_fc_preact(const spl_ranker *R, const floa
     spl_status st = check_ready(R);
     if (st != SPL_OK) return st;
     if (!d_h) return failf(SPL_E_INVALID_ARG, "NULL argument");
+    st = complete_pass(R);
+    if (st != SPL_OK) return st;
     *d_h = R->at<float>(R->off_Hm);
     return SPL_OK;
 }
