@@ -300,7 +300,8 @@ spl_status spl_batch_moments(const spl_batch *batch, int32_t beam, const int64_t
  * (8,1,4) (8,1,8), and (4,1,16) (4,2,16) (2,2,16) with one or two buffers.
  * With 16 wavefronts, a plan whose trials share the delay patterns of adjacent channels
  * is summed by a kernel that forms those channels' sums once per tile (the same integers;
- * its tile extents and staging are its own, and the other fields take no effect). */
+ * its tile extents and staging are its own, and the other fields take no effect); a beam of
+ * such a plan whose block has a pitch of 2^28 bytes or more is summed by the direct kernel. */
 typedef struct spl_tiles {
     int32_t dm_per_wave;
     int32_t time_groups;

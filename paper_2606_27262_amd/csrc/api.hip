@@ -334,11 +334,13 @@ static size_t table_bytes(const spl_plan &p) {
 }
 
 // The plan's shared-row tables, built on first use; false when the plan's delays have too
-// little in common: a modelled tile must take fewer clocks than row staging needs.
+// little in common: a modelled tile must take fewer clocks than row staging needs.  (No row of
+// a block is shorter than n_in: such rows alone can be too long for the kernel.)
 static bool shared_tables(PlanLayout &L) {
     if (!L.shared_tried) {
         L.shared_tried = true;
         const spl_plan &p = *L.plan;
+        if (p.n_in > kSharedPitch - 16) return false;
         static const SharedShape shapes[] = {{4, 8, 8, 6}};
         double best = (double)p.ndm * p.nch / kRowAddsPerClock;   // clocks per output sample
         for (const SharedShape &s : shapes) {
@@ -923,6 +925,21 @@ struct StageTimer {
     }
 };
 
+// A beam whose plan shares rows, but whose block's rows lie further apart than the shared-row
+// kernel addresses.  Its samples are read where they are: that kernel needs none of the tables,
+// so they stay what they are for a search under way and for the next block.
+static bool wide_rows(const spl_batch *B, int b) {
+    return B->layouts[B->layout_of_beam[b]].shared && B->cur_pitch[b] >= kSharedPitch;
+}
+
+// Dedispersion of one beam, a workgroup per work item.
+static hipError_t launch_beam(const spl_batch *B, int b, const DevBeam *beams, const DedispItem *items, hipStream_t s) {
+    const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
+    if (wide_rows(B, b)) return launch_dedisp_beam(beams, b, L.plan->ndm, L.plan->n_dd, s);
+    const int lo = B->item_base[b], hi = lo + L.ntile_d * L.ntile_t;
+    return launch_one(L.tiles, L.shared, L.sh.shape, beams, items, lo, hi, nullptr, hi - lo, B->beam_lds[b], s);
+}
+
 // The launch sequence of one beam range [b_lo, b_hi).
 static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persistent, spl_candidate *cands,
                                 int64_t cand_cap, spl_run_stats *stats, hipStream_t s) {
@@ -947,18 +964,19 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
             const auto &G = B->groups[g];
             const int n = G.item_hi - G.item_lo;
             if (n <= 0) continue;
+            bool wide = false;
+            for (int b = b_lo; b < b_hi && G.shared; ++b) wide = wide || wide_rows(B, b);
+            if (wide) {
+                for (int b = b_lo; b < b_hi; ++b)
+                    if (G.holds(B->layouts[B->layout_of_beam[b]])) HIP_TRY(launch_beam(B, b, beams, items, s));
+                continue;
+            }
             const int grid = std::min(n, G.occ * 256);
             HIP_TRY(launch_one(G.tiles, G.shared, G.shape, beams, items, G.item_lo, G.item_hi, &run->queue[g], grid,
                                G.lds, s));
         }
     } else {
-        for (int b = b_lo; b < b_hi; ++b) {
-            const int lo = B->item_base[b];
-            const PlanLayout &L = B->layouts[B->layout_of_beam[b]];
-            const int hi = lo + L.ntile_d * L.ntile_t;
-            HIP_TRY(launch_one(L.tiles, L.shared, L.sh.shape, beams, items, lo, hi, nullptr, hi - lo, B->beam_lds[b],
-                               s));
-        }
+        for (int b = b_lo; b < b_hi; ++b) HIP_TRY(launch_beam(B, b, beams, items, s));
     }
     HIP_TRY(t_dd.stop());
     // 2. normaliser and integer thresholds
@@ -1048,22 +1066,6 @@ static spl_status check_run_args(const spl_batch *B, const uint8_t *const *d_blo
     return SPL_OK;
 }
 
-// The shared-row kernel addresses 16 rows by 32-bit offsets: a plan given a row pitch of
-// 2^28 bytes or more goes back to row staging, for good.
-static spl_status drop_shared_of_wide_rows(spl_batch *B, const int64_t *pitches) {
-    bool drop = false;
-    for (int b = 0; b < B->nb; ++b) {
-        PlanLayout &L = B->layouts[B->layout_of_beam[b]];
-        if (!L.shared || pitches[b] < ((int64_t)1 << 28)) continue;
-        L.sh = SharedTables{};
-        drop = true;
-    }
-    if (!drop) return SPL_OK;
-    spl_status st = build_layout(B);
-    if (st == SPL_OK && B->ws) st = upload_tables(B);
-    return st;
-}
-
 extern "C" spl_status spl_batch_run(spl_batch *B, const uint8_t *const *d_blocks, const int64_t *pitches,
                                     spl_candidate *d_cands, int64_t capacity, spl_run_stats *d_stats,
                                     hipStream_t stream) {
@@ -1073,16 +1075,16 @@ extern "C" spl_status spl_batch_run(spl_batch *B, const uint8_t *const *d_blocks
     if (!B->tables_uploaded) return fail(SPL_E_INVALID_ARG, "spl_batch_set_workspace was not called");
     spl_status vs = check_run_args(B, d_blocks, pitches, d_cands, capacity, d_stats);
     if (vs != SPL_OK) return vs;
-    vs = drop_shared_of_wide_rows(B, pitches);
-    if (vs != SPL_OK) return vs;
     bool changed = false;
     for (int b = 0; b < B->nb; ++b)
         if (d_blocks[b] != B->cur_x[b] || pitches[b] != B->cur_pitch[b]) changed = true;
     if (changed) {
         if (B->staging_pending) HIP_TRY(hipEventSynchronize(B->staging_done));
         for (int b = 0; b < B->nb; ++b) {
+            const bool was_wide = wide_rows(B, b);
             B->cur_x[b] = d_blocks[b];
             B->cur_pitch[b] = pitches[b];
+            if (wide_rows(B, b) != was_wide) B->g_cap = -1;   // another kernel: captured again below
             B->host_beams[b].x = d_blocks[b];
             B->host_beams[b].pitch = pitches[b];
         }
@@ -1149,8 +1151,6 @@ extern "C" spl_status spl_batch_run_static(spl_batch *B, const uint8_t *const *d
                                            hipStream_t stream) {
     if (!B || !d_blocks || !pitches || !d_stats) return fail(SPL_E_INVALID_ARG, "NULL argument");
     spl_status st = check_run_args(B, d_blocks, pitches, d_cands, capacity, d_stats);
-    if (st != SPL_OK) return st;
-    st = drop_shared_of_wide_rows(B, pitches);
     if (st != SPL_OK) return st;
     if (B->ws_bytes > kStaticScratchBytes)
         return fail(SPL_E_UNSUPPORTED, "the batch needs %zu workspace bytes, the static scratch holds %zu "
@@ -1327,7 +1327,6 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
         B->cur_x[b] = d_blocks[b];
         B->cur_pitch[b] = pitches[b];
     }
-    if (spl_status st = drop_shared_of_wide_rows(B, pitches); st != SPL_OK) return st;
     auto cache = read_cache(cache_path);
     constexpr int kTuneBeams = 4;
     // 16-wavefront tiles (64 trials) share each staged channel row among twice the trials;
@@ -1373,6 +1372,9 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
                 L.tiles.nb = sh[3];
                 L.tiles.cc = cc;
                 if (build_layout(B) != SPL_OK) continue;
+                bool wide = false;   // (the shared-row kernel is not launched on such rows)
+                for (int b = 0; b < B->nb; ++b) wide = wide || (B->layout_of_beam[b] == (int)li && wide_rows(B, b));
+                if (wide) continue;
                 if ((L.shared || L.direct()) && 2 * cc <= dedisp_stage_rows(sh[3]) * sh[2]) continue;   // the same kernel for every cc
                 if (row_lds_bytes(L) > 160 * 1024 - 256) continue;
                 spl_status st = upload_tables(B);

@@ -21,7 +21,12 @@ hipError_t launch_dedisp(int dw, int j, int nw, int sv, int nbuf, const DevBeam 
 // The shape whose kernel reads the samples where they are: it stages no rows, and chan_chunk
 // and lds_bytes mean nothing to it.
 constexpr bool dedisp_direct(int dw, int j, int nw) { return dw == 4 && j == 1 && nw == 4; }
-// The shared-row kernel; lds_bytes holds both row buffers.
+// The same kernel over one beam whatever its tiling, with no work items and no tables but the
+// delays; rows may lie any distance apart.
+hipError_t launch_dedisp_beam(const DevBeam *beams, int beam, int ndm, int n_dd, hipStream_t s);
+// The shared-row kernel, which addresses 16 rows by 32-bit offsets: rows lie less than kSharedPitch
+// bytes apart; lds_bytes holds both row buffers.
+constexpr int64_t kSharedPitch = (int64_t)1 << 28;
 bool shared_shape_supported(const SharedShape &s);
 hipError_t prepare_dedisp_shared(const SharedShape &s, size_t lds_bytes, int *blocks_per_cu);
 hipError_t launch_dedisp_shared(const SharedShape &s, const DevBeam *beams, const DedispItem *items, int item_lo,

@@ -411,7 +411,7 @@ typedef __attribute__((address_space(1))) const int32_t gi32;
 
 __global__ __launch_bounds__(1024, 4) void k_dedisp_direct(const DevBeam *__restrict__ beams,
                                                            const DedispItem *__restrict__ items, int item_lo,
-                                                           int item_hi, int *queue) {
+                                                           int item_hi, int *queue, int beam) {
     __shared__ int32_t s_sum[4][4][3][4][64];   // trials of a wavefront, samples 4 j.., the other quarters'
     __shared__ int s_item;
     constexpr uint32_t kSelOdd = 0x0C030C01u;   // bytes 1, 3 -> 16-bit fields
@@ -428,7 +428,15 @@ __global__ __launch_bounds__(1024, 4) void k_dedisp_direct(const DevBeam *__rest
             it = __builtin_amdgcn_readfirstlane(s_item);
         }
         if (it >= item_hi) break;
-        const DedispItem item = items[it];
+        DedispItem item;
+        if (items) {
+            item = items[it];
+        } else {   // the tiles of one beam, counted
+            const int across = (beams[beam].ndm + 15) / 16;
+            item.beam = beam;
+            item.d0 = 16 * (it % across);
+            item.t0 = 256 * (it / across);
+        }
         const DevBeam &B = beams[item.beam];
         const int nch = B.nch, ndm = B.ndm, n_dd = B.n_dd;
         const int64_t pitch = B.pitch;
@@ -583,7 +591,10 @@ __global__ __launch_bounds__(1024, 4) void k_dedisp_direct(const DevBeam *__rest
                     if (to + e < n_dd) Xr[to + e] = r[e];
             }
         }
-        if (!queue) break;
+        if (!queue) {
+            it += gridDim.x;
+            __syncthreads();   // the quarters' sums are read
+        }
     }
 }
 
@@ -1297,10 +1308,19 @@ template <int DW, int J, int NW, int SV, int NBUF>
 static hipError_t launch_dedisp_t(const DevBeam *beams, const DedispItem *items, int item_lo, int item_hi,
                                   int *queue, int grid, size_t lds_bytes, hipStream_t s) {
     if constexpr (dedisp_direct(DW, J, NW))
-        hipLaunchKernelGGL(k_dedisp_direct, dim3(grid), dim3(1024), 0, s, beams, items, item_lo, item_hi, queue);
+        hipLaunchKernelGGL(k_dedisp_direct, dim3(grid), dim3(1024), 0, s, beams, items, item_lo, item_hi, queue, 0);
     else
         hipLaunchKernelGGL((k_dedisp<DW, J, NW, SV, NBUF>), dim3(grid), dim3(64 * NW), lds_bytes, s, beams, items,
                            item_lo, item_hi, queue);
+    SPL_HIP_LAUNCH_CHECK();
+    return hipSuccess;
+}
+
+hipError_t launch_dedisp_beam(const DevBeam *beams, int beam, int ndm, int n_dd, hipStream_t s) {
+    const int64_t n = (int64_t)((ndm + 15) / 16) * ((n_dd + 255) / 256);
+    if (n < 1 || n > INT_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_dedisp_direct, dim3((unsigned)std::min<int64_t>(n, 1 << 20)), dim3(1024), 0, s, beams,
+                       (const DedispItem *)nullptr, 0, (int)n, (int *)nullptr, beam);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
