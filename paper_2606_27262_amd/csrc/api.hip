@@ -295,7 +295,7 @@ struct spl_batch {
     size_t off_beams = 0, off_items = 0;
     std::vector<size_t> off_X, off_S, off_mu, off_sigma, off_T;   // per beam
     size_t off_S_all = 0, bytes_S_all = 0;
-    size_t off_chunk_off = 0, off_list_status = 0, off_row_start = 0, off_box_status = 0;
+    size_t off_chunk_off = 0, off_row_start = 0, off_box_status = 0;
     size_t off_hits = 0, off_alive0 = 0, off_alive1 = 0, off_pos = 0, off_run = 0;
     size_t off_nms_blk = 0;   // block index of the hit rows [n_rows][nms_nblk] int32
     size_t off_hit_t = 0;     // the hits' times, packed int32 [hit_cap]
@@ -652,8 +652,7 @@ static spl_status build_layout(spl_batch *B) {
         B->off_T[b] = take((size_t)p.ndm * p.nseg * p.widths.size() * sizeof(int32_t));
     }
     B->off_chunk_off = take((size_t)B->n_chunks * sizeof(int64_t));
-    B->off_box_status = take(((size_t)B->n_chunks + nb) * sizeof(uint64_t));   // one ticket word per beam range
-    B->off_list_status = take((size_t)(scan_blocks(B->hit_cap) + 1) * sizeof(uint64_t));
+    B->off_box_status = take(((size_t)B->n_chunks + 1) * sizeof(uint64_t));   // the last: the ticket counter
     B->off_row_start = take((size_t)(B->n_rows + 1) * sizeof(int64_t));
     {
         int n_out_max = 1;
@@ -750,15 +749,19 @@ static void fill_host_beams(spl_batch *B) {
         std::memset(&d, 0, sizeof d);
         d.x = B->cur_x[b];
         d.pitch = B->cur_pitch[b];
-        d.dtab = (const int32_t *)(B->ws + L.off_dcm);
-        d.tile_base = (const int32_t *)(B->ws + L.off_base);
+        d.tables = (const uint8_t *)(B->ws + L.off_dcm);
         if (L.shared) {
-            d.shared = (const uint8_t *)(B->ws + L.off_dcm);
             d.sh_items = (int32_t)L.sh.off_items;
             d.sh_blocks = (int32_t)L.sh.off_blocks;
             d.sh_taps = (int32_t)L.sh.off_taps;
             d.sh_starts = (int32_t)L.sh.off_starts;
             d.sh_buffer = L.sh.buffer;
+        } else {
+            d.tile_base = (const int32_t *)(B->ws + L.off_base);
+            d.ndm_pad = L.ndm_pad;
+            d.chan_chunk = L.tiles.cc;
+            d.lds_quarter = L.quarter;
+            d.tile_dm = L.td;
         }
         d.delays = (const int32_t *)(B->ws + L.off_delays);
         d.X = (int32_t *)(B->ws + B->off_X[b]);
@@ -781,7 +784,6 @@ static void fill_host_beams(spl_batch *B) {
         d.n_in = p.n_in;
         d.nch = p.nch;
         d.ndm = p.ndm;
-        d.ndm_pad = L.ndm_pad;
         d.n_dd = p.n_dd;
         d.n_out = p.n_out;
         d.L = p.L;
@@ -791,9 +793,6 @@ static void fill_host_beams(spl_batch *B) {
         d.row_base = B->row_base[b];
         d.chunk_base = B->chunk_base[b];
         d.nchunk_t = (p.n_out + kBoxTile - 1) / kBoxTile;
-        d.chan_chunk = L.tiles.cc;
-        d.lds_quarter = L.quarter;
-        d.tile_dm = L.td;
         d.beam = b;
         d.w_max = p.w_max;
         d.nst = p.nst;
@@ -949,8 +948,8 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
     const int row_lo = B->row_base[b_lo], row_hi = B->row_base[b_hi];
     const int chunk_lo = B->chunk_base[b_lo], chunk_hi = B->chunk_base[b_hi];
     int64_t *chunk_off = (int64_t *)(B->ws + B->off_chunk_off) + chunk_lo;
-    uint64_t *list_status = (uint64_t *)(B->ws + B->off_list_status);
-    uint64_t *box_status = (uint64_t *)(B->ws + B->off_box_status) + chunk_lo + b_lo;
+    uint64_t *box_status = (uint64_t *)(B->ws + B->off_box_status) + chunk_lo;
+    uint64_t *box_ticket = (uint64_t *)(B->ws + B->off_box_status) + B->n_chunks;
     int64_t *row_start = (int64_t *)(B->ws + B->off_row_start) + row_lo;
     Hit *hits = (Hit *)(B->ws + B->off_hits);
     uint8_t *alive[2] = {(uint8_t *)(B->ws + B->off_alive0), (uint8_t *)(B->ws + B->off_alive1)};
@@ -992,12 +991,16 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
     }
     StageTimer t_bc(B, s, SPL_STAGE_BOXCAR);
     int32_t *hit_t = (int32_t *)(B->ws + B->off_hit_t);
-    HIP_TRY(launch_boxcar_one_pass(beams, b_lo, b_hi, chunk_lo, chunk_hi, w_max, box_status, chunk_off, hits, hit_t,
-                                   cap, &run->n_hits, &run->box_stall, s));
+    HIP_TRY(launch_boxcar_one_pass(beams, b_lo, b_hi, chunk_lo, chunk_hi, w_max, box_status, box_ticket, chunk_off, hits,
+                                   hit_t, cap, &run->n_hits, &run->box_stall, s));
     HIP_TRY(t_bc.stop());
     // 4. peak filters, then ordered compaction into candidate records
     StageTimer t_pk(B, s, SPL_STAGE_PEAKS);
     int32_t *blk = (int32_t *)(B->ws + B->off_nms_blk);
+    // The look-back words of the compaction that follows a list (8 bytes per kScanPerBlock hits
+    // and 8) lie in a buffer of the list's capacity that is free until then: the second filter's
+    // flags, and after the first compaction the hits that it read.
+    uint64_t *list_status = (uint64_t *)alive[1];
     if (max_nst)
         HIP_TRY(launch_rows_first(beams, b_lo, b_hi, row_lo, row_hi - row_lo, chunk_lo, chunk_off, &run->n_hits, cap,
                                   row_start, hit_t, blk, B->nms_nblk, list_status, s));
@@ -1015,6 +1018,7 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
             int64_t *surv_start = (int64_t *)(B->ws + B->off_surv_start) + row_lo;
             HIP_TRY(launch_compact(hits, &run->n_hits, cap, in, list_status, surv, hit_t, pos, &run->n_surv,
                                    &run->box_stall, s));
+            list_status = (uint64_t *)hits;
             HIP_TRY(launch_rows_survivors(row_hi - row_lo, row_start, pos, &run->n_hits, &run->n_surv, cap, surv_start,
                                           hit_t, blk, B->nms_nblk, list_status, s));
             fh = surv;
@@ -1028,7 +1032,7 @@ static spl_status enqueue_range(spl_batch *B, int b_lo, int b_hi, bool persisten
     }
     HIP_TRY(launch_candidates(beams, b_lo, b_hi, fh, fn, cap, in, list_status, &run->n_cand_total, &run->n_cand_beam,
                               &run->box_stall, cands, cand_cap, s));
-    HIP_TRY(launch_pass_end(run, stats, cap, max_nst, b_hi == B->nb, cand_cap, s));
+    HIP_TRY(launch_pass_end(run, box_ticket, stats, cap, max_nst, b_hi == B->nb, cand_cap, s));
     HIP_TRY(t_pk.stop());
     return SPL_OK;
 }
@@ -1038,7 +1042,7 @@ static spl_status enqueue_all(spl_batch *B, spl_candidate *cands, int64_t cap, s
     DevRun *run = (DevRun *)(B->ws + B->off_run);
     HIP_TRY(launch_clear((uint64_t *)run, (int64_t)(sizeof(DevRun) / 8), (uint64_t *)stats,
                          (int64_t)(sizeof(spl_run_stats) / 8), (uint64_t *)(B->ws + B->off_box_status),
-                         (int64_t)B->n_chunks + B->nb, s));
+                         (int64_t)B->n_chunks + 1, s));
     if (B->mode == SPL_MODE_PERSISTENT_GRAPH) {
         spl_status st = enqueue_range(B, 0, B->nb, true, cands, cap, stats, s);
         if (st != SPL_OK) return st;

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
         const DedispItem item = items[it];
         const DevBeam &B = beams[item.beam];
         const int t0 = item.t0, d0 = item.d0;
-        const uint8_t *tab = B.shared;
+        const uint8_t *tab = B.tables;
         const cint32 *tl = as_const((const int32_t *)tab) + 4 * (d0 / TD);
         const int buf_bytes = B.sh_buffer;
 

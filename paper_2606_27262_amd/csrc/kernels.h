@@ -36,12 +36,12 @@ hipError_t launch_thresholds(const DevBeam *beams, int beam_lo, int beam_hi, int
 // Zeroes up to three ranges of 8-byte words.
 hipError_t launch_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64_t *c, int64_t nc, hipStream_t s);
 // Boxcar hits of chunks [chunk_lo, chunk_hi) in one launch (decoupled look-back): status
-// holds chunk_hi - chunk_lo + 1 words, zero at the start, offsets gets each chunk's first
+// holds chunk_hi - chunk_lo words and ticket one, zero at the start, offsets gets each chunk's first
 // hit index, hit_t the hits' times, *n_total the range's hit count; *stall is set if a
 // look-back gave up.
 hipError_t launch_boxcar_one_pass(const DevBeam *beams, int beam_lo, int beam_hi, int chunk_lo, int chunk_hi,
-                                  int w_max, uint64_t *status, int64_t *offsets, Hit *hits, int32_t *hit_t,
-                                  int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s);
+                                  int w_max, uint64_t *status, uint64_t *ticket, int64_t *offsets, Hit *hits,
+                                  int32_t *hit_t, int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s);
 // Chunks of kScanPerBlock hits in a list (the shortest in use): the look-back words of launch_compact and launch_candidates are
 // one more (the ticket counter), and are cleared by the launch_rows call of the list before.
 int scan_blocks(int64_t n_max);
@@ -69,8 +69,8 @@ hipError_t launch_candidates(const DevBeam *beams, int beam_lo, int beam_hi, con
                              int64_t cap, const uint8_t *alive, uint64_t *status, const int64_t *base, int64_t *n_out,
                              int32_t *stall, spl_candidate *cands, int64_t cand_cap, hipStream_t s);
 // End of a beam range; last: also of the run's statistics.
-hipError_t launch_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, bool last, int64_t cand_cap,
-                           hipStream_t s);
+hipError_t launch_pass_end(DevRun *run, uint64_t *box_ticket, spl_run_stats *stats, int64_t hit_cap, int nst, bool last,
+                           int64_t cand_cap, hipStream_t s);
 hipError_t launch_checksum(const int32_t *X, int ndm, int xpitch, int n_dd, unsigned long long *out,
                            hipStream_t s);
 hipError_t launch_mu_sigma(const int64_t *n, const int64_t *s1, const int64_t *s2, int64_t count, double *mu,

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_dedisp(const DevBeam *__restrict
         const DevBeam &B = beams[item.beam];
         const int nch = B.nch, ndm_pad = B.ndm_pad, R = item.row_bytes, quarter = B.lds_quarter;
         const int t0 = item.t0, d0 = item.d0;
-        const int32_t *__restrict__ tab = B.dtab;
+        const int32_t *__restrict__ tab = (const int32_t *)B.tables;
         const int32_t *__restrict__ base = B.tile_base + (size_t)(d0 / B.tile_dm) * nch;
         const int64_t pitch = B.pitch;
         const uint8_t *__restrict__ x = B.x;
@@ -738,13 +738,13 @@ __device__ int64_t box_lookback(uint64_t *status, int idx, int64_t tot, int32_t 
     return excl;
 }
 
-// status: n_chunks + 1 zeroed words (the last is the ticket counter); offsets gets each
+// status, *ticket: n_chunks words and the ticket counter, zero; offsets gets each
 // chunk's first hit index, n_total the range's hit count and stall the look-back's
 // give-up flag.
 __global__ __launch_bounds__(kThreads, 5) void k_boxcar(const DevBeam *__restrict__ beams, int beam_lo,
                                                      int beam_hi, int chunk_lo, int n_chunks, int64_t *offsets,
                                                      Hit *hits, int32_t *hit_t, int64_t cap, uint64_t *status,
-                                                     int64_t *n_total, int32_t *stall) {
+                                                     uint64_t *ticket, int64_t *n_total, int32_t *stall) {
     extern __shared__ __align__(16) uint32_t S[];
     __shared__ __align__(16) uint32_t sh32[5][kThreads / 64];   // kPre stripes' wavefront totals
     __shared__ int64_t sh64[kThreads / 64];
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_boxcar(const DevBeam *__restric
     __shared__ int s_idx;
     constexpr int kQ = kBoxTile / 1024;   // quarters of 1024 samples
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    if (tid == 0) s_idx = (int)atomicAdd((unsigned long long *)&status[n_chunks], 1ull);
+    if (tid == 0) s_idx = (int)atomicAdd((unsigned long long *)ticket, 1ull);
     __syncthreads();
     const int idx = s_idx;   // tickets follow the order in which workgroups start
     const int g = chunk_lo + idx;
@@ -1245,10 +1245,12 @@ __global__ __launch_bounds__(kThreads) void k_all_hits(const DevBeam *__restrict
 }
 
 // End of the launch sequence of a beam range: fold the range's counts into the run
-// statistics; the next range's candidates go after this one's.  The last range's end
-// closes the statistics.
-__global__ void k_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, bool last, int64_t cand_cap) {
+// statistics; the next range's candidates go after this one's, and its boxcar chunks are
+// counted from 0 again.  The last range's end closes the statistics.
+__global__ void k_pass_end(DevRun *run, uint64_t *box_ticket, spl_run_stats *stats, int64_t hit_cap, int nst, bool last,
+                           int64_t cand_cap) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    *box_ticket = 0;
     stats->n_hits += run->n_hits;
     if (run->n_hits > hit_cap && stats->hit_overflow == 0) stats->hit_overflow = 1;
     if (run->box_stall) stats->hit_overflow = 2;
@@ -1379,14 +1381,14 @@ hipError_t launch_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64
 }
 
 hipError_t launch_boxcar_one_pass(const DevBeam *beams, int beam_lo, int beam_hi, int chunk_lo, int chunk_hi,
-                                  int w_max, uint64_t *status, int64_t *offsets, Hit *hits, int32_t *hit_t,
-                                  int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s) {
+                                  int w_max, uint64_t *status, uint64_t *ticket, int64_t *offsets, Hit *hits,
+                                  int32_t *hit_t, int64_t cap, int64_t *n_total, int32_t *stall, hipStream_t s) {
     const int n = chunk_hi - chunk_lo;
-    if (!status || !offsets || !hits || !hit_t || !n_total || !stall) return hipErrorInvalidValue;
+    if (!status || !ticket || !offsets || !hits || !hit_t || !n_total || !stall) return hipErrorInvalidValue;
     if (n <= 0) return launch_clear((uint64_t *)n_total, 1, nullptr, 0, nullptr, 0, s);
     const size_t lds = (size_t)(kBoxTile + w_max + 8) * sizeof(uint32_t);
     hipLaunchKernelGGL(k_boxcar, dim3(n), dim3(kThreads), lds, s, beams, beam_lo, beam_hi, chunk_lo, n, offsets,
-                       hits, hit_t, cap, status, n_total, stall);
+                       hits, hit_t, cap, status, ticket, n_total, stall);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -1461,9 +1463,9 @@ hipError_t launch_nms(const DevBeam *beams, int beam_lo, int beam_hi, int row_lo
     return hipSuccess;
 }
 
-hipError_t launch_pass_end(DevRun *run, spl_run_stats *stats, int64_t hit_cap, int nst, bool last, int64_t cand_cap,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, run, stats, hit_cap, nst, last, cand_cap);
+hipError_t launch_pass_end(DevRun *run, uint64_t *box_ticket, spl_run_stats *stats, int64_t hit_cap, int nst, bool last,
+                           int64_t cand_cap, hipStream_t s) {
+    hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(64), 0, s, run, box_ticket, stats, hit_cap, nst, last, cand_cap);
     SPL_HIP_LAUNCH_CHECK();
     return hipSuccess;
 }

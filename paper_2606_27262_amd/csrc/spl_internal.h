@@ -20,12 +20,24 @@ constexpr int kMaxSharedShapes = 4; // shapes of the shared-row kernel (a group 
 struct DevBeam {
     const uint8_t *x;        // block [nch][pitch]
     int64_t pitch;           // bytes
-    const int32_t *dtab;     // LDS byte offset of each delay from its staged row origin,
-                             // channel-major [nch][ndm_pad]:
-                             // ((s - b) & ~3) + (s & 3)*lds_quarter, b = tile_base & ~15
-    const int32_t *tile_base;// min delay over each DM tile [ndm_tiles][nch]
+    const uint8_t *tables;   // of the beam's dedispersion kernel: row staging, the LDS byte offset of each
+                             // delay from its staged row origin, int32 channel-major [nch][ndm_pad]:
+                             // ((s - b) & ~3) + (s & 3)*lds_quarter, b = tile_base & ~15;
+                             // shared rows, the blob of SharedTables
+    union {
+        struct {                        // row staging
+            const int32_t *tile_base;   // min delay over each DM tile [ndm_tiles][nch]
+            int32_t ndm_pad;
+            int32_t chan_chunk;         // channels staged in LDS per step (power of two <= 256)
+            int32_t lds_quarter;        // bytes per shifted copy of the staged rows in the LDS
+            int32_t tile_dm;            // DM trials per dedispersion tile
+        };
+        struct {                        // shared rows
+            int32_t sh_items, sh_blocks, sh_taps, sh_starts;   // byte offsets in the tables
+            int32_t sh_buffer;          // LDS bytes of one buffer of rows
+        };
+    };
     const int32_t *delays;   // delay table in samples [ndm][nch] (snippet extraction)
-    const uint8_t *shared;   // tables of k_dedisp_shared (then dtab and tile_base are not used)
     int32_t *X;              // DM transform [ndm][xpitch]
     int64_t *S1, *S2;        // [ndm][nseg]
     double *mu, *sigma;      // [ndm][nseg]
@@ -36,16 +48,11 @@ struct DevBeam {
     double fref, flo;        // highest and lowest channel centres (MHz)
     double tsamp;            // s
     int32_t n_in;            // samples per channel the block carries
-    int32_t nch, ndm, ndm_pad, n_dd, n_out, L, nseg, nw;
+    int32_t nch, ndm, n_dd, n_out, L, nseg, nw;
     int32_t xpitch;          // int32 elements per DM row
     int32_t row_base;        // global row index of (beam, d = 0)
     int32_t chunk_base;      // global boxcar chunk of (d = 0, k = 0)
     int32_t nchunk_t;        // boxcar chunks per row
-    int32_t chan_chunk;      // channels staged in LDS per step (power of two <= 256)
-    int32_t lds_quarter;     // bytes per shifted copy of the staged rows in the LDS
-    int32_t tile_dm;         // DM trials per dedispersion tile
-    int32_t sh_items, sh_blocks, sh_taps, sh_starts;   // byte offsets in `shared`
-    int32_t sh_buffer;       // LDS bytes of one buffer of shared rows
     int32_t beam;
     int32_t w_max;
     int32_t nst;             // peak filters of this beam's plan
