@@ -1597,8 +1597,12 @@ extern "C" spl_status spl_debug_shared_delays(const spl_batch *B, int32_t beam, 
     if (!B || !host_out || beam < 0 || beam >= B->nb) return fail(SPL_E_INVALID_ARG, "bad argument");
     const PlanLayout &L = B->layouts[B->layout_of_beam[beam]];
     if (!L.shared) return fail(SPL_E_UNSUPPORTED, "the beam's channels are staged one by one");
-    std::vector<int32_t> all;
-    decode_shared(L.sh, L.plan->nch, &all);
-    std::memcpy(host_out, all.data(), (size_t)L.plan->ndm * L.plan->nch * sizeof(int32_t));
+    try {
+        std::vector<int32_t> all;
+        decode_shared(L.sh, L.plan->nch, &all);
+        std::memcpy(host_out, all.data(), (size_t)L.plan->ndm * L.plan->nch * sizeof(int32_t));
+    } catch (const std::bad_alloc &) {
+        return fail(SPL_E_OOM, "host allocation failed");
+    }
     return SPL_OK;
 }

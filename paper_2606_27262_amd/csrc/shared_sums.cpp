@@ -244,10 +244,16 @@ void build_tile(const int32_t *delays, int stride, int ndm, int nch, const Share
     o->ok = true;
 }
 
-}  // namespace
+// Threads that are joined whatever ends the scope.
+struct Helpers {
+    std::vector<std::thread> threads;
+    ~Helpers() {
+        for (std::thread &t : threads) t.join();
+    }
+};
 
-bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, double max_clocks,
-                  SharedTables *out) {
+bool build(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, double max_clocks,
+           SharedTables *out) {
     const int td = sh.td(), ntiles = (ndm + td - 1) / td;
     if (td < 1 || td > kMaxTrials || nch < kSharedChans || nch > 65536 || ndm < 1) return false;
     std::vector<Tile> tiles(ntiles);
@@ -266,15 +272,17 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
         }
     };
     // a tile of the 4096-channel band takes 2.5 ms: helpers from a few tiles of such size on
-    std::vector<std::thread> helpers;
     const int64_t size = (int64_t)ntiles * td * nch;
     const int n_help = size < (1 << 18) ? 0 : std::min({7, ntiles - 1, (int)std::thread::hardware_concurrency() - 1});
-    try {
-        for (int i = 0; i < n_help; ++i) helpers.emplace_back(work);
-    } catch (const std::system_error &) {   // fewer helpers
+    {
+        Helpers helpers;
+        try {
+            for (int i = 0; i < n_help; ++i) helpers.threads.emplace_back(work);
+        } catch (const std::system_error &) {   // fewer helpers
+        } catch (const std::bad_alloc &) {
+        }
+        work();
     }
-    work();
-    for (std::thread &t : helpers) t.join();
 
     size_t n_items = 0, n_blocks = 0, n_taps = 0, n_starts = 0;
     SharedTables &t = *out;
@@ -326,6 +334,17 @@ bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_
         starts = std::copy(o.starts.begin(), o.starts.end(), starts);
     }
     return true;
+}
+
+}  // namespace
+
+bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape sh, size_t max_bytes, double max_clocks,
+                  SharedTables *out) {
+    try {
+        return build(delays, ndm, nch, sh, max_bytes, max_clocks, out);
+    } catch (const std::bad_alloc &) {   // (no exception leaves the C ABI: the plan goes without tables)
+        return false;
+    }
 }
 
 void decode_shared(const SharedTables &t, int nch, std::vector<int32_t> *out) {

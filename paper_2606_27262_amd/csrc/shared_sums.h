@@ -75,7 +75,7 @@ struct SharedTables {
 
 // Builds the tables for delays [ndm][nch] (rows past ndm repeat the last trial).  False
 // when nch is not in [16, 65536], a run of one channel does not fit the shape, the tables exceed
-// max_bytes, or their clocks are seen to exceed max_clocks by far.
+// max_bytes, their clocks are seen to exceed max_clocks by far, or memory runs out.
 bool build_shared(const int32_t *delays, int ndm, int nch, SharedShape shape, size_t max_bytes, double max_clocks,
                   SharedTables *out);
 
