@@ -334,8 +334,11 @@ spl_status spl_batch_stage_times(spl_batch *batch, double *ms, int64_t *count, i
  * given blocks (uint8 [nch][pitch] device blocks as for spl_batch_run) for every compiled
  * tile shape and staging depth that fits, check that each shape gives a bit-identical DM
  * transform (SPL_E_INTERNAL otherwise), and keep the fastest.  Results are cached in the
- * text file cache_path (NULL: no cache), one line per plan signature (sizes and a hash of
- * the delay table); a cached plan is not re-timed unless flags has SPL_TUNE_FORCE.
+ * text file cache_path (NULL: no cache), one line per plan signature (sizes, a hash of the
+ * delay table and a number of the kernels that were timed: lines of other kernels are kept but
+ * not used); a cached plan is not re-timed unless flags has SPL_TUNE_FORCE.  The shared-row
+ * kernel and the direct one take no chan_chunk and are timed once, the former under the tiling
+ * that a new batch would have.
  * Synchronous on `stream`; overwrites the batch's intermediate results and uses only the
  * attached workspace (which is sized for every tiling).
  */

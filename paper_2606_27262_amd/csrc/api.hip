@@ -460,6 +460,22 @@ static Tiles default_row_tiles(const spl_plan &p, int64_t beams, double *clocks)
     return best;
 }
 
+// The tiling that names the shared-row kernel for a plan: the first of these 16-wavefront shapes
+// whose row staging takes the plan too (layout_plan's limits).
+static bool shared_tiles(const spl_plan &p, Tiles *out) {
+    static const int shapes[][2] = {{4, 2}, {2, 2}, {4, 1}};
+    for (const auto &sh : shapes) {
+        const int bytes = 256 * sh[1] + 32 + (int)align_up((size_t)widest_tile(p, 16 * sh[0]), 16);
+        if (bytes > 2048 || !dedisp_shape_supported(sh[0], sh[1], 16, bytes <= 1024 ? 1 : 2, 1)) continue;
+        *out = Tiles{};
+        out->dw = sh[0];
+        out->j = sh[1];
+        out->nw = 16;
+        return true;
+    }
+    return false;
+}
+
 // The 16-wavefront tiles where shared rows are modelled to take less time than the row
 // staging of the tiles above on the whole chip (tiles per CU, rounded up, times the clocks
 // of one): a few large tiles leave CUs idle that many small ones would fill.
@@ -471,20 +487,8 @@ static Tiles default_tiles(PlanLayout &L, int64_t beams) {
     by_row *= p.nch;
     const int td = L.sh.shape.td(), ts = 2 * L.sh.shape.half();
     const double by_sums = tile_clocks(p, beams, td, ts, 1, td * ts / (L.sh.clocks / L.sh.ntiles));
-    if (by_sums < by_row) {
-        // (the row staging of the shape has to take the plan too: layout_plan's limits)
-        static const int shapes[][2] = {{4, 2}, {2, 2}, {4, 1}};
-        for (const auto &sh : shapes) {
-            const int bytes = 256 * sh[1] + 32 + (int)align_up((size_t)widest_tile(p, 16 * sh[0]), 16);
-            if (bytes > 2048 || !dedisp_shape_supported(sh[0], sh[1], 16, bytes <= 1024 ? 1 : 2, 1)) continue;
-            Tiles t;
-            t.dw = sh[0];
-            t.j = sh[1];
-            t.nw = 16;
-            return t;
-        }
-    }
-    return row;
+    Tiles sums;
+    return by_sums < by_row && shared_tiles(p, &sums) ? sums : row;
 }
 
 // Channels per staging step: the largest power of two <= 256 whose four shifted copies
@@ -1263,12 +1267,14 @@ uint64_t fnv64(const void *p, size_t n, uint64_t h = 1469598103934665603ull) {
     return h;
 }
 
-// Everything the dedispersion kernel's speed depends on: sizes and the delay table.
+// Everything the dedispersion kernel's speed depends on: the kernels behind the tile shapes (a
+// cached choice is a measurement of them), sizes and the delay table.
+constexpr int kTunedKernels = 2;   // 1 (not written): every shape staged rows
 std::string plan_signature(const spl_plan &p) {
     uint64_t h = fnv64(p.delays.data(), p.delays.size() * sizeof(int32_t));
     char buf[160];
-    snprintf(buf, sizeof buf, "nch%d-ndm%d-nout%d-ndd%d-d%016llx", p.nch, p.ndm, p.n_out, p.n_dd,
-             (unsigned long long)h);
+    snprintf(buf, sizeof buf, "nch%d-ndm%d-nout%d-ndd%d-d%016llx-k%d", p.nch, p.ndm, p.n_out, p.n_dd,
+             (unsigned long long)h, kTunedKernels);
     return buf;
 }
 
@@ -1366,6 +1372,8 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
         best.ms = 1e300;
         bool have_ref = false;
         unsigned long long ref = 0;
+        Tiles sums;   // the shared-row kernel is timed under one name only
+        const bool named = shared_tiles(*B->layouts[li].plan, &sums);
         for (const auto &sh : shapes) {
             for (int cc = 2; cc <= dedisp_stage_rows(sh[3]) * sh[2]; cc *= 2) {
                 PlanLayout &L = B->layouts[li];
@@ -1376,10 +1384,15 @@ extern "C" spl_status spl_autotune(spl_batch *B, const uint8_t *const *d_blocks,
                 L.tiles.nb = sh[3];
                 L.tiles.cc = cc;
                 if (build_layout(B) != SPL_OK) continue;
-                bool wide = false;   // (the shared-row kernel is not launched on such rows)
-                for (int b = 0; b < B->nb; ++b) wide = wide || (B->layout_of_beam[b] == (int)li && wide_rows(B, b));
-                if (wide) continue;
-                if ((L.shared || L.direct()) && 2 * cc <= dedisp_stage_rows(sh[3]) * sh[2]) continue;   // the same kernel for every cc
+                if (L.shared || L.direct()) {   // the same kernel for every chunk: timed once, with the default one
+                    if (cc > 2) break;
+                    if (L.shared && !(named && L.tiles.dw == sums.dw && L.tiles.j == sums.j && L.tiles.nb == sums.nb)) break;
+                    bool wide = false;   // (the shared-row kernel is not launched on such rows)
+                    for (int b = 0; b < B->nb; ++b) wide = wide || (B->layout_of_beam[b] == (int)li && wide_rows(B, b));
+                    if (wide) break;
+                    L.tiles.cc = 0;
+                    if (build_layout(B) != SPL_OK) break;
+                }
                 if (row_lds_bytes(L) > 160 * 1024 - 256) continue;
                 spl_status st = upload_tables(B);
                 if (st != SPL_OK) { result = st; break; }
