@@ -341,17 +341,11 @@ static bool shared_tables(PlanLayout &L) {
         L.shared_tried = true;
         const spl_plan &p = *L.plan;
         if (p.n_in > kSharedPitch - 16) return false;
-        static const SharedShape shapes[] = {{4, 8, 8, 6}};
-        double best = (double)p.ndm * p.nch / kRowAddsPerClock;   // clocks per output sample
-        for (const SharedShape &s : shapes) {
-            SharedTables t;
-            if (!build_shared(p.delays.data(), p.ndm, p.nch, s, table_bytes(p), best * (2 * s.half()), &t)) continue;
-            const double c = t.clocks / (2 * s.half());
-            if (c < best) {
-                best = c;
-                L.sh = std::move(t);
-            }
-        }
+        const SharedShape shape{4, 8, 8, 6};
+        const double by_row = (double)p.ndm * p.nch / kRowAddsPerClock * (2 * shape.half());   // clocks of a time tile
+        SharedTables t;
+        if (build_shared(p.delays.data(), p.ndm, p.nch, shape, table_bytes(p), by_row, &t) && t.clocks < by_row)
+            L.sh = std::move(t);
     }
     return L.sh.ntiles > 0;
 }

@@ -406,14 +406,6 @@ __global__ __launch_bounds__(64 * (NP + 8)) void k_dedisp_shared(const DevBeam *
 // (staging wavefronts, trials per summing wavefront, packed dwords per lane and trial, groups per item, of raw samples held)
 #define SPL_SHARED_SHAPES(X) X(4, 8, 8, 6, 6)
 
-bool shared_shape_supported(const SharedShape &s) {
-#define SPL_X(a, b, c, d, e) \
-    if (s.np == a && s.dw == b && s.m == c && s.gp == d) return true;
-    SPL_SHARED_SHAPES(SPL_X)
-#undef SPL_X
-    return false;
-}
-
 template <int NP, int DW, int M, int GP, int RS>
 static hipError_t prepare_t(size_t lds_bytes, int *blocks_per_cu) {
     hipError_t err = hipFuncSetAttribute((const void *)k_dedisp_shared<NP, DW, M, GP, RS>,

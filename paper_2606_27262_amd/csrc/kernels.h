@@ -27,7 +27,6 @@ hipError_t launch_dedisp_beam(const DevBeam *beams, int beam, int ndm, int n_dd,
 // The shared-row kernel, which addresses 16 rows by 32-bit offsets: rows lie less than kSharedPitch
 // bytes apart; lds_bytes holds both row buffers.
 constexpr int64_t kSharedPitch = (int64_t)1 << 28;
-bool shared_shape_supported(const SharedShape &s);
 hipError_t prepare_dedisp_shared(const SharedShape &s, size_t lds_bytes, int *blocks_per_cu);
 hipError_t launch_dedisp_shared(const SharedShape &s, const DevBeam *beams, const DedispItem *items, int item_lo,
                                 int item_hi, int *queue, int grid, size_t lds_bytes, hipStream_t stream);

@@ -48,7 +48,7 @@ struct SharedItem {
     int32_t row_bytes;  // LDS bytes of a row
     int32_t c0;         // channels c0 .. c0 + 15 are read
     int32_t last;       // 1: the chunk's last round
-    int32_t reserved[2];
+    int32_t pad[2];     // 8 words: lane l & 7 of a staging wavefront loads word l
 };
 // A summing wavefront's block of a chunk (kSharedBlock int32, read lane by lane): runs |
 // channels << 8 (where the 16-bit fields' high bytes move on after the chunk: the channels

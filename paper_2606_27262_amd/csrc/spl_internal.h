@@ -14,7 +14,7 @@ constexpr int kNmsBlockShift = 6;     // the peak filter indexes hit rows in blo
 constexpr int kScanPerBlock = 512;    // hits per chunk of a short list's compaction
 constexpr int kMaxWmax = 8192;
 constexpr int kMaxShapeGroups = 4;  // distinct row-staging tile shapes per batch
-constexpr int kMaxSharedShapes = 4; // shapes of the shared-row kernel (a group of each may join them)
+constexpr int kMaxSharedShapes = 1; // compiled shapes of the shared-row kernel (a group of it may join them)
 
 // One beam of a batch, resident in the workspace.
 struct DevBeam {
