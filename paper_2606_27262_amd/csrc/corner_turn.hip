@@ -5,8 +5,8 @@
 // A workgroup moves a tile of 128 samples x 128 channels through the LDS: 16-byte global
 // loads along channels (eight threads read a sample's 128 bytes), then each thread takes
 // 16 consecutive samples of four channels as dwords, transposes them 4 x 4 bytes at a time
-// and writes four 16-byte pieces (byte by byte from the LDS, a 4096 x 26305 block took 38.3 us, now
-// 34.2); eight neighbouring threads cover a row's 128 samples, so reads and writes both move
+// and writes four 16-byte pieces (byte by byte from the LDS, a 4096 x 26305 block that lay in the
+// last-level cache took 38.3 us, now 34.2; from HBM it takes 51.6 us either way); eight neighbouring threads cover a row's 128 samples, so reads and writes both move
 // 128-byte pieces.  (Measured on a 4096 x 26305 block against 64 x 256, 128 x 256,
 // 64 x 512 and 256 x 128 tiles: the fastest, 73 % of a plain device copy's rate.)  The
 // LDS row stride of 132 bytes spreads a wave's gathers over the banks (2-way at most).

@@ -6,7 +6,7 @@
 // One wave per (window, channel) row, its lanes on 64 consecutive samples at a time, so
 // the byte loads and stores and the FP32/u32 window loads are coalesced; zero signal
 // (the padding of narrow bursts) costs one load.  The work is
-// binary64 arithmetic (a few erfc per sample), not memory: a burst's window holds
+// binary64 arithmetic (an erfc per sample), not memory: a burst's window holds
 // ~10^5-10^6 values per beam.
 //
 // The transition row is never formed.  The cumulative row sum up to state k is the mass

@@ -72,7 +72,10 @@ __global__ void k_clear(uint64_t *a, int64_t na, uint64_t *b, int64_t nb, uint64
 // 8-wavefront tiles of 256 x 2 samples took 131 and 145, and one workgroup a CU then
 // neither staged nor summed while it waited at its barriers (two beams of the 2048-channel
 // 300-500 MHz band: 12.1 ms in this kernel, 11.4 with fewer sums' instructions, 7.2 with
-// two workgroups a CU).  The LDS loads of the next
+// two workgroups a CU).  Of the shapes that would take more, (4,2,8) then spills 3 registers,
+// (4,2,8) with two vectors a row 14 and (8,1,8) 1, and all are faster for it: 4 x 512 trials x
+// 1024 channels x 16384 samples take (4,2,8) 0.99 ms (1.45 unbounded), with long rows 1.55
+// (2.07), (8,1,8) 1.18 (1.73), (8,1,4) 1.47 (1.55), (4,2,4) 1.26 (1.35).  The LDS loads of the next
 // channel are in flight while the current one is summed, and the global loads of the
 // next chunk while the current chunk is summed.
 // SV: 16-byte input vectors staged per lane and row (rows of up to 1024*SV bytes).
@@ -667,7 +670,7 @@ __global__ __launch_bounds__(kThreads) void k_thresholds(const DevBeam *__restri
 }
 
 // ------------------------------------------------------------------- boxcars
-// Workgroup = one row chunk of kBoxTile owned samples.  The LDS holds the inclusive
+// Workgroup = one row chunk of kBoxTile owned samples.  The LDS holds the exclusive
 // prefix sums S[i] = X[t0] + ... + X[t0+i-1] as wrapping uint32; a window sum S[t+w] - S[t] is
 // exact because every true sum is below 2^31.
 // Thread k evaluates the 4 consecutive samples 4k + 1024q + {0..3} of each quarter q, so
@@ -689,8 +692,9 @@ __device__ __forceinline__ uint32_t lds_u32(const uint32_t *S, int i) { return S
 constexpr uint64_t kStatAggregate = 1ull << 62;   // the chunk's own hit count
 constexpr uint64_t kStatInclusive = 2ull << 62;   // hits of every chunk up to and including it
 constexpr uint64_t kStatValue = (1ull << 62) - 1;
-constexpr int kLookbackPolls = 1 << 16;           // gives up (and reports it) after this many polls:
-                                                  // over 60 ms, against ~25 us per chunk
+constexpr int kLookbackPolls = 1 << 16;           // gives up (and reports it) after this many polls: each
+                                                  // sleeps 16 x 64 clocks, 28 ms together without
+                                                  // their loads, against ~25 us per chunk
 
 // The hit count tot of chunk idx, published as soon as it is known (chunk 0's count is
 // its inclusive prefix).
@@ -1028,8 +1032,9 @@ __global__ __launch_bounds__(kThreads) void k_rows(const DevBeam *__restrict__ b
 // dependent loads: chunks of 512 hits, 2 turns a wavefront, while every chunk has its
 // workgroup (the others take no ticket), of 4096 in longer lists.  The two launches of 1 beam
 // of 128 trials 14 and 14 -> 6 and 4 us against a ticket for each of 1024 workgroups; 18
-// million hits 486 -> 169 us against chunks of 512.  CANDS: as candidate records after `*base` earlier ones; else as the list that the
-// later, wider filters see, with its packed times, and pos[p] the survivors before p.
+// million hits 486 -> 169 us against chunks of 512.  CANDS: as candidate records after `*base`
+// earlier ones; else as the list that the later, wider filters see, with its packed times, and
+// pos[p] the survivors before p.
 struct Survivors {
     const Hit *hits;
     const int64_t *n_hits;

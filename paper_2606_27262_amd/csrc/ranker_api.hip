@@ -57,8 +57,8 @@ constexpr int kW[kLayers] = {256, 128, 64, 32};
 constexpr int kCin[kLayers] = {2, 32, 32, 32};
 constexpr int kKp[kLayers] = {32, 288, 288, 288};
 constexpr int kFcIn = 2048, kFcHidden = 64;
-// workgroups (and partial sums) of a weight-gradient pass: the buffer holds
-// kWgradParts of a 32-channel layer, the first layer (a 32 x 32 result) up to kWgradPartsFirst in the same buffer
+// workgroups (and partial sums) of a weight-gradient pass: the buffer holds kWgradParts of a
+// 32-channel layer; the first layer (a 32 x 32 result) has up to kWgradPartsFirst in it
 constexpr int kWgradParts = 2048;
 constexpr int kWgradPartsFirst = kWgradParts * 9;
 // partial sums of a 32-channel layer, 36 KB each to write and to sum: two workgroups a CU
@@ -288,8 +288,8 @@ spl_status backward(spl_ranker *R, const uint16_t *snip, int n, const float *lab
         const int64_t P = R->P(k);
         const uint16_t *in = k == 0 ? snip : R->at<uint16_t>(R->off_X[k - 1]);
         const uint8_t *arg = R->at<uint8_t>(R->off_arg[k]);
-        // first layer: about 16 slabs of 32 pixels per wavefront; the others: one
-        // workgroup per slab up to kWgradGroups
+        // first layer: 8 slabs of 64 pixels per wavefront; the others: one workgroup per
+        // slab of 32 up to kWgradGroups
         const int parts = (int)std::max<int64_t>(
             1, std::min<int64_t>(k == 0 ? kWgradPartsFirst : kWgradGroups, k == 0 ? P / 32 / 64 : P / 32));
         if (k == 0) {
