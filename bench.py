@@ -283,6 +283,33 @@ def counter_traffic(workload, tiles):
     return {"fetch_bytes": int(m.group(7)), "write_bytes": int(m.group(8))}
 
 
+def counted_lds_clocks(workload, tiles):
+    """Clocks in which a CU's LDS served the dedispersion launch, summed over the CUs
+    (SQ_LDS_IDX_ACTIVE), from the committed counter summary of this workload; None under
+    the conditions of counter_traffic."""
+    import re
+    path = os.path.join(ROOT, "profiles", f"dedisp_{workload}_sq_counters.md")
+    if counter_traffic(workload, tiles) is None or not os.path.exists(path):
+        return None
+    m = re.search(r"^counters: workload=(\S+) kernel=k_dedisp_shared lds_active_clocks=(\d+) "
+                  r"dedisp_src_sha256=([0-9a-f]{64})$", open(path).read(), re.M)
+    if not m or m.group(1) != workload or dedisp_source_hash() != m.group(3):
+        return None
+    return int(m.group(2))
+
+
+def dedisp_kernels(batch):
+    """The dedispersion kernel of every beam of a batch."""
+    kernel = {}
+    for b, p in enumerate(batch.plans):
+        if id(p) not in kernel:
+            t = batch.tiles(b)
+            direct = (t["dm_per_wave"], t["time_groups"], t["waves"]) == (4, 1, 4)
+            kernel[id(p)] = ("k_dedisp_direct" if direct else
+                             "k_dedisp" if batch.shared_delays(b) is None else "k_dedisp_shared")
+    return [kernel[id(p)] for p in batch.plans]
+
+
 def corner_turn_leg(spl, plan, reps=12, nbuf=4):
     """Corner turn of blocks of the workload's first plan (time-major spectra in,
     channel-major rows out): HIP-event time per launch and the achieved bytes/s, with
@@ -564,10 +591,11 @@ def uneven_leg(spl, W, args, steps=5, warmup=2, seed=4):
     """The 32-beam uneven batch (16 beams of the 2048-channel 300-500 MHz plan, 16 of the
     4096-channel 550-750 MHz plan with 3072 trials), blocks made on the GPU with the
     workload's recipe (ten pulses, 2 % RFI channels, zero-DM bursts; torch's noise), one
-    persistent graph launch with autotuned tiles: ms per step, throughput, the
-    dedispersion launch against the add peak, and per band the plain path against the
-    ranker path on the step's candidates (recall and false alarms of the injected pulses,
-    at the ranker's own operating point and at the plain path's false-alarm count)."""
+    persistent graph launch with autotuned tiles: ms per step, throughput, the rate of the
+    plain sum's adds with the kernels that stand for them, and per band the plain path
+    against the ranker path on the step's candidates (recall and false alarms of the
+    injected pulses, at the ranker's own operating point and at the plain path's
+    false-alarm count)."""
     import tempfile
 
     import numpy as np
@@ -621,7 +649,7 @@ def uneven_leg(spl, W, args, steps=5, warmup=2, seed=4):
            "value": sum(p.info["ndm"] * p.info["n_out"] for p in plans) / (ms / 1e3),
            "unit": "DM-trial·samples/s", "real_time_factor": ms / 1e3 / block_s,
            "dedisp_ms_per_step": dd_ms / steps, "dedisp_adds_per_s": adds / (dd_ms / steps / 1e3),
-           "dedisp_frac_add_peak": adds / (dd_ms / steps / 1e3) / PEAK_ADDS,
+           "dedisp_kernels": {f"{p.info['nchans']}ch": k for p, k in zip(plans[:2], dedisp_kernels(batch))},
            "tiles": {f"{p.info['nchans']}ch": batch.tiles(b) for b, p in ((0, plans[0]), (1, plans[1]))},
            "candidates": st["n_candidates"], "hits": st["n_hits"], "hit_overflow": st["hit_overflow"],
            "cand_overflow": st["cand_overflow"]}
@@ -823,6 +851,18 @@ def main():
                      "peak_two_adds_per_lane": 2 * PEAK_ADDS / 1e12,
                      "frac_two_adds_per_lane": achieved / (2 * PEAK_ADDS)},
     }
+    kernels = sorted(set(dedisp_kernels(batch)))
+    out["roofline"]["kernel"] = " + ".join(kernels)
+    if "k_dedisp_shared" in kernels:
+        # This kernel does not make the plain sum's adds, so their rate is no rate of it: of the
+        # resources that it takes, the LDS is the nearest to its peak that a count stands for (clocks
+        # in which an LDS is active, counted; 256 CUs x 2.4 GHz).  adds_per_launch stay the plain sum's.
+        clocks = counted_lds_clocks(args.workload, [batch.tiles(b) for b in range(nb)])
+        rate = None if clocks is None or launches_per_step != 1 else clocks / avg_launch_s / 1e9
+        r = out["roofline"]
+        r.update({"bound": "lds", "achieved": rate, "peak": 256 * 2.4, "unit": "G LDS clocks/s",
+                  "frac": None if rate is None else rate / (256 * 2.4), "plain_sum_tadds_per_s": achieved / 1e12})
+        del r["peak_two_adds_per_lane"], r["frac_two_adds_per_lane"]
     tr = counter_traffic(args.workload, [batch.tiles(b) for b in range(nb)])
     if tr is not None and launches_per_step == 1:
         out["roofline"]["traffic"] = tr["fetch_bytes"] + tr["write_bytes"]
