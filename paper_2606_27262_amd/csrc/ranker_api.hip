@@ -2,8 +2,8 @@
 // master parameters into the BF16 GEMM operands (and scatter GEMM weight gradients
 // back), and the launch sequence of a forward pass, a backward pass and an Adam step.
 //
-// Per batch of Nb candidates (Nb = max_batch rounded up to 32; a pass over fewer
-// candidates pads with zero images whose gradients are zero):
+// Per batch of Nb candidates (Nb = max_batch rounded up to 32; a training pass over fewer
+// candidates pads with zero images whose gradients are zero, a scoring pass does not):
 //   layer k = 1..4, input H_k x W_k (64x256, 32x128, 16x64, 8x32), Cin_k (2, 32, 32, 32),
 //   P_k = Nb*H_k*W_k output pixels, K_k = 9*Cin_k padded to a multiple of 32 (32, 288):
 //     X_k, arg_k = maxpool(ReLU(conv(X_{k-1}, Wp_k) + b_k))   NHWC BF16, one kernel: the
